@@ -1711,6 +1711,19 @@ int cs_segment(cs_ctx *ctx, const float *rgb, int H, int W, const float *loglik,
         for (int v = 0; v < 5; ++v) o_state[b][v] = (v < 4 || mdl) ? cv.take(plane) : 0;
     const size_t o_m = cv.take(sizeof(double) * (size_t)(prm->iterations + 1) * L);
     const size_t o_ms = cv.take(sizeof(double) * (size_t)(prm->iterations + 1) * L);
+    PdArgs a{};
+    a.H = H;
+    a.W = W;
+    a.L = L;
+    a.iters = prm->iterations;
+    a.mdl = mdl ? 1 : 0;
+    a.N = N;
+    // FP32 with few labels: tiles held on chip over several iterations
+    const bool tiled = prm->precision == CS_FP32 && L <= kPdTileLabels;
+    const int S = tiled ? pd_tile_steps(lc_of(ctx), a) : 1;
+    const int rows = tiled ? pd_resident_rows(lc_of(ctx), a) : 0;
+    const size_t o_ex = rows ? cv.take(sizeof(uint64_t) * pd_resident_words(a, rows)) : 0;
+    const size_t o_mp = tiled && mdl ? cv.take(sizeof(double) * 2 * L * (size_t)pd_tiles(a, S)) : 0;
     if ((rc = ensure_ws(ctx, cv.off))) return rc;
     char *ws = ctx->ws;
     double *small = (double *)(ws + o_small);
@@ -1721,13 +1734,6 @@ int cs_segment(cs_ctx *ctx, const float *rgb, int H, int W, const float *loglik,
     rc = edge_weight_stage(ctx, rgb, H, W, prm->gamma, prm->precision, ws + o_g, nullptr, (double *)(ws + o_mag),
                            (double *)(ws + o_part), small, &gamma);
     if (rc) return rc;
-    PdArgs a{};
-    a.H = H;
-    a.W = W;
-    a.L = L;
-    a.iters = prm->iterations;
-    a.mdl = mdl ? 1 : 0;
-    a.N = N;
     a.lambda = prm->lambda;
     a.nu = prm->nu;
     // diagonal preconditioning (alpha = 1) with the interior column sums
@@ -1746,17 +1752,32 @@ int cs_segment(cs_ctx *ctx, const float *rgb, int H, int W, const float *loglik,
     }
     a.mval = (double *)(ws + o_m);
     a.msum = (double *)(ws + o_ms);
+    a.mpart = (double *)(ws + o_mp);
+    a.exch = (uint64_t *)(ws + o_ex);
     {
         Timed t(ctx, "pd_init");
         HIP_TRY(launch_pd_init(lc, a, prm->precision, loglik));
     }
-    for (int it = 0; it < prm->iterations; ++it) {
+    int buf = 0, it = 0;
+    if (rows) {
         Timed t(ctx, "pd_iter");
-        HIP_TRY(launch_pd_iter(lc, a, prm->precision, it));
+        if (launch_pd_resident(lc, a, rows) == hipSuccess) {
+            buf = 1;
+            it = prm->iterations;
+        }
     }
+    const bool one_launch = it > 0;
+    for (; it < prm->iterations; it += S, buf ^= 1) {
+        Timed t(ctx, "pd_iter");
+        if (tiled)
+            HIP_TRY(launch_pd_tile(lc, a, it, buf, S, std::min(S, prm->iterations - it)));
+        else
+            HIP_TRY(launch_pd_iter(lc, a, prm->precision, it));
+    }
+    if (tiled && mdl && !one_launch && prm->iterations > 0) HIP_TRY(launch_pd_msum(lc, a, S));
     {
         Timed t(ctx, "pd_finish");
-        HIP_TRY(launch_pd_finish(lc, a, prm->precision, labels, u, used, (double *)(ws + o_part),
+        HIP_TRY(launch_pd_finish(lc, a, prm->precision, buf, labels, u, used, (double *)(ws + o_part),
                                  stats ? small + 1 : nullptr));
     }
     if (stats) {

@@ -405,6 +405,8 @@ struct PdArgs {
     void *u[2], *ub[2], *px[2], *py[2], *mu[2];
     double *mval;            // (iters + 1) x L: m^t
     double *msum;            // (iters + 1) x L: sum_x mu^t (zero before)
+    uint64_t *exch;          // resident form: the tiles' exchange words (pd_resident_words)
+    double *mpart;           // tile launches with a label cost: 2 x L x tiles sums of mu
 };
 // |grad I| into mag (N doubles), per-workgroup partial sums into part
 // (ceil(N / 256) doubles), then g in the working precision (g, N values) and/or
@@ -418,8 +420,24 @@ hipError_t launch_edge_weight(const LaunchCtx &lc, const float *rgb, int H, int 
 // (3 + L) doubles of scratch).
 hipError_t launch_pd_init(const LaunchCtx &lc, const PdArgs &a, int precision, const float *loglik);
 hipError_t launch_pd_iter(const LaunchCtx &lc, const PdArgs &a, int precision, int t);
-hipError_t launch_pd_finish(const LaunchCtx &lc, const PdArgs &a, int precision, int32_t *labels, float *u_out,
-                            unsigned long long *used, double *part, double *energies);
+// buf: the buffer of the state after the last iteration
+hipError_t launch_pd_finish(const LaunchCtx &lc, const PdArgs &a, int precision, int buf, int32_t *labels,
+                            float *u_out, unsigned long long *used, double *part, double *energies);
+// Tile form of the iteration (k_pd_tile.hip), FP32 and at most kPdTileLabels
+// labels: iterations t .. t + steps - 1 (steps <= S) from buffer cur into the
+// other one, S the iterations per launch that pd_tile_steps chose, and with a
+// label cost the sums of mu after the last iteration (msum).
+constexpr int kPdTileLabels = 16;
+int pd_tile_steps(const LaunchCtx &lc, const PdArgs &a);
+int64_t pd_tiles(const PdArgs &a, int S);
+hipError_t launch_pd_tile(const LaunchCtx &lc, const PdArgs &a, int t, int cur, int S, int steps);
+// Resident form (every iteration in one cooperative launch, state in buffer 1
+// afterwards): the rows of its tiles, 0 where the image does not fit; its
+// exchange words; the launch (an error leaves the start state as it was).
+int pd_resident_rows(const LaunchCtx &lc, const PdArgs &a);
+size_t pd_resident_words(const PdArgs &a, int th);
+hipError_t launch_pd_resident(const LaunchCtx &lc, const PdArgs &a, int th);
+hipError_t launch_pd_msum(const LaunchCtx &lc, const PdArgs &a, int S);
 
 // ---- unsupervised data term (k_unsup.hip) ----
 constexpr int kUnsupMaxClasses = 16;  // colour or texture classes

@@ -20,7 +20,8 @@
 // threads, so the same values) instead of waiting for them, which keeps an
 // iteration to one launch with ping-pong buffers.  The pixel's L candidate
 // values stay in registers for the simplex projection (Michelot's finite
-// algorithm).  The m update needs sum_x mu^{t+1} over the whole image: the
+// algorithm).  FP32 with up to 16 labels runs on tiles held on chip instead
+// (k_pd_tile.hip); the kernels here take FP64 and more labels.  The m update needs sum_x mu^{t+1} over the whole image: the
 // launch adds it up (one FP64 atomic per label and workgroup) and the next
 // launch applies it.
 //
@@ -688,23 +689,27 @@ static void pd_iter_launch(const LaunchCtx &lc, const PdArgs &a, int t) {
             hipLaunchKernelGGL((k_pd_dual<T, true>), g2, dim3(256), 0, lc.stream, a, t, nb);
         else
             hipLaunchKernelGGL((k_pd_dual<T, false>), g2, dim3(256), 0, lc.stream, a, t, nb);
-        if (a.L <= 16)
-            hipLaunchKernelGGL((k_pd_primal<T, 16>), grid, dim3(256), 0, lc.stream, a, t);
-        else
-            hipLaunchKernelGGL((k_pd_primal<T, 64>), grid, dim3(256), 0, lc.stream, a, t);
+        // (FP32 with at most 16 labels takes the tile form)
+        if constexpr (sizeof(T) == 8)
+            if (a.L <= 16) {
+                hipLaunchKernelGGL((k_pd_primal<T, 16>), grid, dim3(256), 0, lc.stream, a, t);
+                return;
+            }
+        hipLaunchKernelGGL((k_pd_primal<T, 64>), grid, dim3(256), 0, lc.stream, a, t);
         return;
     }
-    if (a.L <= 16) {
-        if (a.mdl)
-            hipLaunchKernelGGL((k_pd_iter<T, 16, true>), grid, dim3(256), 0, lc.stream, a, t);
-        else
-            hipLaunchKernelGGL((k_pd_iter<T, 16, false>), grid, dim3(256), 0, lc.stream, a, t);
-    } else {
-        if (a.mdl)
-            hipLaunchKernelGGL((k_pd_iter<T, 64, true>), grid, dim3(256), 0, lc.stream, a, t);
-        else
-            hipLaunchKernelGGL((k_pd_iter<T, 64, false>), grid, dim3(256), 0, lc.stream, a, t);
-    }
+    if constexpr (sizeof(T) == 8)
+        if (a.L <= 16) {
+            if (a.mdl)
+                hipLaunchKernelGGL((k_pd_iter<T, 16, true>), grid, dim3(256), 0, lc.stream, a, t);
+            else
+                hipLaunchKernelGGL((k_pd_iter<T, 16, false>), grid, dim3(256), 0, lc.stream, a, t);
+            return;
+        }
+    if (a.mdl)
+        hipLaunchKernelGGL((k_pd_iter<T, 64, true>), grid, dim3(256), 0, lc.stream, a, t);
+    else
+        hipLaunchKernelGGL((k_pd_iter<T, 64, false>), grid, dim3(256), 0, lc.stream, a, t);
 }
 
 hipError_t launch_pd_iter(const LaunchCtx &lc, const PdArgs &a, int precision, int t) {
@@ -716,10 +721,9 @@ hipError_t launch_pd_iter(const LaunchCtx &lc, const PdArgs &a, int precision, i
 }
 
 template <typename T>
-static hipError_t pd_finish(const LaunchCtx &lc, const PdArgs &a, int32_t *labels, float *u_out,
+static hipError_t pd_finish(const LaunchCtx &lc, const PdArgs &a, int buf, int32_t *labels, float *u_out,
                             unsigned long long *used, double *part, double *energies) {
     const unsigned nb = (unsigned)((a.N + 255) / 256);
-    const int buf = a.iters & 1;
     hipLaunchKernelGGL(k_pd_labels<T>, dim3(nb), dim3(256), 0, lc.stream, a, buf, labels, u_out, used);
     if (energies) {
         hipLaunchKernelGGL(k_pd_energy<T>, dim3(nb), dim3(256), 0, lc.stream, a, buf, labels, part);
@@ -728,10 +732,10 @@ static hipError_t pd_finish(const LaunchCtx &lc, const PdArgs &a, int32_t *label
     return hipGetLastError();
 }
 
-hipError_t launch_pd_finish(const LaunchCtx &lc, const PdArgs &a, int precision, int32_t *labels, float *u_out,
-                            unsigned long long *used, double *part, double *energies) {
-    if (precision == CS_FP64) return pd_finish<double>(lc, a, labels, u_out, used, part, energies);
-    return pd_finish<float>(lc, a, labels, u_out, used, part, energies);
+hipError_t launch_pd_finish(const LaunchCtx &lc, const PdArgs &a, int precision, int buf, int32_t *labels,
+                            float *u_out, unsigned long long *used, double *part, double *energies) {
+    if (precision == CS_FP64) return pd_finish<double>(lc, a, buf, labels, u_out, used, part, energies);
+    return pd_finish<float>(lc, a, buf, labels, u_out, used, part, energies);
 }
 
 }  // namespace cs
