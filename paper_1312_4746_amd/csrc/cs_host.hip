@@ -1821,14 +1821,15 @@ int cs_unsupervised_loglik(cs_ctx *ctx, const float *rgb, int H, int W, const ui
     HIP_TRY(hipSetDevice(ctx->device));
     if ((rc = check_inputs_finite(ctx, rgb, 3 * N, nullptr, 0, 0))) return rc;
     const int nw = (k + 63) / 64;
-    const int64_t nb = (N + 255) / 256;
     Carve cv;
     const size_t o_cc = cv.take(sizeof(double) * Kc * 3);
     const size_t o_tc = cv.take(sizeof(uint64_t) * Kt * nw);
     const size_t o_cl = cv.take(sizeof(int32_t) * (size_t)N);
     const size_t o_tl = cv.take(sizeof(int32_t) * (size_t)N);
-    const size_t o_cp = cv.take(sizeof(double) * (size_t)nb * Kc * 4);
-    const size_t o_tn = cv.take(sizeof(unsigned int) * ((size_t)Kt * k + Kt));
+    const size_t parts = (size_t)unsup_parts(N);
+    const size_t o_cp = cv.take(sizeof(double) * parts * Kc * 4);
+    const size_t o_tp = cv.take(sizeof(unsigned int) * parts * Kt * nw * 64);
+    const size_t o_tn = cv.take(sizeof(unsigned int) * parts * Kt);
     if ((rc = ensure_ws(ctx, cv.off))) return rc;
     UnsupArgs a{};
     a.rgb = rgb;
@@ -1847,20 +1848,14 @@ int cs_unsupervised_loglik(cs_ctx *ctx, const float *rgb, int H, int W, const ui
     a.clab = colour_labels ? colour_labels : (int32_t *)(ctx->ws + o_cl);
     a.tlab = texture_labels ? texture_labels : (int32_t *)(ctx->ws + o_tl);
     a.cpart = (double *)(ctx->ws + o_cp);
-    a.tcount = (unsigned int *)(ctx->ws + o_tn);
-    a.tsize = a.tcount + (size_t)Kt * k;
+    a.tpart = (unsigned int *)(ctx->ws + o_tp);
+    a.tsize = (unsigned int *)(ctx->ws + o_tn);
     const LaunchCtx lc = lc_of(ctx);
-    HIP_TRY(launch_fill_u32(lc, a.tcount, (size_t)Kt * k + Kt, 0u));
     HIP_TRY(launch_unsup_init(lc, a, init));
     {
-        Timed t(ctx, "kmeans");
-        for (int it = 0; it < prm->iterations; ++it) HIP_TRY(launch_kmeans_step(lc, a, true));
-        HIP_TRY(launch_kmeans_step(lc, a, false));
-    }
-    {
-        Timed t(ctx, "kmedians");
-        for (int it = 0; it < prm->iterations; ++it) HIP_TRY(launch_kmedians_step(lc, a, true));
-        HIP_TRY(launch_kmedians_step(lc, a, false));
+        Timed t(ctx, "cluster");
+        for (int it = 0; it < prm->iterations; ++it) HIP_TRY(launch_unsup_step(lc, a, true));
+        HIP_TRY(launch_unsup_step(lc, a, false));
     }
     Timed t(ctx, "unsup_loglik");
     HIP_TRY(launch_unsup_loglik(lc, a, loglik));

@@ -450,17 +450,19 @@ struct UnsupArgs {
     double *ccent;          // Kc x 3 colour centroids
     uint64_t *tcent;        // Kt x nw texture centroids
     int32_t *clab, *tlab;   // N colour and texture classes
-    double *cpart;          // ceil(N / 256) x Kc x 4 partial sums
-    unsigned int *tcount;   // Kt x k bit counts (zero before an assignment with counts)
-    unsigned int *tsize;    // Kt class sizes (idem)
+    // per-workgroup partials of an assignment (unsup_parts(N) workgroups)
+    double *cpart;          // Kc x 4 x parts colour sums and counts
+    unsigned int *tpart;    // parts x Kt nw 64 bit counts
+    unsigned int *tsize;    // Kt x parts class sizes
 };
 struct UnsupInit {
     int32_t pix[2 * kUnsupMaxClasses];  // pixels of the first centroids: Kc colour, then Kt texture
 };
 hipError_t launch_unsup_init(const LaunchCtx &lc, const UnsupArgs &a, const UnsupInit &init);
-// One assignment (and, with update, the centroids moved to their classes).
-hipError_t launch_kmeans_step(const LaunchCtx &lc, const UnsupArgs &a, bool update);
-hipError_t launch_kmedians_step(const LaunchCtx &lc, const UnsupArgs &a, bool update);
+// One assignment of both clusterings (and, with update, the centroids moved to
+// their classes).
+int unsup_parts(int64_t N);
+hipError_t launch_unsup_step(const LaunchCtx &lc, const UnsupArgs &a, bool update);
 hipError_t launch_unsup_loglik(const LaunchCtx &lc, const UnsupArgs &a, float *loglik);
 
 // ---- learned surrogate (k_mlp.hip) ----
