@@ -1704,6 +1704,7 @@ int cs_segment(cs_ctx *ctx, const float *rgb, int H, int W, const float *loglik,
     const size_t o_mag = cv.take(sizeof(double) * (size_t)N);
     const size_t o_part = cv.take(sizeof(double) * (size_t)nb * (3 + L));
     const size_t o_small = cv.take(sizeof(double) * 8);  // gamma, energies, labels present
+    const size_t o_used = cv.take(sizeof(uint64_t) * (size_t)nb);
     const size_t o_g = cv.take(es * (size_t)N);
     const size_t o_f = cv.take(plane);
     size_t o_state[2][5];
@@ -1727,9 +1728,8 @@ int cs_segment(cs_ctx *ctx, const float *rgb, int H, int W, const float *loglik,
     if ((rc = ensure_ws(ctx, cv.off))) return rc;
     char *ws = ctx->ws;
     double *small = (double *)(ws + o_small);
-    unsigned long long *used = (unsigned long long *)(small + 4);
+    unsigned long long *used = (unsigned long long *)(ws + o_used);
     const LaunchCtx lc = lc_of(ctx);
-    HIP_TRY(launch_fill_u32(lc, (unsigned int *)used, 2, 0u));
     double gamma = 0.0;
     rc = edge_weight_stage(ctx, rgb, H, W, prm->gamma, prm->precision, ws + o_g, nullptr, (double *)(ws + o_mag),
                            (double *)(ws + o_part), small, &gamma);
@@ -1756,7 +1756,7 @@ int cs_segment(cs_ctx *ctx, const float *rgb, int H, int W, const float *loglik,
     a.exch = (uint64_t *)(ws + o_ex);
     {
         Timed t(ctx, "pd_init");
-        HIP_TRY(launch_pd_init(lc, a, prm->precision, loglik));
+        HIP_TRY(launch_pd_init(lc, a, prm->precision, loglik, !tiled || prm->iterations == 0));
     }
     int buf = 0, it = 0;
     if (rows) {

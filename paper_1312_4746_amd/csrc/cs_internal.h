@@ -413,12 +413,13 @@ struct PdArgs {
 // FP32 (g32), and the gamma used (gamma_out, device, nullable).
 hipError_t launch_edge_weight(const LaunchCtx &lc, const float *rgb, int H, int W, double gamma, double *mag,
                               double *part, int precision, void *g, float *g32, double *gamma_out);
-// Start state (and f = -loglik as planes), iteration t (reads buffer t & 1,
-// writes the other), then the labels (and u pixel-major into u_out when
-// non-null), the labels present (used, zero before) and, with energies
-// non-null, {primal, binary without label cost, dual} (part: ceil(N / 256) x
-// (3 + L) doubles of scratch).
-hipError_t launch_pd_init(const LaunchCtx &lc, const PdArgs &a, int precision, const float *loglik);
+// f = -loglik as planes and, with full, the start state; iteration t (reads
+// buffer t & 1, writes the other); then the labels (and u pixel-major into
+// u_out when non-null), the labels present per workgroup (used, ceil(N / 256)
+// words) and, with energies non-null, {primal, binary without label cost,
+// dual, labels present as a bit mask} (part: ceil(N / 256) x (3 + L) doubles
+// of scratch).
+hipError_t launch_pd_init(const LaunchCtx &lc, const PdArgs &a, int precision, const float *loglik, bool full);
 hipError_t launch_pd_iter(const LaunchCtx &lc, const PdArgs &a, int precision, int t);
 // buf: the buffer of the state after the last iteration
 hipError_t launch_pd_finish(const LaunchCtx &lc, const PdArgs &a, int precision, int buf, int32_t *labels,

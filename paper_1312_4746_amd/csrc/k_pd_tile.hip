@@ -183,9 +183,19 @@ __global__ __launch_bounds__(kTd *kTd) void k_pd_tile(PdArgs a, int t, int cur, 
     const float s_xi = (float)a.sigma_xi, s_mu = (float)a.sigma_mu, t_u = (float)a.tau_u;
 
     float u[L], ub[L], px[L], py[L], f[L], mu[MDL ? L : 1];
-    {
+    const float *F = (const float *)a.f;
+    if (t == 0) {
+        // the start state: u = u_bar = 1 / L, every multiplier 0
+#pragma unroll
+        for (int l = 0; l < L; ++l) {
+            f[l] = F[l * N + x];
+            u[l] = ub[l] = 1.0f / (float)L;
+            px[l] = py[l] = 0.0f;
+            if constexpr (MDL) mu[l] = 0.0f;
+        }
+    } else {
         const float *U = (const float *)a.u[cur], *UB = (const float *)a.ub[cur], *PX = (const float *)a.px[cur],
-                    *PY = (const float *)a.py[cur], *F = (const float *)a.f;
+                    *PY = (const float *)a.py[cur];
         const float *MU = MDL ? (const float *)a.mu[cur] : nullptr;
 #pragma unroll
         for (int l = 0; l < L; ++l) {

@@ -102,24 +102,21 @@ __global__ __launch_bounds__(256) void k_grad_mag(const float *rgb, int H, int W
 }
 
 // g(x) = exp(-|grad I| / gamma) / (2 gamma); gamma <= 0 selects the mean of
-// |grad I| (every workgroup adds the partial sums in the same order).
+// |grad I| (every workgroup adds the partial sums in the same order, all its
+// threads at once: one thread's chain over 603 partials was most of 34 us).
 template <typename T>
 __global__ __launch_bounds__(256) void k_edge_weight(const double *mag, int64_t N, const double *part, int nparts,
                                                      double gamma, T *g, float *g32, double *gamma_out) {
 #pragma clang fp contract(off)
-    __shared__ double s_gamma;
-    if (threadIdx.x == 0) {
-        double gm = gamma;
-        if (!(gm > 0.0)) {
-            double s = 0.0;
-            for (int i = 0; i < nparts; ++i) s = s + part[i];
-            gm = s / (double)N;
-        }
-        s_gamma = gm;
-        if (blockIdx.x == 0 && gamma_out) *gamma_out = gm;
+    __shared__ double red[4];
+    double gm = gamma;
+    if (!(gm > 0.0)) {
+        double s = 0.0;
+#pragma unroll 4
+        for (int i = threadIdx.x; i < nparts; i += 256) s = s + part[i];
+        gm = block_sum(s, red) / (double)N;
     }
-    __syncthreads();
-    const double gm = s_gamma;
+    if (blockIdx.x == 0 && threadIdx.x == 0 && gamma_out) *gamma_out = gm;
     const int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (x >= N) return;
     const double v = exp(-mag[x] / gm) / (2.0 * gm);
@@ -128,27 +125,45 @@ __global__ __launch_bounds__(256) void k_edge_weight(const double *mag, int64_t 
 }
 
 // ---- initial state and the data term ----
+// A workgroup's 256 pixels: their pixel-major rows read in order, turned in
+// LDS, written as planes; with full also the start state (the on-chip forms
+// start from it without reading it).
 template <typename T>
-__global__ __launch_bounds__(256) void k_pd_init(PdArgs a, const float *loglik) {
-    const int64_t N = a.N;
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t < (int64_t)a.L * N) {
-        const int l = (int)(t / N);
-        const int64_t x = t - (int64_t)l * N;
-        T *f = (T *)a.f, *u = (T *)a.u[0], *ub = (T *)a.ub[0];
-        T *px = (T *)a.px[0], *py = (T *)a.py[0];
-        f[t] = -(T)loglik[x * a.L + l];
-        const T u0 = (T)1 / (T)a.L;
-        u[t] = u0;
-        ub[t] = u0;
-        px[t] = (T)0;
-        py[t] = (T)0;
-        if (a.mdl) ((T *)a.mu[0])[t] = (T)0;
+__global__ __launch_bounds__(256) void k_pd_init(PdArgs a, const float *loglik, int full) {
+    extern __shared__ float s_f[];  // [L][257]
+    const int64_t N = a.N, x0 = (int64_t)blockIdx.x * 256;
+    const int L = a.L, n = (int)(N - x0 < 256 ? N - x0 : 256);
+    int px = threadIdx.x / L, l = threadIdx.x - px * L;
+    const int dp = 256 / L, dl = 256 - dp * L;
+    for (int e = threadIdx.x; e < n * L; e += 256) {
+        s_f[l * 257 + px] = loglik[x0 * L + e];
+        px += dp;
+        l += dl;
+        if (l >= L) {
+            l -= L;
+            ++px;
+        }
     }
-    if (t < (int64_t)a.L) {
-        a.mval[t] = 1.0;  // m^0 = 1 (every label present)
+    __syncthreads();
+    T *f = (T *)a.f;
+    if ((int)threadIdx.x < n)
+        for (int q = 0; q < L; ++q) f[q * N + x0 + threadIdx.x] = -(T)s_f[q * 257 + threadIdx.x];
+    if (blockIdx.x == 0 && (int)threadIdx.x < L) a.mval[threadIdx.x] = 1.0;  // m^0 = 1 (every label present)
+    if (!full) return;
+    if ((int)threadIdx.x < n) {
+        T *u = (T *)a.u[0], *ub = (T *)a.ub[0], *qx = (T *)a.px[0], *qy = (T *)a.py[0], *mu = (T *)a.mu[0];
+        const T u0 = (T)1 / (T)L;
+        for (int q = 0; q < L; ++q) {
+            const int64_t t = q * N + x0 + threadIdx.x;
+            u[t] = u0;
+            ub[t] = u0;
+            qx[t] = (T)0;
+            qy[t] = (T)0;
+            if (a.mdl) mu[t] = (T)0;
+        }
     }
-    if (a.mdl && t < (int64_t)(a.iters + 1) * a.L) a.msum[t] = 0.0;
+    if (a.mdl)
+        for (int64_t t = x0 + threadIdx.x; t < (int64_t)(a.iters + 1) * L; t += (int64_t)gridDim.x * 256) a.msum[t] = 0.0;
 }
 
 // Per-label part of an iteration at pixel x: the new dual vector xi^{t+1}(x)
@@ -496,19 +511,25 @@ __global__ __launch_bounds__(256) void k_pd_primal(PdArgs a, int t) {
     }
 }
 
-// Labels l(x) = argmax_i u_i(x) (ties to the lowest label) and u pixel-major.
+// Labels l(x) = argmax_i u_i(x) (ties to the lowest label), the labels present
+// in the workgroup (used, one word each) and u pixel-major (turned in LDS:
+// stores one row of L per lane were most of 35 us at 481 x 321).
 template <typename T>
 __global__ __launch_bounds__(256) void k_pd_labels(PdArgs a, int buf, int32_t *labels, float *u_out,
                                                    unsigned long long *used) {
-    const int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    extern __shared__ float s_u[];  // [L][257]
+    __shared__ unsigned long long s_bits[4];
+    const int64_t x0 = (int64_t)blockIdx.x * 256, x = x0 + threadIdx.x;
+    const int L = a.L, n = (int)(a.N - x0 < 256 ? a.N - x0 : 256);
     const T *U = (const T *)a.u[buf];
-    uint64_t bit = 0;
+    unsigned long long bit = 0;
     if (x < a.N) {
         int best = 0;
         T bv = U[x];
-        for (int l = 0; l < a.L; ++l) {
+#pragma unroll 4
+        for (int l = 0; l < L; ++l) {
             const T v = U[(int64_t)l * a.N + x];
-            if (u_out) u_out[x * a.L + l] = (float)v;
+            if (u_out) s_u[l * 257 + threadIdx.x] = (float)v;
             if (v > bv) {
                 bv = v;
                 best = l;
@@ -517,135 +538,144 @@ __global__ __launch_bounds__(256) void k_pd_labels(PdArgs a, int buf, int32_t *l
         labels[x] = best;
         bit = 1ull << best;
     }
-    // labels present: OR over the wave, one atomic per wave
     for (int off = 32; off >= 1; off >>= 1) bit |= __shfl_xor(bit, off);
-    if ((threadIdx.x & 63) == 0 && bit) atomicOr(used, (unsigned long long)bit);
+    if ((threadIdx.x & 63) == 0) s_bits[threadIdx.x >> 6] = bit;
+    __syncthreads();
+    if (threadIdx.x == 0) used[blockIdx.x] = s_bits[0] | s_bits[1] | s_bits[2] | s_bits[3];
+    if (!u_out) return;
+    int px = threadIdx.x / L, l = threadIdx.x - px * L;
+    const int dp = 256 / L, dl = 256 - dp * L;
+    for (int e = threadIdx.x; e < n * L; e += 256) {
+        u_out[x0 * L + e] = s_u[l * 257 + px];
+        px += dp;
+        l += dl;
+        if (l >= L) {
+            l -= L;
+            ++px;
+        }
+    }
 }
 
-// Per-workgroup partial energies in FP64: [0] the relaxed primal data and
-// boundary terms, [1] the binary energy without the label cost, [2] the dual
-// pixel terms, then L maxima of u_i (for the label-cost term of the primal).
+// Per-workgroup partial energies in FP64, row q of part (workgroup b at
+// [q nb + b]): [0] the relaxed primal data and boundary terms, [1] the binary
+// energy without the label cost, [2] the dual pixel terms, then L maxima of
+// u_i (for the label-cost term of the primal).  A wave without a gradient of
+// u_i takes no root for it, and the roots of the binary differences are 0, 1
+// and sqrt 2.
 template <typename T>
 __global__ __launch_bounds__(256) void k_pd_energy(PdArgs a, int buf, const int32_t *labels, double *part) {
 #pragma clang fp contract(off)
     __shared__ double red[4];
+    __shared__ double s_max[4][kMaxLabels];
     const int64_t N = a.N;
     const int H = a.H, W = a.W, L = a.L;
     const int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const bool in = x < N;
     const int c = in ? (int)(x % W) : 0, r = in ? (int)(x / W) : 0;
+    const bool mx = in && c < W - 1, my = in && r < H - 1, hasl = in && c > 0, hasu = in && r > 0;
+    const int64_t xc = in ? x : 0, xr = mx ? x + 1 : xc, xd = my ? x + W : xc, xl = hasl ? x - 1 : xc,
+                  xu = hasu ? x - W : xc;
     const T *U = (const T *)a.u[buf], *PX = (const T *)a.px[buf], *PY = (const T *)a.py[buf];
     const T *F = (const T *)a.f, *G = (const T *)a.g;
     const T *MU = a.mdl ? (const T *)a.mu[buf] : nullptr;
-    double prim = 0.0, bin = 0.0, dual = 0.0;
-    if (in) {
-        const double hg = 0.5 * a.lambda * (double)G[x];
-        const int lx = labels[x];
-        const int lr = c < W - 1 ? labels[x + 1] : lx, ld = r < H - 1 ? labels[x + W] : lx;
-        double dmin = 0.0;
-        for (int l = 0; l < L; ++l) {
-            const int64_t o = (int64_t)l * N + x;
-            const double u = (double)U[o];
-            const double dx = c < W - 1 ? (double)U[o + 1] - u : 0.0;
-            const double dy = r < H - 1 ? (double)U[o + W] - u : 0.0;
-            prim = prim + (u * (double)F[o] + hg * sqrt(dx * dx + dy * dy));
-            // binary segmentation: indicator of label l at x, x + 1, x + W
-            const double bx = (double)(lr == l) - (double)(lx == l), by = (double)(ld == l) - (double)(lx == l);
-            bin = bin + hg * sqrt(bx * bx + by * by);
-            // dual: f - div xi (- mu)
-            double d = c < W - 1 ? (double)PX[o] : 0.0;
-            if (c > 0) d = d - (double)PX[o - 1];
-            if (r < H - 1) d = d + (double)PY[o];
-            if (r > 0) d = d - (double)PY[o - W];
-            double q = -d + (double)F[o];
-            if (a.mdl) q = q - (double)MU[o];
-            dmin = l == 0 ? q : (q < dmin ? q : dmin);
+    double prim = 0.0, bin = 0.0, dual = 0.0, dmin = 0.0;
+    const double hg = 0.5 * a.lambda * (double)G[xc];
+    const int lx = labels[xc], lr = labels[xr], ld = labels[xd];
+#pragma unroll 2
+    for (int l = 0; l < L; ++l) {
+        const int64_t o = (int64_t)l * N;
+        const double u = (double)U[o + xc], f = (double)F[o + xc];
+        const double ur = (double)U[o + xr], ud = (double)U[o + xd];
+        const double pc = (double)PX[o + xc], pl = (double)PX[o + xl], qc = (double)PY[o + xc],
+                     qu = (double)PY[o + xu], m = a.mdl ? (double)MU[o + xc] : 0.0;
+        const double dx = mx ? ur - u : 0.0, dy = my ? ud - u : 0.0;
+        double root = 0.0;
+        if (__any(dx != 0.0 || dy != 0.0)) root = sqrt(dx * dx + dy * dy);
+        prim = prim + (u * f + hg * root);
+        // binary segmentation: indicator of label l at x, x + 1, x + W
+        const int two = ((lr == l) != (lx == l)) + ((ld == l) != (lx == l));
+        bin = bin + hg * (two == 0 ? 0.0 : two == 1 ? 1.0 : 1.4142135623730951);
+        // dual: f - div xi (- mu)
+        double d = mx ? pc : 0.0;
+        if (hasl) d = d - pl;
+        if (my) d = d + qc;
+        if (hasu) d = d - qu;
+        double q = -d + f;
+        if (a.mdl) q = q - m;
+        dmin = l == 0 ? q : (q < dmin ? q : dmin);
+        if (a.mdl) {
+            T v = in ? (T)u : (T)0;
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) {
+                const T w = __shfl_xor(v, off);
+                v = v < w ? w : v;
+            }
+            if ((threadIdx.x & 63) == 0) s_max[threadIdx.x >> 6][l] = (double)v;
         }
+    }
+    if (in) {
         bin = bin + (double)F[(int64_t)lx * N + x];
         dual = dmin;
+    } else {
+        prim = bin = 0.0;
     }
     double t0 = block_sum(prim, red);
     double t1 = block_sum(bin, red);
     double t2 = block_sum(dual, red);
-    const int64_t stride = 3 + L;
+    const int64_t nb = gridDim.x;
     if (threadIdx.x == 0) {
-        part[blockIdx.x * stride + 0] = t0;
-        part[blockIdx.x * stride + 1] = t1;
-        part[blockIdx.x * stride + 2] = t2;
+        part[blockIdx.x] = t0;
+        part[nb + blockIdx.x] = t1;
+        part[2 * nb + blockIdx.x] = t2;
     }
-    if (a.mdl) {
-        for (int l = 0; l < L; ++l) {
-            double m = in ? (double)U[(int64_t)l * N + x] : 0.0;
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) m = fmax(m, __shfl_xor(m, off));
-            __syncthreads();
-            if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-            __syncthreads();
-            if (threadIdx.x == 0)
-                part[blockIdx.x * stride + 3 + l] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
-        }
+    if (a.mdl && (int)threadIdx.x < L) {
+        const int l = threadIdx.x;
+        part[(3 + l) * nb + blockIdx.x] = fmax(fmax(s_max[0][l], s_max[1][l]), fmax(s_max[2][l], s_max[3][l]));
     }
 }
 
-// The partial energies added in workgroup order (one workgroup); for a label
-// cost also m^T, the label-cost terms and sum_i min(0, nu + sum_x mu_i).
-// out: {primal, binary (without the label cost), dual}
-__global__ __launch_bounds__(64) void k_pd_energy_final(PdArgs a, const double *part, int nparts, double *out) {
+// The partial energies added in a fixed order (one workgroup, a wave per row:
+// lanes strided, then a butterfly); for a label cost also the label-cost terms
+// and sum_i min(0, nu + sum_x mu_i).  out: {primal, binary (without the label
+// cost), dual}, then the labels present as a bit mask.
+__global__ __launch_bounds__(1024) void k_pd_energy_final(PdArgs a, const double *part, const unsigned long long *used,
+                                                         int nparts, double *out) {
 #pragma clang fp contract(off)
-    // lane i sums the parts of its contiguous chunk in order (loads eight at a
-    // time), then lane 0 adds the 64 lane sums in order: a fixed order
-    __shared__ double s3[3][64];
-    __shared__ double smx[64];
-    const int lane = threadIdx.x;
-    const int L = a.L;
-    const int64_t stride = 3 + L;
-    const int per = (nparts + 63) / 64, i0 = lane * per, i1 = i0 + per < nparts ? i0 + per : nparts;
-    double p = 0.0, b = 0.0, d = 0.0;
-    for (int i = i0; i < i1; i += 8) {
-        double v[8][3];
+    __shared__ double s_row[3 + kMaxLabels];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int L = a.L, rows = 3 + (a.mdl ? L : 0);
+    for (int q = wave; q < rows; q += 16) {
+        const double *p = part + (int64_t)q * nparts;
+        const bool mx = q >= 3;
+        double v = mx ? -INFINITY : 0.0;
+#pragma unroll 8
+        for (int i = lane; i < nparts; i += 64) v = mx ? fmax(v, p[i]) : v + p[i];
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-#pragma unroll
-            for (int q = 0; q < 3; ++q) v[u][q] = i + u < i1 ? part[(int64_t)(i + u) * stride + q] : 0.0;
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (i + u < i1) {
-                p = p + v[u][0];
-                b = b + v[u][1];
-                d = d + v[u][2];
-            }
+        for (int off = 32; off >= 1; off >>= 1) {
+            const double w = __shfl_xor(v, off);
+            v = mx ? fmax(v, w) : v + w;
+        }
+        if (lane == 0) s_row[q] = v;
     }
-    s3[0][lane] = p;
-    s3[1][lane] = b;
-    s3[2][lane] = d;
+    if (wave == 15) {
+        unsigned long long bits = 0;
+#pragma unroll 8
+        for (int i = lane; i < nparts; i += 64) bits |= used[i];
+        for (int off = 32; off >= 1; off >>= 1) bits |= __shfl_xor(bits, off);
+        if (lane == 0) *reinterpret_cast<unsigned long long *>(out + 3) = bits;
+    }
     __syncthreads();
-    double mdl_p = 0.0, mdl_d = 0.0;
-    if (a.mdl) {
-        for (int l = 0; l < L; ++l) {
-            double mx = -INFINITY;
-            for (int i = i0; i < i1; ++i) mx = fmax(mx, part[(int64_t)i * stride + 3 + l]);
-            smx[lane] = mx;
-            __syncthreads();
-            if (lane == 0) {
-                double m2 = smx[0];
-                for (int q = 1; q < 64; ++q) m2 = fmax(m2, smx[q]);
-                mdl_p = mdl_p + a.nu * m2;
+    if (threadIdx.x == 0) {
+        double mdl_p = 0.0, mdl_d = 0.0;
+        if (a.mdl)
+            for (int l = 0; l < L; ++l) {
+                mdl_p = mdl_p + a.nu * s_row[3 + l];
                 const double sl = a.nu + a.msum[(int64_t)a.iters * L + l];
                 mdl_d = mdl_d + (sl < 0.0 ? sl : 0.0);
             }
-            __syncthreads();
-        }
-    }
-    if (lane == 0) {
-        double pp = 0.0, bb = 0.0, dd = 0.0;
-        for (int q = 0; q < 64; ++q) {
-            pp = pp + s3[0][q];
-            bb = bb + s3[1][q];
-            dd = dd + s3[2][q];
-        }
-        out[0] = pp + mdl_p;
-        out[1] = bb;
-        out[2] = dd + mdl_d;
+        out[0] = s_row[0] + mdl_p;
+        out[1] = s_row[1];
+        out[2] = s_row[2] + mdl_d;
     }
 }
 
@@ -668,14 +698,13 @@ hipError_t launch_edge_weight(const LaunchCtx &lc, const float *rgb, int H, int 
     return hipGetLastError();
 }
 
-hipError_t launch_pd_init(const LaunchCtx &lc, const PdArgs &a, int precision, const float *loglik) {
-    int64_t n = (int64_t)a.L * a.N;
-    if (n < (int64_t)(a.iters + 1) * a.L) n = (int64_t)(a.iters + 1) * a.L;
-    const dim3 grid((unsigned)((n + 255) / 256));
+hipError_t launch_pd_init(const LaunchCtx &lc, const PdArgs &a, int precision, const float *loglik, bool full) {
+    const dim3 grid((unsigned)((a.N + 255) / 256));
+    const size_t lds = sizeof(float) * 257 * (size_t)a.L;
     if (precision == CS_FP64)
-        hipLaunchKernelGGL(k_pd_init<double>, grid, dim3(256), 0, lc.stream, a, loglik);
+        hipLaunchKernelGGL(k_pd_init<double>, grid, dim3(256), lds, lc.stream, a, loglik, full ? 1 : 0);
     else
-        hipLaunchKernelGGL(k_pd_init<float>, grid, dim3(256), 0, lc.stream, a, loglik);
+        hipLaunchKernelGGL(k_pd_init<float>, grid, dim3(256), lds, lc.stream, a, loglik, full ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -724,10 +753,11 @@ template <typename T>
 static hipError_t pd_finish(const LaunchCtx &lc, const PdArgs &a, int buf, int32_t *labels, float *u_out,
                             unsigned long long *used, double *part, double *energies) {
     const unsigned nb = (unsigned)((a.N + 255) / 256);
-    hipLaunchKernelGGL(k_pd_labels<T>, dim3(nb), dim3(256), 0, lc.stream, a, buf, labels, u_out, used);
+    hipLaunchKernelGGL(k_pd_labels<T>, dim3(nb), dim3(256), u_out ? sizeof(float) * 257 * (size_t)a.L : 0, lc.stream,
+                       a, buf, labels, u_out, used);
     if (energies) {
         hipLaunchKernelGGL(k_pd_energy<T>, dim3(nb), dim3(256), 0, lc.stream, a, buf, labels, part);
-        hipLaunchKernelGGL(k_pd_energy_final, dim3(1), dim3(64), 0, lc.stream, a, part, (int)nb, energies);
+        hipLaunchKernelGGL(k_pd_energy_final, dim3(1), dim3(1024), 0, lc.stream, a, part, used, (int)nb, energies);
     }
     return hipGetLastError();
 }

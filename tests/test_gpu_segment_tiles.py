@@ -31,3 +31,15 @@ def test_radii_beyond_the_short_root_and_quotient(ctx):  # noqa: F811
         _check(ctx, w.rgb, ll, lam, 0.0, 20, "fp32")
     w.rgb[:, :, 35:] *= 0.01
     _check(ctx, w.rgb, ll, 1.0, 0.0, 20, "fp32")
+
+
+@pytest.mark.parametrize("H,W,L,nu,prec", [(23, 29, 64, 0.0, "fp32"), (33, 40, 63, 4.0, "fp64"), (16, 16, 33, 2.0, "fp32"),
+                                           (257, 3, 16, 5.0, "fp32")])
+def test_start_and_finish_at_the_label_limits(ctx, H, W, L, nu, prec):  # noqa: F811
+    """The planes turned in LDS (up to 64 labels x 256 pixels) and the energies'
+    rows, partial last workgroups among them."""
+    w = make_workload("seg_tiles", H=H, W=W, R=2, p=3, k=8, seed=19, per_region=1)
+    w.L = L
+    w.region = w.region % L
+    for iters in (0, 2):
+        _check(ctx, w.rgb, _synthetic_term(w, seed=L), 1.0, nu, iters, prec)
