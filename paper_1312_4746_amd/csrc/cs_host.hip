@@ -1282,7 +1282,7 @@ struct cs_mlp {
     int64_t t = 0;  // Adam steps taken
     char *mem = nullptr;
     float *params = nullptr, *m = nullptr, *v = nullptr;
-    short *W1b = nullptr, *W2b = nullptr, *W3b = nullptr, *W2Tb = nullptr, *W3Tb = nullptr;
+    short *W1f = nullptr, *W2f = nullptr, *W3f = nullptr, *W2Tf = nullptr, *W3Tf = nullptr;
 };
 
 namespace {
@@ -1305,11 +1305,11 @@ MlpAdamArgs mlp_adam_args(cs_mlp *n) {
     a.in = n->in;
     a.in_pad = n->in_pad;
     a.out = n->out;
-    a.W1b = n->W1b;
-    a.W2b = n->W2b;
-    a.W3b = n->W3b;
-    a.W2Tb = n->W2Tb;
-    a.W3Tb = n->W3Tb;
+    a.W1f = n->W1f;
+    a.W2f = n->W2f;
+    a.W3f = n->W3f;
+    a.W2Tf = n->W2Tf;
+    a.W3Tf = n->W3Tf;
     return a;
 }
 
@@ -1321,8 +1321,8 @@ int mlp_kc(int B) {
     return 1;
 }
 
-// One forward/backward over B rows (idx or rows 0..B-1), then the weight
-// gradients; scratch carved from the context workspace.
+// One forward/backward over B rows (idx or rows 0..B-1) and what the gradient
+// launch takes from it; scratch carved from the context workspace.
 int mlp_backprop(cs_ctx *ctx, cs_mlp *n, const float *x, const float *ell, const int32_t *idx, int64_t n_rows,
                  int B, MlpAdamArgs &ad) {
     const int kc = mlp_kc(B);
@@ -1336,7 +1336,6 @@ int mlp_backprop(cs_ctx *ctx, cs_mlp *n, const float *x, const float *ell, const
     const size_t o_dz1 = cv.take(sizeof(short) * (size_t)kMlpHid * B);
     const size_t o_bg = cv.take(sizeof(float) * (size_t)ntiles * kMlpBiasStride);
     const size_t o_lp = cv.take(sizeof(float) * (size_t)ntiles);
-    const size_t o_gp = cv.take(sizeof(float) * (size_t)kc * n->P);
     int rc = ensure_ws(ctx, cv.off);
     if (rc) return rc;
     MlpTrainArgs t{};
@@ -1348,11 +1347,11 @@ int mlp_backprop(cs_ctx *ctx, cs_mlp *n, const float *x, const float *ell, const
     t.in = n->in;
     t.in_pad = n->in_pad;
     t.out = n->out;
-    t.W1b = n->W1b;
-    t.W2b = n->W2b;
-    t.W3b = n->W3b;
-    t.W2Tb = n->W2Tb;
-    t.W3Tb = n->W3Tb;
+    t.W1f = n->W1f;
+    t.W2f = n->W2f;
+    t.W3f = n->W3f;
+    t.W2Tf = n->W2Tf;
+    t.W3Tf = n->W3Tf;
     t.b1 = n->params + n->off_b1;
     t.b2 = n->params + n->off_b2;
     t.b3 = n->params + n->off_b3;
@@ -1364,33 +1363,17 @@ int mlp_backprop(cs_ctx *ctx, cs_mlp *n, const float *x, const float *ell, const
     t.DZ1t = (short *)(ctx->ws + o_dz1);
     t.bgrad = (float *)(ctx->ws + o_bg);
     t.lossp = (float *)(ctx->ws + o_lp);
-    MlpWgradArgs w{};
-    w.Xt = t.Xt;
-    w.H1t = t.H1t;
-    w.H2t = t.H2t;
-    w.DYt = t.DYt;
-    w.DZ2t = t.DZ2t;
-    w.DZ1t = t.DZ1t;
-    w.B = B;
-    w.in = n->in;
-    w.in_pad = n->in_pad;
-    w.out = n->out;
-    w.kc = kc;
-    w.P = n->P;
-    w.off_W1 = 0;
-    w.off_W2 = n->off_W2;
-    w.off_W3 = n->off_W3;
-    w.gpart = (float *)(ctx->ws + o_gp);
     const LaunchCtx lc = lc_of(ctx);
     {
         Timed tm(ctx, "mlp_fwdbwd");
         HIP_TRY(launch_mlp_fwdbwd(lc, t));
     }
-    {
-        Timed tm(ctx, "mlp_wgrad");
-        HIP_TRY(launch_mlp_wgrad(lc, w));
-    }
-    ad.gpart = w.gpart;
+    ad.Xt = t.Xt;
+    ad.H1t = t.H1t;
+    ad.H2t = t.H2t;
+    ad.DYt = t.DYt;
+    ad.DZ2t = t.DZ2t;
+    ad.DZ1t = t.DZ1t;
     ad.bgrad = t.bgrad;
     ad.lossp = t.lossp;
     ad.kc = kc;
@@ -1432,7 +1415,7 @@ int cs_mlp_init(cs_ctx *ctx, cs_mlp **net, int in_dim, int hidden, int out_dim, 
     Carve cv;
     const size_t o_p = cv.take(sizeof(float) * n->P), o_m = cv.take(sizeof(float) * n->P),
                  o_v = cv.take(sizeof(float) * n->P);
-    const size_t o_w1 = cv.take(sizeof(short) * kMlpHid * n->in_pad);
+    const size_t o_w1 = cv.take(sizeof(short) * kMlpHid * ((n->in_pad + 31) / 32 * 32));
     const size_t o_w2 = cv.take(sizeof(short) * kMlpHid * kMlpHid);
     const size_t o_w2t = cv.take(sizeof(short) * kMlpHid * kMlpHid);
     const size_t o_w3 = cv.take(sizeof(short) * kMlpOutPad * kMlpHid);
@@ -1444,11 +1427,11 @@ int cs_mlp_init(cs_ctx *ctx, cs_mlp **net, int in_dim, int hidden, int out_dim, 
     n->params = (float *)(n->mem + o_p);
     n->m = (float *)(n->mem + o_m);
     n->v = (float *)(n->mem + o_v);
-    n->W1b = (short *)(n->mem + o_w1);
-    n->W2b = (short *)(n->mem + o_w2);
-    n->W2Tb = (short *)(n->mem + o_w2t);
-    n->W3b = (short *)(n->mem + o_w3);
-    n->W3Tb = (short *)(n->mem + o_w3t);
+    n->W1f = (short *)(n->mem + o_w1);
+    n->W2f = (short *)(n->mem + o_w2);
+    n->W2Tf = (short *)(n->mem + o_w2t);
+    n->W3f = (short *)(n->mem + o_w3);
+    n->W3Tf = (short *)(n->mem + o_w3t);
     const LaunchCtx lc = lc_of(ctx);
     int rc = CS_OK;
     auto chk = [&](hipError_t e) {
@@ -1507,7 +1490,7 @@ int cs_mlp_grad(cs_ctx *ctx, cs_mlp *net, const float *x, const float *ell, int6
     a.grad_out = grad;
     a.loss_out = loss;
     Timed tm(ctx, "mlp_adam");
-    HIP_TRY(launch_mlp_adam(lc_of(ctx), a));
+    HIP_TRY(launch_mlp_grad_adam(lc_of(ctx), a));
     return CS_OK;
 }
 
@@ -1529,7 +1512,7 @@ int cs_mlp_train(cs_ctx *ctx, cs_mlp *net, const float *x, const float *ell, int
         a.bc2 = (float)(1.0 - std::pow(0.999, (double)net->t));
         a.loss_out = loss_trace ? loss_trace + s : nullptr;
         Timed tm(ctx, "mlp_adam");
-        HIP_TRY(launch_mlp_adam(lc_of(ctx), a));
+        HIP_TRY(launch_mlp_grad_adam(lc_of(ctx), a));
     }
     return CS_OK;
 }
@@ -1538,7 +1521,9 @@ int cs_mlp_fit_output_bias(cs_ctx *ctx, cs_mlp *net, const float *ell, int64_t n
     if (!ctx) return CS_ERR_ARG;
     if (!net || !ell || n < 1) return fail(ctx, CS_ERR_ARG, "null pointer or n < 1");
     HIP_TRY(hipSetDevice(ctx->device));
-    HIP_TRY(launch_mlp_bias_mean(lc_of(ctx), ell, n, net->out, net->params + net->off_b3));
+    int rc = ensure_ws(ctx, mlp_bias_mean_bytes(n, net->out));
+    if (rc) return rc;
+    HIP_TRY(launch_mlp_bias_mean(lc_of(ctx), ell, n, net->out, (double *)ctx->ws, net->params + net->off_b3));
     return CS_OK;
 }
 
@@ -1556,9 +1541,9 @@ static int mlp_forward_impl(cs_ctx *ctx, const cs_mlp *net, const float *x, cons
     a.in = net->in;
     a.in_pad = net->in_pad;
     a.out = net->out;
-    a.W1b = net->W1b;
-    a.W2b = net->W2b;
-    a.W3b = net->W3b;
+    a.W1f = net->W1f;
+    a.W2f = net->W2f;
+    a.W3f = net->W3f;
     a.b1 = net->params + net->off_b1;
     a.b2 = net->params + net->off_b2;
     a.b3 = net->params + net->off_b3;

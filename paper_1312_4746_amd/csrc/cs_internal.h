@@ -477,27 +477,22 @@ struct MlpTrainArgs {
     const int32_t *idx;    // B row indices, or null (row b)
     int64_t n_rows;        // rows of x and ell (indices are clamped to them)
     int B, in, in_pad, out;
-    const short *W1b, *W2b, *W3b, *W2Tb, *W3Tb;  // BF16 working copies
+    const short *W1f, *W2f, *W3f, *W2Tf, *W3Tf;  // BF16 working copies in fragment order (frag_at)
     const float *b1, *b2, *b3;
-    short *Xt, *H1t, *H2t, *DYt, *DZ2t, *DZ1t;   // feature-major [unit][B]
+    short *Xt, *H1t, *H2t, *DYt, *DZ2t, *DZ1t;   // [16-row tile][unit][16]
     float *bgrad;          // [B/16][kMlpBiasStride] per-tile bias-gradient sums
     float *lossp;          // [B/16] per-tile squared error
 };
-struct MlpWgradArgs {
-    const short *Xt, *H1t, *H2t, *DYt, *DZ2t, *DZ1t;
-    int B, in, in_pad, out, kc;
-    int64_t P, off_W1, off_W2, off_W3;
-    float *gpart;          // [kc][P]
-};
 struct MlpAdamArgs {
     float *params, *m, *v;
-    const float *gpart, *bgrad, *lossp;
+    const short *Xt, *H1t, *H2t, *DYt, *DZ2t, *DZ1t;  // of the batch (see MlpTrainArgs)
+    const float *bgrad, *lossp;
     float *grad_out;       // non-null: write the gradient, no update
     float *loss_out;       // non-null: mean loss of the batch
     int64_t P, off_b1, off_W2, off_b2, off_W3, off_b3;
-    int kc, ntiles, B, in, in_pad, out;
+    int kc, ntiles, B, in, in_pad, out;  // kc row chunks (at most 16) of ntiles / kc tiles
     float lr, bc1, bc2;    // step size, 1 - beta1^t, 1 - beta2^t
-    short *W1b, *W2b, *W3b, *W2Tb, *W3Tb;
+    short *W1f, *W2f, *W3f, *W2Tf, *W3Tf;
 };
 struct MlpInferArgs {
     const float *x;        // explicit rows x in, or null: features from rgb/alpha
@@ -505,16 +500,17 @@ struct MlpInferArgs {
     int H, W, k;
     int64_t n;
     int in, in_pad, out;
-    const short *W1b, *W2b, *W3b;
+    const short *W1f, *W2f, *W3f;
     const float *b1, *b2, *b3;
     float *y;              // n x out
 };
 hipError_t launch_mlp_fwdbwd(const LaunchCtx &lc, const MlpTrainArgs &a);
-hipError_t launch_mlp_wgrad(const LaunchCtx &lc, const MlpWgradArgs &a);
-hipError_t launch_mlp_adam(const LaunchCtx &lc, const MlpAdamArgs &a);
+hipError_t launch_mlp_grad_adam(const LaunchCtx &lc, const MlpAdamArgs &a);
 hipError_t launch_mlp_convert(const LaunchCtx &lc, const MlpAdamArgs &a);
 hipError_t launch_mlp_infer(const LaunchCtx &lc, const MlpInferArgs &a);
-hipError_t launch_mlp_bias_mean(const LaunchCtx &lc, const float *ell, int64_t n, int out, float *b3);
+// part: mlp_bias_mean_bytes of scratch
+size_t mlp_bias_mean_bytes(int64_t n, int out);
+hipError_t launch_mlp_bias_mean(const LaunchCtx &lc, const float *ell, int64_t n, int out, double *part, float *b3);
 // Exact fallback of the surrogate: pixels whose top-two outputs differ by less
 // than margin are listed (count zero before), and exact rows are put back.
 hipError_t launch_mlp_uncertain(const LaunchCtx &lc, const float *y, int64_t n, int L, float margin, int32_t *list,

@@ -14,11 +14,22 @@
 // backward pass reuses the same layout with the transposed weights as A.
 //
 // Weight gradients dW = delta^T act are reductions over the batch; the
-// forward/backward kernel stores the BF16 activations and deltas feature-major
-// ([unit][row]) so that the gradient kernel reads 4 consecutive rows per lane
-// for both MFMA operands.  Partial sums over row chunks are added in a fixed
-// order by the Adam kernel (deterministic).
+// forward/backward kernel stores the BF16 activations and deltas of each
+// 16-row tile as [unit][16 rows], so that the gradient kernel reads 4
+// consecutive rows per lane for both MFMA operands and a wave's operand is 512
+// consecutive bytes.  The gradient kernel adds its row chunks' partial sums in
+// a fixed order (deterministic) and applies Adam to them itself.
+//
+// A training step is a short serial chain (batch 4096: one 16-row tile per
+// compute unit), so what bounds it is latency, not the 0.8 GFLOP: every weight
+// fragment of the forward and backward pass is requested before the first
+// product, and the gradient's chunks meet in LDS instead of memory and a third
+// launch.  Batch 4096, 103 inputs, 10 outputs: 36 -> 17.4 us of
+// kernels per step (10.3 and 7.0; the gradient launch is bound by the 262 KB
+// that a workgroup reads through its L1 and by the trip from the other XCDs).
 #pragma clang fp contract(off)
+
+#include <type_traits>
 
 #include "cs_internal.h"
 #include "cs_device.h"
@@ -55,61 +66,59 @@ __device__ __forceinline__ float gelu_grad(float z) {
            z * __builtin_amdgcn_exp2f(-0.5f * 1.4426950408889634f * z * z) * 0.39894228040143268f;
 }
 
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ s16x8 ld8(const short *p) { return *reinterpret_cast<const s16x8 *>(p); }
+__device__ __forceinline__ s16x4 half8(s16x8 v, int i) {
+    return i ? s16x4{v[4], v[5], v[6], v[7]} : s16x4{v[0], v[1], v[2], v[3]};
+}
+__device__ __forceinline__ void st4(short *p, s16x4 v) { *reinterpret_cast<s16x4 *>(p) = v; }
 __device__ __forceinline__ s16x4 ld4(const short *p) { return *reinterpret_cast<const s16x4 *>(p); }
 __device__ __forceinline__ f32x4 mfma(s16x4 a, s16x4 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
 }
 
-// One 16-row tile through the three layers.  xb[ks]: the tile's inputs as
-// B fragments (features 16ks + 4g .. +3 of row j).  W1 row stride ld1, W2 and
-// W3 row stride ld2 (elements); the pointers may point to LDS or global.
-template <bool KEEP>
-__device__ __forceinline__ void mlp_tile_forward(const s16x4 (&xb)[kMlpMaxIn / 16], int nks, const short *W1,
-                                                 int ld1, const short *W2, const short *W3, int ld2,
-                                                 const float *b1, const float *b2, const float *b3, int out,
-                                                 int g, int j, float (&z1)[8][4], float (&z2)[8][4],
-                                                 s16x4 (&h2b)[8], f32x4 &y) {
-    s16x4 h1b[8];
-#pragma unroll
-    for (int hb = 0; hb < 8; ++hb) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        const short *wr = W1 + (16 * hb + j) * ld1 + 4 * g;
-        // weight fragments loaded unconditionally (clamped step), used below nks
-        s16x4 wf[kMlpMaxIn / 16];
-#pragma unroll
-        for (int ks = 0; ks < kMlpMaxIn / 16; ++ks) wf[ks] = ld4(wr + 16 * (ks < nks ? ks : nks - 1));
-#pragma unroll
-        for (int ks = 0; ks < kMlpMaxIn / 16; ++ks)
-            if (ks < nks) acc = mfma(wf[ks], xb[ks], acc);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const float z = acc[r] + b1[16 * hb + 4 * g + r];
-            if (KEEP) z1[hb][r] = z;
-            h1b[hb][r] = to_bf16(gelu(z));
-        }
-    }
-#pragma unroll
-    for (int hb = 0; hb < 8; ++hb) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        const short *wr = W2 + (16 * hb + j) * ld2 + 4 * g;
-#pragma unroll
-        for (int kb = 0; kb < 8; ++kb) acc = mfma(ld4(wr + 16 * kb), h1b[kb], acc);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const float z = acc[r] + b2[16 * hb + 4 * g + r];
-            if (KEEP) z2[hb][r] = z;
-            h2b[hb][r] = to_bf16(gelu(z));
-        }
-    }
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    const short *wr = W3 + j * ld2 + 4 * g;
-#pragma unroll
-    for (int kb = 0; kb < 8; ++kb) acc = mfma(ld4(wr + 16 * kb), h2b[kb], acc);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int o = 4 * g + r;
-        y[r] = acc[r] + (o < out ? b3[o] : 0.0f);
-    }
+// BF16 weight copies in fragment order: the A fragments of MFMA step ks of
+// the 16-row block hb, 8 bytes per lane (row 16 hb + j, columns 16 ks + 4 g ..
+// +3 for lane 16 g + j), two steps per lane side by side, so that a wave's
+// load is 1 KiB in a row (row-major weights cost a line per row and load).
+// Place of element (row, col) of a matrix with np pairs of steps per block:
+__device__ __forceinline__ int frag_at(int row, int col, int np) {
+    return (((row >> 4) * np + (col >> 5)) * 64 + ((col >> 2) & 3) * 16 + (row & 15)) * 8 + ((col >> 4) & 1) * 4 +
+           (col & 3);
+}
+// The 16 columns of W3^T (one step per block).
+__device__ __forceinline__ int frag16_at(int row, int col) {
+    return ((row >> 4) * 64 + (col >> 2) * 16 + (row & 15)) * 4 + (col & 3);
+}
+// Transposes a wave's 16 x 16 fragment within its quads: lane (g, 4 a + b)
+// gives units 4 g .. +3 of row 4 a + b and gets unit 4 g + b of rows 4 a .. +3.
+__device__ __forceinline__ s16x4 quad_transpose(s16x4 f, int lane) {
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    const u32x2 v = __builtin_bit_cast(u32x2, f);
+    auto xor1 = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xb1, 0xf, 0xf, true); };
+    auto xor2 = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4e, 0xf, 0xf, true); };
+    // pairs: even lanes keep their first unit and take the neighbour's, odd
+    // lanes the second (bytes of {other, own})
+    const uint32_t sel = lane & 1 ? 0x03020706u : 0x05040100u;
+    const uint32_t p = __builtin_amdgcn_perm(xor1(v[0]), v[0], sel), q = __builtin_amdgcn_perm(xor1(v[1]), v[1], sel);
+    const bool high = lane & 2;
+    const uint32_t o = xor2(high ? p : q);
+    return __builtin_bit_cast(s16x4, high ? u32x2{o, q} : u32x2{p, o});
+}
+
+// Sum over the 16 lanes of a row (every lane gets it), in the order of a
+// butterfly over lane bits 0, 1, 2, 3: quad permutes, then mirrors (all lanes
+// of a quad, then of an 8-group, hold the same value).
+__device__ __forceinline__ float row_sum16(float v) {
+    auto dpp = [](float x, auto ctrl) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value,
+                                                                     0xf, 0xf, true));
+    };
+    v += dpp(v, std::integral_constant<int, 0xb1>{});   // quad_perm 1 0 3 2
+    v += dpp(v, std::integral_constant<int, 0x4e>{});   // quad_perm 2 3 0 1
+    v += dpp(v, std::integral_constant<int, 0x141>{});  // row_half_mirror
+    v += dpp(v, std::integral_constant<int, 0x140>{});  // row_mirror
+    return v;
 }
 
 // ---- forward + backward of one batch (training and the gradient call) ----
@@ -117,97 +126,135 @@ __device__ __forceinline__ void mlp_tile_forward(const s16x4 (&xb)[kMlpMaxIn / 1
 // (units 32w .. 32w + 31) of both hidden layers.  A layer's MFMA result
 // fragments are the next layer's B operand for the same lane, so they pass
 // between the waves through LDS as they are (lane l's fragment of block b at
-// [b][l]).  The output layer and dY (16 outputs, one block) are computed by
-// every wave alike; wave 0 writes them.
+// [b][l]); the input blocks, loaded by the waves in turn, pass the same way.
+// The output layer and dY (16 outputs, one block) are computed by every wave
+// alike; wave 0 writes them.  With one wave per SIMD nothing hides a load, so
+// the weights of every layer (116 registers) are requested at the start.
 __global__ __launch_bounds__(256) void k_mlp_fwdbwd(MlpTrainArgs a) {
-    __shared__ s16x4 sh_h1[8][64], sh_h2[8][64], sh_dz2[8][64];
+    constexpr int kKs = kMlpMaxIn / 16;
+    __shared__ s16x4 sh_x[kKs][64], sh_h1[8][64], sh_h2[8][64], sh_dz2[8][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int g = lane >> 4, j = lane & 15;
     const int wt = blockIdx.x;  // tile
     const int b0 = wt * 16;
     if (b0 >= a.B) return;  // uniform over the workgroup
     const int rb = b0 + j;
-    int64_t row = a.idx ? (int64_t)a.idx[rb] : (int64_t)rb;
-    row = row < 0 ? 0 : (row >= a.n_rows ? a.n_rows - 1 : row);  // memory-safe on bad input
-    const int nks = a.in_pad / 16;
-    // inputs loaded unconditionally (clamped feature index: the loads are in
-    // flight together), zero past in
-    float xv[kMlpMaxIn / 16][4];
-#pragma unroll
-    for (int ks = 0; ks < kMlpMaxIn / 16; ++ks)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int f = 16 * ks + 4 * g + q;
-            xv[ks][q] = a.x[row * a.in + (f < a.in ? f : a.in - 1)];
-        }
-    s16x4 xb[kMlpMaxIn / 16];
-#pragma unroll
-    for (int ks = 0; ks < kMlpMaxIn / 16; ++ks)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) xb[ks][q] = to_bf16(16 * ks + 4 * g + q < a.in ? xv[ks][q] : 0.0f);
-    // layer 1, own blocks
-    float z1[2][4], z2[2][4];
-    s16x4 h1b[2], h2b[2];
+    const int nks = a.in_pad / 16, np = (nks + 1) / 2;
+    const int32_t *ip = a.idx ? a.idx + rb : nullptr;
+    const int32_t iv = ip ? *ip : rb;
+    // weight fragments and biases (clamped steps past nks, not used)
+    s16x8 w1[2][kKs / 2], w2[2][4], w3[4], w2t[2][4];
+    s16x4 w3t[2];
+    f32x4 bias1[2], bias2[2];
+    float bias3[4];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const int hb = 2 * wave + h;
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        const short *wr = a.W1b + (16 * hb + j) * a.in_pad + 4 * g;
-        s16x4 wf[kMlpMaxIn / 16];
 #pragma unroll
-        for (int ks = 0; ks < kMlpMaxIn / 16; ++ks) wf[ks] = ld4(wr + 16 * (ks < nks ? ks : nks - 1));
+        for (int k = 0; k < kKs / 2; ++k) w1[h][k] = ld8(a.W1f + ((hb * np + (k < np ? k : np - 1)) * 64 + lane) * 8);
 #pragma unroll
-        for (int ks = 0; ks < kMlpMaxIn / 16; ++ks)
-            if (ks < nks) acc = mfma(wf[ks], xb[ks], acc);
+        for (int k = 0; k < 4; ++k) w2[h][k] = ld8(a.W2f + ((hb * 4 + k) * 64 + lane) * 8);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w3[k] = ld8(a.W3f + (k * 64 + lane) * 8);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int hb = 2 * wave + h;
+        w3t[h] = ld4(a.W3Tf + (hb * 64 + lane) * 4);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) w2t[h][k] = ld8(a.W2Tf + ((hb * 4 + k) * 64 + lane) * 8);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            z1[h][r] = acc[r] + a.b1[16 * hb + 4 * g + r];
+            bias1[h][r] = a.b1[16 * hb + 4 * g + r];
+            bias2[h][r] = a.b2[16 * hb + 4 * g + r];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) bias3[r] = a.b3[4 * g + r < a.out ? 4 * g + r : 0];
+    __builtin_amdgcn_sched_barrier(0);  // the weights are requested before the row index is waited for
+    int64_t row = iv;
+    row = row < 0 ? 0 : (row >= a.n_rows ? a.n_rows - 1 : row);  // memory-safe on bad input
+    // inputs: this wave's blocks, four consecutive features per lane (zero
+    // past in)
+    f32x4 xv[kKs / 4];
+#pragma unroll
+    for (int q = 0; q < kKs / 4; ++q) {
+        const int f0 = 16 * (wave + 4 * q) + 4 * g;
+        const float *xr = a.x + row * a.in;
+        if (16 * (wave + 4 * q) + 16 <= a.in) {
+            __builtin_memcpy(&xv[q], xr + f0, 16);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) xv[q][r] = xr[f0 + r < a.in ? f0 + r : a.in - 1];
+        }
+    }
+    float ell[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int o = 4 * g + r;
+        ell[r] = a.ell[row * a.out + (o < a.out ? o : 0)];
+    }
+    s16x4 xo[kKs / 4];
+#pragma unroll
+    for (int q = 0; q < kKs / 4; ++q) {
+        const int ks = wave + 4 * q;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) xo[q][r] = to_bf16(16 * ks + 4 * g + r < a.in ? xv[q][r] : 0.0f);
+        sh_x[ks][lane] = xo[q];
+    }
+    __syncthreads();
+    // layer 1, own blocks
+    s16x4 xb[kKs];
+#pragma unroll
+    for (int ks = 0; ks < kKs; ++ks) xb[ks] = sh_x[ks][lane];
+    float z1[2][4], z2[2][4];
+    s16x4 h1b[2], h2b[2];
+    f32x4 acc1[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int ks = 0; ks < kKs; ++ks)
+        if (ks < nks)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) acc1[h] = mfma(half8(w1[h][ks / 2], ks & 1), xb[ks], acc1[h]);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            z1[h][r] = acc1[h][r] + bias1[h][r];
             h1b[h][r] = to_bf16(gelu(z1[h][r]));
         }
-        sh_h1[hb][lane] = h1b[h];
+        sh_h1[2 * wave + h][lane] = h1b[h];
     }
     __syncthreads();
     // layer 2, own blocks, from every block of layer 1
+    f32x4 acc2[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int kb = 0; kb < 8; ++kb) {
+        const s16x4 hf = sh_h1[kb][lane];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) acc2[h] = mfma(half8(w2[h][kb / 2], kb & 1), hf, acc2[h]);
+    }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        const int hb = 2 * wave + h;
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        const short *wr = a.W2b + (16 * hb + j) * kMlpHid + 4 * g;
-        s16x4 wf[8];
-#pragma unroll
-        for (int kb = 0; kb < 8; ++kb) wf[kb] = ld4(wr + 16 * kb);
-#pragma unroll
-        for (int kb = 0; kb < 8; ++kb) acc = mfma(wf[kb], sh_h1[kb][lane], acc);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            z2[h][r] = acc[r] + a.b2[16 * hb + 4 * g + r];
+            z2[h][r] = acc2[h][r] + bias2[h][r];
             h2b[h][r] = to_bf16(gelu(z2[h][r]));
         }
-        sh_h2[hb][lane] = h2b[h];
+        sh_h2[2 * wave + h][lane] = h2b[h];
     }
     __syncthreads();
     // output layer (every wave): y^T = W3 h2^T
     f32x4 y = {0.f, 0.f, 0.f, 0.f};
-    {
-        const short *wr = a.W3b + j * kMlpHid + 4 * g;
-        s16x4 wf[8];
 #pragma unroll
-        for (int kb = 0; kb < 8; ++kb) wf[kb] = ld4(wr + 16 * kb);
+    for (int kb = 0; kb < 8; ++kb) y = mfma(half8(w3[kb / 2], kb & 1), sh_h2[kb][lane], y);
 #pragma unroll
-        for (int kb = 0; kb < 8; ++kb) y = mfma(wf[kb], sh_h2[kb][lane], y);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int o = 4 * g + r;
-            y[r] += o < a.out ? a.b3[o] : 0.0f;
-        }
-    }
+    for (int r = 0; r < 4; ++r) y[r] += 4 * g + r < a.out ? bias3[r] : 0.0f;
     // clipped targets t = max(l, max_i l_i - 20); the row max over the four
     // lanes that share row j (lanes j, j+16, j+32, j+48)
-    float ell[4], mx = -INFINITY;
+    float mx = -INFINITY;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int o = 4 * g + r;
-        ell[r] = o < a.out ? a.ell[row * a.out + o] : -INFINITY;
+        if (4 * g + r >= a.out) ell[r] = -INFINITY;
         mx = fmaxf(mx, ell[r]);
     }
     mx = fmaxf(mx, __shfl_xor(mx, 16));
@@ -230,185 +277,206 @@ __global__ __launch_bounds__(256) void k_mlp_fwdbwd(MlpTrainArgs a) {
     s16x4 dz2b[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        const int hb = 2 * wave + h;
-        const f32x4 acc = mfma(ld4(a.W3Tb + (16 * hb + j) * kMlpOutPad + 4 * g), dyb, f32x4{0.f, 0.f, 0.f, 0.f});
+        const f32x4 acc = mfma(w3t[h], dyb, f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             dz2[h][r] = acc[r] * gelu_grad(z2[h][r]);
             dz2b[h][r] = to_bf16(dz2[h][r]);
         }
-        sh_dz2[hb][lane] = dz2b[h];
+        sh_dz2[2 * wave + h][lane] = dz2b[h];
     }
     __syncthreads();
     // dH1^T = W2^T dZ2^T, dZ1 = dH1 * GELU'(z1), own blocks
     float dz1[2][4];
+    f32x4 accd[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int hb = 2 * wave + h;
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        const short *wr = a.W2Tb + (16 * hb + j) * kMlpHid + 4 * g;
-        s16x4 wf[8];
+    for (int kb = 0; kb < 8; ++kb) {
+        const s16x4 df = sh_dz2[kb][lane];
 #pragma unroll
-        for (int kb = 0; kb < 8; ++kb) wf[kb] = ld4(wr + 16 * kb);
-#pragma unroll
-        for (int kb = 0; kb < 8; ++kb) acc = mfma(wf[kb], sh_dz2[kb][lane], acc);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) dz1[h][r] = acc[r] * gelu_grad(z1[h][r]);
+        for (int h = 0; h < 2; ++h) accd[h] = mfma(half8(w2t[h][kb / 2], kb & 1), df, accd[h]);
     }
-    // feature-major BF16 stores for the weight-gradient products (the input
-    // blocks split over the waves)
-    const int B = a.B;
-#pragma unroll
-    for (int ks = 0; ks < kMlpMaxIn / 16; ++ks)
-        if (ks < nks && (ks & 3) == wave)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) a.Xt[(int64_t)(16 * ks + 4 * g + q) * B + rb] = xb[ks][q];
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int64_t u = (int64_t)(16 * (2 * wave + h) + 4 * g + r) * B + rb;
-            a.H1t[u] = h1b[h][r];
-            a.H2t[u] = h2b[h][r];
-            a.DZ2t[u] = dz2b[h][r];
-            a.DZ1t[u] = to_bf16(dz1[h][r]);
-        }
+        for (int r = 0; r < 4; ++r) dz1[h][r] = accd[h][r] * gelu_grad(z1[h][r]);
+    // BF16 stores for the weight-gradient products, [tile][unit][row] (the
+    // input blocks split over the waves): 4 rows of a unit per lane
+    const int unit = 4 * g + (j & 3), r0 = j & 12;
+#pragma unroll
+    for (int q = 0; q < kKs / 4; ++q) {
+        const int ks = wave + 4 * q;
+        if (ks < nks)
+            st4(a.Xt + ((int64_t)wt * a.in_pad + 16 * ks + unit) * 16 + r0, quad_transpose(xo[q], lane));
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int64_t u = ((int64_t)wt * kMlpHid + 16 * (2 * wave + h) + unit) * 16 + r0;
+        s16x4 dz1b;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dz1b[r] = to_bf16(dz1[h][r]);
+        st4(a.H1t + u, quad_transpose(h1b[h], lane));
+        st4(a.H2t + u, quad_transpose(h2b[h], lane));
+        st4(a.DZ2t + u, quad_transpose(dz2b[h], lane));
+        st4(a.DZ1t + u, quad_transpose(dz1b, lane));
+    }
     // bias gradients and squared error of the tile: sums over its 16 rows (FP32)
     float *bg = a.bgrad + (int64_t)wt * kMlpBiasStride;
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < 2; ++h) {
+        f32x4 s1, s2;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            float s1 = dz1[h][r], s2 = dz2[h][r];
-#pragma unroll
-            for (int off = 1; off < 16; off <<= 1) {
-                s1 += __shfl_xor(s1, off);
-                s2 += __shfl_xor(s2, off);
-            }
-            const int u = 16 * (2 * wave + h) + 4 * g + r;
-            if (j == 0) {
-                bg[u] = s1;
-                bg[kMlpHid + u] = s2;
-            }
+            s1[r] = row_sum16(dz1[h][r]);
+            s2[r] = row_sum16(dz2[h][r]);
         }
+        if (j == 0) {
+            *reinterpret_cast<f32x4 *>(bg + 16 * (2 * wave + h) + 4 * g) = s1;
+            *reinterpret_cast<f32x4 *>(bg + kMlpHid + 16 * (2 * wave + h) + 4 * g) = s2;
+        }
+    }
     if (wave == 0) {
+        st4(a.DYt + ((int64_t)wt * kMlpOutPad + unit) * 16 + r0, quad_transpose(dyb, lane));
+        f32x4 s3;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) a.DYt[(int64_t)(4 * g + r) * B + rb] = dyb[r];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            float s3 = dy[r];
-#pragma unroll
-            for (int off = 1; off < 16; off <<= 1) s3 += __shfl_xor(s3, off);
-            if (j == 0) bg[2 * kMlpHid + 4 * g + r] = s3;
-        }
+        for (int r = 0; r < 4; ++r) s3[r] = row_sum16(dy[r]);
+        if (j == 0) *reinterpret_cast<f32x4 *>(bg + 2 * kMlpHid + 4 * g) = s3;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) sq += __shfl_xor(sq, off);
         if (lane == 0) a.lossp[wt] = sq;
     }
 }
 
-// ---- weight gradients: one wave per (16x16 output tile, row chunk) ----
-__global__ __launch_bounds__(256) void k_mlp_wgrad(MlpWgradArgs a) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int g = lane >> 4, j = lane & 15;
-    const int item = blockIdx.x * 4 + wave;
-    const int nks = a.in_pad / 16;
-    const int t1 = 8 * nks, t2 = t1 + 64, ntile = t2 + 8;
-    if (item >= ntile * a.kc) return;
-    const int tile = item % ntile, kc = item / ntile;
-    const short *Am, *Bm;
-    int hb, ib, ncols, nrows;
-    int64_t off;
-    if (tile < t1) {          // dW1 = dZ1^T X
-        hb = tile / nks; ib = tile % nks; Am = a.DZ1t; Bm = a.Xt; off = a.off_W1; ncols = a.in; nrows = kMlpHid;
-    } else if (tile < t2) {   // dW2 = dZ2^T H1
-        hb = (tile - t1) / 8; ib = (tile - t1) % 8; Am = a.DZ2t; Bm = a.H1t; off = a.off_W2; ncols = kMlpHid;
-        nrows = kMlpHid;
-    } else {                  // dW3 = dY^T H2
-        hb = 0; ib = tile - t2; Am = a.DYt; Bm = a.H2t; off = a.off_W3; ncols = kMlpHid; nrows = a.out;
-    }
-    const int B = a.B, chunk = B / a.kc, k0 = kc * chunk;
-    const short *ar = Am + (int64_t)(16 * hb + j) * B + 4 * g;
-    const short *br = Bm + (int64_t)(16 * ib + j) * B + 4 * g;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int k = k0; k < k0 + chunk; k += 16) acc = mfma(ld4(ar + k), ld4(br + k), acc);
-    float *gp = a.gpart + (int64_t)kc * a.P + off;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int rr = 16 * hb + 4 * g + r, cc = 16 * ib + j;
-        if (rr < nrows && cc < ncols) gp[(int64_t)rr * ncols + cc] = acc[r];
-    }
-}
-
-// ---- Adam (or gradient output) over the flat parameter vector ----
-// Adam update of parameter p with gradient g, and its BF16 working copies.
-__device__ void adam_update(const MlpAdamArgs &a, int64_t p, float gsum) {
+// ---- weight gradients and Adam (or gradient output) ----
+// Adam update of parameter p with gradient g from its moments and value (read
+// ahead by the caller), and its BF16 working copies.
+__device__ __forceinline__ void adam_update(const MlpAdamArgs &a, int64_t p, float gsum, float m0, float v0, float w0) {
     if (a.grad_out) {
         a.grad_out[p] = gsum;
         return;
     }
-    const float m = kAdamB1 * a.m[p] + (1.0f - kAdamB1) * gsum;
-    const float v = kAdamB2 * a.v[p] + (1.0f - kAdamB2) * gsum * gsum;
+    const float m = kAdamB1 * m0 + (1.0f - kAdamB1) * gsum;
+    const float v = kAdamB2 * v0 + (1.0f - kAdamB2) * gsum * gsum;
     a.m[p] = m;
     a.v[p] = v;
     const float mhat = m / a.bc1, vhat = v / a.bc2;
-    const float w = a.params[p] - a.lr * mhat / (sqrtf(vhat) + kAdamEps);
+    const float w = w0 - a.lr * mhat / (sqrtf(vhat) + kAdamEps);
     a.params[p] = w;
     const short wb = to_bf16(w);
     if (p < a.off_b1) {
-        const int h = (int)(p / a.in), i = (int)(p % a.in);
-        a.W1b[h * a.in_pad + i] = wb;
+        const int h = (int)p / a.in, i = (int)p - h * a.in;
+        a.W1f[frag_at(h, i, (a.in_pad + 31) / 32)] = wb;
     } else if (p >= a.off_W2 && p < a.off_b2) {
         const int h = (int)((p - a.off_W2) / kMlpHid), k = (int)((p - a.off_W2) % kMlpHid);
-        a.W2b[h * kMlpHid + k] = wb;
-        a.W2Tb[k * kMlpHid + h] = wb;
+        a.W2f[frag_at(h, k, 4)] = wb;
+        a.W2Tf[frag_at(k, h, 4)] = wb;
     } else if (p >= a.off_W3 && p < a.off_b3) {
         const int o = (int)((p - a.off_W3) / kMlpHid), h = (int)((p - a.off_W3) % kMlpHid);
-        a.W3b[o * kMlpHid + h] = wb;
-        a.W3Tb[h * kMlpOutPad + o] = wb;
+        a.W3f[frag_at(o, h, 4)] = wb;
+        a.W3Tf[frag16_at(h, o)] = wb;
     }
 }
 
 // Sum over the lanes of a wave in a fixed order (butterfly), every lane gets it.
-__device__ float wave_sum_f32(float v) {
+__device__ __forceinline__ float wave_sum_f32(float v) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
     return v;
 }
 
-// The first `wblocks` workgroups update the weights: thread p adds the kc
-// row-chunk partials of its gradient (coalesced over p).  The others take one
-// wave per bias unit (and one for the loss): each lane adds every 64th
-// per-tile partial, in a fixed order, then the wave adds its lanes.
-__global__ __launch_bounds__(256) void k_mlp_adam(MlpAdamArgs a, int wblocks) {
+// The first workgroups take one 16 x 16 tile of a weight gradient each (tiles of
+// one row block of the deltas on one XCD: workgroup w runs on XCD w mod 8):
+// wave c
+// the rows of chunk c (kc chunks, a chain of 16-row products in row order),
+// whose partial sums meet in LDS and are added in chunk order by the thread
+// that then updates the parameter.  The others add the per-tile bias
+// gradients, 16 units each, and the last one the loss.
+__global__ __launch_bounds__(1024) void k_mlp_grad_adam(MlpAdamArgs a, int wblocks) {
+    __shared__ float s_part[16][256];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if ((int)blockIdx.x < wblocks) {
-        const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-        if (p >= a.P) return;
-        const bool bias = (p >= a.off_b1 && p < a.off_W2) || (p >= a.off_b2 && p < a.off_W3) || p >= a.off_b3;
-        if (bias) return;
+        const int g = lane >> 4, j = lane & 15;
+        const int nks = a.in_pad / 16, t1 = 8 * nks, t2 = t1 + 64, tile = blockIdx.x;
+        const short *Am, *Bm;
+        int hb, ib, ncols, nrows, ua, ub;
+        int64_t off;
+        if (tile < t1) {          // dW1 = dZ1^T X
+            hb = tile % 8; ib = tile / 8; Am = a.DZ1t; Bm = a.Xt; off = 0; ncols = a.in; nrows = kMlpHid;
+            ua = kMlpHid; ub = a.in_pad;
+        } else if (tile < t2) {   // dW2 = dZ2^T H1
+            hb = (tile - t1) % 8; ib = (tile - t1) / 8; Am = a.DZ2t; Bm = a.H1t; off = a.off_W2; ncols = kMlpHid;
+            nrows = kMlpHid; ua = kMlpHid; ub = kMlpHid;
+        } else {                  // dW3 = dY^T H2
+            hb = 0; ib = tile - t2; Am = a.DYt; Bm = a.H2t; off = a.off_W3; ncols = kMlpHid; nrows = a.out;
+            ua = kMlpOutPad; ub = kMlpHid;
+        }
+        // this thread's parameter: row 16 hb + e / 16, column 16 ib + e % 16
+        const int e = threadIdx.x, rr = 16 * hb + (e >> 4), cc = 16 * ib + (e & 15);
+        const bool mine = e < 256 && rr < nrows && cc < ncols;
+        const int64_t p = off + (int64_t)rr * ncols + cc;
+        float m0 = 0.0f, v0 = 0.0f, w0 = 0.0f;
+        if (mine && !a.grad_out) {
+            m0 = a.m[p];
+            v0 = a.v[p];
+            w0 = a.params[p];
+        }
+        if (wave < a.kc) {
+            const int chunk = a.ntiles / a.kc, k0 = wave * chunk;  // in 16-row tiles
+            const short *ar = Am + ((int64_t)k0 * ua + 16 * hb + j) * 16 + 4 * g;
+            const short *br = Bm + ((int64_t)k0 * ub + 16 * ib + j) * 16 + 4 * g;
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+            int k = 0;
+            for (; k + 16 <= chunk; k += 16) {
+                s16x4 av[16], bv[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) {
+                    av[u] = ld4(ar + (int64_t)(k + u) * ua * 16);
+                    bv[u] = ld4(br + (int64_t)(k + u) * ub * 16);
+                }
+#pragma unroll
+                for (int u = 0; u < 16; ++u) acc = mfma(av[u], bv[u], acc);
+            }
+#pragma unroll 4
+            for (; k < chunk; ++k) acc = mfma(ld4(ar + (int64_t)k * ua * 16), ld4(br + (int64_t)k * ub * 16), acc);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s_part[wave][(4 * g + r) * 16 + j] = acc[r];
+        }
+        __syncthreads();
+        if (!mine) return;
         float gsum = 0.0f;
-        for (int c = 0; c < a.kc; ++c) gsum += a.gpart[(int64_t)c * a.P + p];
-        adam_update(a, p, gsum);
+        for (int c = 0; c < a.kc; ++c) gsum += s_part[c][e];
+        adam_update(a, p, gsum, m0, v0, w0);
         return;
     }
-    const int lane = threadIdx.x & 63;
-    const int u = ((int)blockIdx.x - wblocks) * 4 + (threadIdx.x >> 6);  // bias unit, or the loss
+    // 16 bias units per workgroup: thread (slot, unit) adds every 64th tile's
+    // partial from its slot on, then wave w adds the 64 slots of unit w
+    const int u0 = ((int)blockIdx.x - wblocks) * 16;
     const int nbias = 2 * kMlpHid + a.out;
-    if (u > nbias) return;
-    if (u == nbias) {
-        if (!a.loss_out) return;
+    if (u0 >= 2 * kMlpHid + kMlpOutPad) {  // the workgroup past the units: the loss
+        if (wave != 0 || !a.loss_out) return;
         float s = 0.0f;
+#pragma unroll 4
         for (int t = lane; t < a.ntiles; t += 64) s += a.lossp[t];
         s = wave_sum_f32(s);
         if (lane == 0) *a.loss_out = s / ((float)a.B * (float)a.out);
         return;
     }
-    float s = 0.0f;
-    for (int t = lane; t < a.ntiles; t += 64) s += a.bgrad[(int64_t)t * kMlpBiasStride + u];
-    s = wave_sum_f32(s);
-    if (lane != 0) return;
+    const int u = u0 + wave;
+    const bool mine = lane == 0 && u < nbias;
     const int64_t p = u < kMlpHid ? a.off_b1 + u : u < 2 * kMlpHid ? a.off_b2 + (u - kMlpHid) : a.off_b3 + (u - 2 * kMlpHid);
-    adam_update(a, p, s);
+    float m0 = 0.0f, v0 = 0.0f, w0 = 0.0f;
+    if (mine && !a.grad_out) {
+        m0 = a.m[p];
+        v0 = a.v[p];
+        w0 = a.params[p];
+    }
+    const int slot = threadIdx.x >> 4, uu = threadIdx.x & 15;
+    float s = 0.0f;
+#pragma unroll 4
+    for (int t = slot; t < a.ntiles; t += 64) s += a.bgrad[(int64_t)t * kMlpBiasStride + u0 + uu];
+    s_part[uu][slot] = s;
+    __syncthreads();
+    s = wave_sum_f32(s_part[wave][lane]);
+    if (mine) adam_update(a, p, s, m0, v0, w0);
 }
 
 // ---- exact fallback of the surrogate ----
@@ -498,15 +566,15 @@ __global__ __launch_bounds__(256) void k_mlp_convert(MlpAdamArgs a) {
     const short wb = to_bf16(a.params[p]);
     if (p < a.off_b1) {
         const int h = (int)(p / a.in), i = (int)(p % a.in);
-        a.W1b[h * a.in_pad + i] = wb;
+        a.W1f[frag_at(h, i, (a.in_pad + 31) / 32)] = wb;
     } else if (p >= a.off_W2 && p < a.off_b2) {
         const int h = (int)((p - a.off_W2) / kMlpHid), k = (int)((p - a.off_W2) % kMlpHid);
-        a.W2b[h * kMlpHid + k] = wb;
-        a.W2Tb[k * kMlpHid + h] = wb;
+        a.W2f[frag_at(h, k, 4)] = wb;
+        a.W2Tf[frag_at(k, h, 4)] = wb;
     } else if (p >= a.off_W3 && p < a.off_b3) {
         const int o = (int)((p - a.off_W3) / kMlpHid), h = (int)((p - a.off_W3) % kMlpHid);
-        a.W3b[o * kMlpHid + h] = wb;
-        a.W3Tb[h * kMlpOutPad + o] = wb;
+        a.W3f[frag_at(o, h, 4)] = wb;
+        a.W3Tf[frag16_at(h, o)] = wb;
     }
 }
 
@@ -530,7 +598,6 @@ __global__ __launch_bounds__(256) void k_mlp_convert(MlpAdamArgs a) {
 // twice the GELU (gelu2x), 12 VALU instructions each, which is what bounds
 // the kernel.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
 constexpr int kInfWaves = 12;          // waves per workgroup; two workgroups per CU (weights in LDS twice)
 constexpr int kInfBlocksPerCu = 2;
 constexpr int kInfNT = 1;              // 16-pixel tiles per wave and round (each weight fragment read feeds kInfNT products)
@@ -578,17 +645,33 @@ __global__ __launch_bounds__(64 * kInfWaves) __attribute__((amdgpu_waves_per_eu(
     const int w = rows_x ? (head ? a.in - 5 : a.in) : a.k;
     const int ld = rows_x ? a.in : a.k;
     const float *src0 = rows_x ? a.x + (head ? 5 : 0) : a.alpha;
-    for (int e = tid; e < kMlpHid * kInfIn; e += 64 * kInfWaves) {
-        const int h = e / kInfIn, c = e - h * kInfIn;
-        // network column of kernel feature c, or -1 for a zero slot
-        const int nc = !head ? (c < a.in ? c : -1) : c < w ? 5 + c : c >= kInfIn - 5 ? c - (kInfIn - 5) : -1;
-        sW1[h * kInfLd + c] = nc >= 0 ? a.W1b[h * a.in_pad + nc] : (short)0;
+    for (int e = tid; e < kMlpHid * kInfLd / 8; e += 64 * kInfWaves) *reinterpret_cast<s16x8 *>(sW1 + 8 * e) = s16x8{};
+    __syncthreads();
+    // 8 weights of a row per lane, in fragment order
+    const int np = (a.in_pad + 31) / 32;
+    for (int e = tid; e < 8 * np * 64; e += 64 * kInfWaves) {
+        const s16x8 v = ld8(a.W1f + 8 * e);
+        const int l = e & 63, blk = e >> 6, hb = blk / np, kp = blk - hb * np;
+        short *dst = sW1 + (16 * hb + (l & 15)) * kInfLd;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            // kernel feature of network column nc
+            const int nc = 32 * kp + 16 * (q >> 2) + 4 * (l >> 4) + (q & 3);
+            if (nc < a.in) dst[!head ? nc : nc < 5 ? kInfIn - 5 + nc : nc - 5] = v[q];
+        }
     }
     // the hidden layers hold twice their activations (gelu2x): halved weights
-    for (int e = tid; e < kMlpHid * kMlpHid; e += 64 * kInfWaves)
-        sW2[(e / kMlpHid) * kInfLd + e % kMlpHid] = half_bf16(a.W2b[e]);
-    for (int e = tid; e < kMlpOutPad * kMlpHid; e += 64 * kInfWaves)
-        sW3[(e / kMlpHid) * kInfLd + e % kMlpHid] = half_bf16(a.W3b[e]);
+    auto stage = [&](short *dst0, const short *src, int blocks) {
+        for (int e = tid; e < blocks * 4 * 64; e += 64 * kInfWaves) {
+            const s16x8 v = ld8(src + 8 * e);
+            const int l = e & 63, blk = e >> 6;
+            short *dst = dst0 + (16 * (blk >> 2) + (l & 15)) * kInfLd + 32 * (blk & 3) + 4 * (l >> 4);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) dst[16 * (q >> 2) + (q & 3)] = half_bf16(v[q]);
+        }
+    };
+    stage(sW2, a.W2f, 8);
+    stage(sW3, a.W3f, 1);
     for (int e = tid; e < 2 * kMlpHid + kMlpOutPad; e += 64 * kInfWaves)
         sb[e] = e < kMlpHid ? a.b1[e] : e < 2 * kMlpHid ? a.b2[e - kMlpHid] : (e - 2 * kMlpHid < a.out ? a.b3[e - 2 * kMlpHid] : 0.f);
     __syncthreads();
@@ -762,27 +845,51 @@ __global__ __launch_bounds__(256) void k_mlp_features(const float *rgb, int H, i
 }
 
 // Output bias b3_i = mean over the rows of the clipped target
-// t_i = max(l_i, max_j l_j - 20); one workgroup per label, FP64 sum.
-__global__ __launch_bounds__(256) void k_mlp_bias_mean(const float *ell, int64_t n, int out, float *b3) {
-    __shared__ double red[256];
-    const int lab = blockIdx.x;
-    double s = 0.0;
-    for (int64_t r = threadIdx.x; r < n; r += 256) {
-        float mx = -INFINITY;
-        for (int o = 0; o < out; ++o) mx = fmaxf(mx, ell[r * out + o]);
-        s += (double)fmaxf(ell[r * out + lab], mx - kClipNats);
+// t_i = max(l_i, max_j l_j - 20), FP64 sums: per workgroup (a thread takes a
+// row's every label, so a row is read once; one workgroup per label read every
+// row 16 times over, 35 us for 8192 rows), then the workgroups' sums in a
+// fixed order.
+__global__ __launch_bounds__(256) void k_mlp_target_sums(const float *ell, int64_t n, int out, double *part) {
+    __shared__ double red[4][kMlpOutPad];
+    double s[kMlpOutPad];
+#pragma unroll
+    for (int o = 0; o < kMlpOutPad; ++o) s[o] = 0.0;
+    for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < n; r += (int64_t)gridDim.x * 256) {
+        float v[kMlpOutPad];
+#pragma unroll
+        for (int o = 0; o < kMlpOutPad; ++o) v[o] = ell[r * out + (o < out ? o : 0)];
+        float mx = v[0];
+#pragma unroll
+        for (int o = 1; o < kMlpOutPad; ++o) mx = fmaxf(mx, v[o]);
+#pragma unroll
+        for (int o = 0; o < kMlpOutPad; ++o) s[o] += (double)fmaxf(v[o], mx - kClipNats);
     }
-    red[threadIdx.x] = s;
+#pragma unroll
+    for (int o = 0; o < kMlpOutPad; ++o) {
+        if (o >= out) continue;
+        double t = s[o];
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) t += __shfl_xor(t, off);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][o] = t;
+    }
     __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if (threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) b3[lab] = (float)(red[0] / (double)n);
+    const int o = threadIdx.x;
+    if (o < out) part[(int64_t)o * gridDim.x + blockIdx.x] = ((red[0][o] + red[1][o]) + red[2][o]) + red[3][o];
+}
+__global__ __launch_bounds__(64) void k_mlp_bias_mean(const double *part, int nparts, int64_t n, float *b3) {
+    double s = 0.0;
+    for (int i = threadIdx.x; i < nparts; i += 64) s += part[(int64_t)blockIdx.x * nparts + i];
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+    if (threadIdx.x == 0) b3[blockIdx.x] = (float)(s / (double)n);
 }
 
-hipError_t launch_mlp_bias_mean(const LaunchCtx &lc, const float *ell, int64_t n, int out, float *b3) {
-    hipLaunchKernelGGL(k_mlp_bias_mean, dim3((unsigned)out), dim3(256), 0, lc.stream, ell, n, out, b3);
+static unsigned target_parts(int64_t n) { return (unsigned)(n < 256 * 256 ? (n + 255) / 256 : 256); }
+size_t mlp_bias_mean_bytes(int64_t n, int out) { return sizeof(double) * (size_t)out * target_parts(n); }
+hipError_t launch_mlp_bias_mean(const LaunchCtx &lc, const float *ell, int64_t n, int out, double *part, float *b3) {
+    const unsigned parts = target_parts(n);
+    hipLaunchKernelGGL(k_mlp_target_sums, dim3(parts), dim3(256), 0, lc.stream, ell, n, out, part);
+    hipLaunchKernelGGL(k_mlp_bias_mean, dim3((unsigned)out), dim3(64), 0, lc.stream, part, (int)parts, n, b3);
     return hipGetLastError();
 }
 
@@ -791,16 +898,10 @@ hipError_t launch_mlp_fwdbwd(const LaunchCtx &lc, const MlpTrainArgs &a) {
     hipLaunchKernelGGL(k_mlp_fwdbwd, dim3((unsigned)tiles), dim3(256), 0, lc.stream, a);
     return hipGetLastError();
 }
-hipError_t launch_mlp_wgrad(const LaunchCtx &lc, const MlpWgradArgs &a) {
-    const int ntile = 8 * (a.in_pad / 16) + 64 + 8;
-    const int items = ntile * a.kc;
-    hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)((items + 3) / 4)), dim3(256), 0, lc.stream, a);
-    return hipGetLastError();
-}
-hipError_t launch_mlp_adam(const LaunchCtx &lc, const MlpAdamArgs &a) {
-    const int wblocks = (int)((a.P + 255) / 256);
-    const int bblocks = (2 * kMlpHid + a.out + 1 + 3) / 4;  // one wave per bias unit and one for the loss
-    hipLaunchKernelGGL(k_mlp_adam, dim3((unsigned)(wblocks + bblocks)), dim3(256), 0, lc.stream, a, wblocks);
+hipError_t launch_mlp_grad_adam(const LaunchCtx &lc, const MlpAdamArgs &a) {
+    const int wblocks = 8 * (a.in_pad / 16) + 64 + 8;      // 16 x 16 tiles of the three weight gradients
+    const int bblocks = (2 * kMlpHid + kMlpOutPad) / 16 + 1;  // 16 bias units each, then the loss
+    hipLaunchKernelGGL(k_mlp_grad_adam, dim3((unsigned)(wblocks + bblocks)), dim3(1024), 0, lc.stream, a, wblocks);
     return hipGetLastError();
 }
 hipError_t launch_mlp_convert(const LaunchCtx &lc, const MlpAdamArgs &a) {
