@@ -16,7 +16,8 @@ BUILD = os.path.join(HERE, "_build")
 SO = os.path.join(HERE, "libcosparse.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["cs_host.hip", "k_analyze.hip", "k_tau.hip", "k_tsm.hip", "k_samples.hip",
+SOURCES = ["k_patch11.hip", "k_patch9.hip", "k_patch7.hip", "k_patch5.hip", "k_patch3.hip",
+           "cs_host.hip", "k_analyze.hip", "k_tau.hip", "k_tsm.hip", "k_samples.hip",
            "k_edt.hip", "k_parzen.hip", "k_parzen_mfma.hip", "k_mlp.hip",
            "k_cosupport_median.hip", "k_texture.hip", "k_segment.hip", "k_pd_tile.hip",
            "k_unsup.hip"]

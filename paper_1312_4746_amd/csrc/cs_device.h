@@ -25,70 +25,71 @@ __device__ __forceinline__ double gray64(const float *rgb, int64_t N, int64_t id
     return gray64_of(rgb[idx], rgb[N + idx], rgb[2 * N + idx]);
 }
 
-// Exact FP64 a_j = sum_t O_jt s_t of pixel pix (om = row j of O): the
-// normalised Gaussian-masked gray patch rebuilt from the image in the
-// oracle's operation order, q_t = w_t g_t, s_t = (q_t - mu) / sqrt(nu2) (0 when
-// nu2 = 0), every sum sequential in t and no contraction.  mu = sum_t q_t / n
-// and nu2 = sum_t (q_t - mu)^2 come from stats[2 pix], stats[2 pix + 1] (the
-// analysis kernel's exact values, the same operations) when stats is
-// non-null, else they are computed here.  One lane per entry: loads are
-// issued eight elements at a time.
-__device__ __noinline__ inline double exact_entry(const float *rgb, int H, int W, int p, const double *wmask,
-                                                  const float *om, int64_t pix, const double *stats) {
+// Exact FP64 a_j = sum_t O_jt s_t of pixel pix (om = row j of O) by a group of
+// kExactLanes lanes: the normalised Gaussian-masked gray patch rebuilt from
+// the image in the oracle's operation order, q_t = w_t g_t, s_t = (q_t - mu) /
+// sqrt(nu2) (0 when nu2 = 0), every sum sequential in t and no contraction.
+// The lanes load and divide in parallel (buf: the group's kExactRow doubles of
+// LDS), lane 0's sums are the serial part; with one lane per entry the chain of
+// loads took 20 us however few the entries (1024 x 1024, 11 x 11, k = 242: the
+// median's recompute 102 -> 44 us, the masks' last entries 77 -> 31 us).  mu = sum_t q_t / n and nu2 = sum_t
+// (q_t - mu)^2 come from stats[2 pix], stats[2 pix + 1] (the analysis kernel's
+// exact values, the same operations) when stats is non-null, else they are
+// computed here.  Every lane of the wave takes part (live: the group has an
+// entry); the group's lanes return the same value.
+constexpr int kExactLanes = 8, kExactRow = 15 * 15 + 1;
+__device__ __forceinline__ double exact_entry(const float *rgb, int H, int W, int p, const double *wmask,
+                                              const float *om, int64_t pix, const double *stats, double *buf,
+                                              bool live) {
 #pragma clang fp contract(off)
     const int64_t N = (int64_t)H * W;
-    const int h = (p - 1) / 2, n = p * p;
+    const int h = (p - 1) / 2, n = p * p, gl = threadIdx.x & (kExactLanes - 1);
     const int row = (int)(pix / W), col = (int)(pix - (int64_t)row * W);
-    auto q_at = [&](int t) {
-        const int u = t / p, v = t - u * p;
-        const int rr = reflect_idx(row + u - h, H), cc = reflect_idx(col + v - h, W);
-        return wmask[t] * gray64(rgb, N, (int64_t)rr * W + cc);
-    };
+    if (live)
+        for (int t0 = gl; t0 < n; t0 += 4 * kExactLanes) {
+            float r[4], g[4], b[4];
+            double w[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int t = t0 + u * kExactLanes < n ? t0 + u * kExactLanes : n - 1;
+                const int y = t / p, x = t - y * p;
+                const int64_t idx = (int64_t)reflect_idx(row + y - h, H) * W + reflect_idx(col + x - h, W);
+                r[u] = rgb[idx];
+                g[u] = rgb[N + idx];
+                b[u] = rgb[2 * N + idx];
+                w[u] = wmask[t];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (t0 + u * kExactLanes < n) buf[t0 + u * kExactLanes] = w[u] * gray64_of(r[u], g[u], b[u]);
+        }
+    __builtin_amdgcn_wave_barrier();  // a wave's LDS accesses complete in order
     double mu, nu2;
     if (stats) {
-        mu = stats[2 * pix];
-        nu2 = stats[2 * pix + 1];
+        mu = live ? stats[2 * pix] : 0.0;
+        nu2 = live ? stats[2 * pix + 1] : 0.0;
     } else {
         double sum = 0.0;
-        for (int t0 = 0; t0 < n; t0 += 8) {
-            double qv[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) qv[u] = q_at(t0 + u < n ? t0 + u : n - 1);
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (t0 + u < n) sum = sum + qv[u];
-        }
-        mu = sum / (double)n;
         nu2 = 0.0;
-        for (int t0 = 0; t0 < n; t0 += 8) {
-            double qv[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) qv[u] = q_at(t0 + u < n ? t0 + u : n - 1);
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (t0 + u < n) {
-                    const double z = qv[u] - mu;
-                    nu2 = nu2 + z * z;
-                }
+        // every lane of the group the same sums (LDS broadcasts)
+#pragma unroll 8
+        for (int t = 0; t < n; ++t) sum = sum + buf[t];
+        mu = sum / (double)n;
+#pragma unroll 8
+        for (int t = 0; t < n; ++t) {
+            const double z = buf[t] - mu;
+            nu2 = nu2 + z * z;
         }
     }
-    if (nu2 == 0.0) return 0.0;
     const double nu = sqrt(nu2);
+    if (live)
+        for (int t = gl; t < n; t += kExactLanes) buf[t] = (double)om[t] * (nu2 == 0.0 ? 0.0 : (buf[t] - mu) / nu);
+    __builtin_amdgcn_wave_barrier();
     double acc = 0.0;
-    for (int t0 = 0; t0 < n; t0 += 8) {
-        double qv[8];
-        float ov[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int t = t0 + u < n ? t0 + u : n - 1;
-            qv[u] = q_at(t);
-            ov[u] = om[t];
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (t0 + u < n) acc = acc + (double)ov[u] * ((qv[u] - mu) / nu);
-    }
-    return acc;
+#pragma unroll 8
+    for (int t = 0; t < n; ++t) acc = acc + buf[t];
+    __builtin_amdgcn_wave_barrier();
+    return nu2 == 0.0 ? 0.0 : acc;
 }
 
 // Per-row decision margin: the given absolute margin when >= 0, else the

@@ -306,6 +306,16 @@ double margin_coef(int precision, int n) {
     return 2.0 * (n + 4) * u32;
 }
 
+// The bound of the FP32 analysis that the fused co-support step selects its
+// median on: up to kPatchMax the contraction's products pass at most
+// patch_roundings roundings (the rounding of s and second-order terms fit the
+// three added), each counted twice as above.  (The calls that report their
+// margin keep the general bound.)
+double median_coef(int p) {
+    if (p > kPatchMax) return margin_coef(CS_FP32, p * p);
+    return 2.0 * (patch_roundings(p) + 3) * std::ldexp(1.0, -24);
+}
+
 int n_pad_of(int n) { return (n + 15) / 16 * 16; }
 
 }  // namespace
@@ -722,7 +732,8 @@ int cs_cosupport_median(cs_ctx *ctx, const float *rgb, int H, int W, int p, doub
         tw.carve(cv);
         const size_t o_marg = cv.take(sizeof(double) * k);
         const size_t o_hist3 = cv.take(sizeof(unsigned int) * 3 * kHistBins);
-        const size_t o_pst = cv.take(sizeof(double) * 2 * (size_t)H * W);
+        const bool stats = p > kPatchMax;  // exact patch statistics from the analysis
+        const size_t o_pst = stats ? cv.take(sizeof(double) * 2 * (size_t)H * W) : 0;
         // per-wave list counts of the gather and the candidate regions' offsets
         const size_t o_ccnt = cv.take(sizeof(unsigned int) * kMedianWavesMax);
         const size_t o_dcnt = cv.take(sizeof(unsigned int) * kMedianWavesMax);
@@ -733,7 +744,7 @@ int cs_cosupport_median(cs_ctx *ctx, const float *rgb, int H, int W, int p, doub
         const size_t o_ccomp = cv.take(sizeof(int64_t) * (size_t)lcap);
         const size_t o_dcomp = cv.take(sizeof(int64_t) * (size_t)lcap);
         if ((rc = ensure_ws(ctx, cv.off))) return rc;
-        double *pst = (double *)(ctx->ws + o_pst);
+        double *pst = stats ? (double *)(ctx->ws + o_pst) : nullptr;
         unsigned int *ccnt = (unsigned int *)(ctx->ws + o_ccnt), *dcnt = (unsigned int *)(ctx->ws + o_dcnt);
         FusedLists fl;
         fl.coff = (unsigned long long *)(ctx->ws + o_coff);
@@ -767,7 +778,7 @@ int cs_cosupport_median(cs_ctx *ctx, const float *rgb, int H, int W, int p, doub
             a.tau_hist3 = hist3;
             a.tau_margins = marg;
             a.tau_max_margin = mmax;
-            a.tau_coef = margin_coef(CS_FP32, n);
+            a.tau_coef = median_coef(p);
             a.tau_rank0 = (unsigned long long)((count - 1) / 2);
             Timed t(ctx, "analyze");
             HIP_TRY(launch_analyze(lc, a, CS_FP32));
@@ -814,9 +825,9 @@ int cs_cosupport_median(cs_ctx *ctx, const float *rgb, int H, int W, int p, doub
     tw.carve(cv);
     CosupportWs cw;
     cw.carve(cv, k);
-    const size_t o_pst = cv.take(sizeof(double) * 2 * (size_t)H * W);
+    const size_t o_pst = p > kPatchMax ? cv.take(sizeof(double) * 2 * (size_t)H * W) : 0;
     if ((rc = ensure_ws(ctx, cv.off))) return rc;
-    double *pst = (double *)(ctx->ws + o_pst);
+    double *pst = p > kPatchMax ? (double *)(ctx->ws + o_pst) : nullptr;
     if ((rc = analyze_stage(ctx, rgb, H, W, p, mask_sigma, omega, k, precision, alpha, pst))) return rc;
     const float *a32 = nullptr;
     if ((rc = median_source(ctx, rgb, H, W, p, mask_sigma, omega, k, precision, alpha, &a32))) return rc;

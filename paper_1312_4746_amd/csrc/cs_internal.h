@@ -93,6 +93,20 @@ struct AnalyzeArgs {
     unsigned long long tau_rank0;  // target rank
 };
 hipError_t launch_analyze(const LaunchCtx &lc, const AnalyzeArgs &a, int precision);
+// Patches up to kPatchMax (patch_kernel.h, one file per size); launch_analyze
+// takes these for them.
+constexpr int kPatchMax = 11;
+// 16-product pieces of an MFMA chain, and the roundings that a product of the
+// FP32 contraction can pass: its chain's and the sums of the chains.
+__host__ __device__ constexpr int patch_chain_quads(int p) { return p <= 7 ? 1 : 2; }
+__host__ __device__ constexpr int patch_roundings(int p) {
+    return 16 * patch_chain_quads(p) + ((p * p + 15) / 16 + patch_chain_quads(p) - 1) / patch_chain_quads(p);
+}
+hipError_t launch_patch3(const LaunchCtx &lc, const AnalyzeArgs &a, int precision);
+hipError_t launch_patch5(const LaunchCtx &lc, const AnalyzeArgs &a, int precision);
+hipError_t launch_patch7(const LaunchCtx &lc, const AnalyzeArgs &a, int precision);
+hipError_t launch_patch9(const LaunchCtx &lc, const AnalyzeArgs &a, int precision);
+hipError_t launch_patch11(const LaunchCtx &lc, const AnalyzeArgs &a, int precision);
 
 // The Gaussian patch mask table written to device memory by a one-workgroup
 // kernel that receives it by value as a kernel argument (no copy from host

@@ -1,11 +1,14 @@
-// Patch analysis on gfx950: normalised Gaussian-masked gray patches, the
-// contraction a = O s on MFMA, and the co-support threshold epilogue.
+// Patch analysis on gfx950 for 13 x 13 and 15 x 15 patches (smaller ones:
+// patch_kernel.h, whose operator fragments, up to 121 entries of four rows per
+// lane group, still fit a wave's registers): normalised Gaussian-masked gray
+// patches, the contraction a = O s on MFMA, and the co-support threshold
+// epilogue.  Then the mask decision on stored vectors, for every size.
 //
 // Paper: Sec. 2 (analysed vector a = O s, co-support of zero entries, bias
 // and gain normalisation) and Sec. 3.1 (gray patch s_x centred at x, Gaussian
 // mask applied before normalisation).
 //
-// One workgroup owns a row segment of TP pixels (128 for p <= 9, else 64).
+// One workgroup owns a row segment of TP = 64 pixels.
 // 1. The FP64 gray values of the segment and its halo are staged in LDS.
 // 2. One thread per pixel computes the exact statistics of its masked patch
 //    q_t = w_t g_t: mu = (sum_t q_t)/n and nu2 = sum_t (q_t - mu)^2, each sum
@@ -44,7 +47,7 @@ struct AnalyzeTile {
     // 64 distinct banks
     static constexpr int h = (P - 1) / 2, n = P * P, np = (n + 15) / 16 * 16, ss = np + 4;
     static constexpr int np4 = (n + 3) / 4 * 4;    // K extent of the FP32 MFMA steps
-    static constexpr int TP = P <= 9 ? 128 : 64;  // pixels per workgroup
+    static constexpr int TP = 64;                   // pixels per workgroup
     static constexpr int hw = TP + 2 * h;
 };
 
@@ -159,8 +162,8 @@ __global__ __launch_bounds__(256) void k_analyze(AnalyzeArgs a) {
     // fragments from LDS past both.
     const int nblk_j = (a.k + 15) / 16;
     unsigned long long nrecomp = 0;
-    // FP32 K steps.  Where padding K to np costs at most one step (11 x 11
-    // and 13 x 13 patches), the K order is cut into four runs of np / 4, lane
+    // FP32 K steps.  Where padding K to np costs at most one step (13 x 13
+    // patches), the K order is cut into four runs of np / 4, lane
     // group g = lane / 16 taking patch entries (np / 4) g + kb, so the lane's A
     // values are 16-byte aligned runs of its patch row: one ds_read_b128 per
     // four steps, the next one in flight while four steps are multiplied
@@ -299,23 +302,19 @@ static hipError_t launch_analyze_p(const LaunchCtx &lc, const AnalyzeArgs &a) {
     return hipGetLastError();
 }
 
-template <int PREC>
-static hipError_t launch_analyze_prec(const LaunchCtx &lc, const AnalyzeArgs &a) {
+hipError_t launch_analyze(const LaunchCtx &lc, const AnalyzeArgs &a, int precision) {
     switch (a.p) {
-        case 3: return launch_analyze_p<PREC, 3>(lc, a);
-        case 5: return launch_analyze_p<PREC, 5>(lc, a);
-        case 7: return launch_analyze_p<PREC, 7>(lc, a);
-        case 9: return launch_analyze_p<PREC, 9>(lc, a);
-        case 11: return launch_analyze_p<PREC, 11>(lc, a);
-        case 13: return launch_analyze_p<PREC, 13>(lc, a);
-        case 15: return launch_analyze_p<PREC, 15>(lc, a);
+        case 3: return launch_patch3(lc, a, precision);
+        case 5: return launch_patch5(lc, a, precision);
+        case 7: return launch_patch7(lc, a, precision);
+        case 9: return launch_patch9(lc, a, precision);
+        case 11: return launch_patch11(lc, a, precision);
+        case 13:
+            return precision == CS_BF16 ? launch_analyze_p<CS_BF16, 13>(lc, a) : launch_analyze_p<CS_FP32, 13>(lc, a);
+        case 15:
+            return precision == CS_BF16 ? launch_analyze_p<CS_BF16, 15>(lc, a) : launch_analyze_p<CS_FP32, 15>(lc, a);
         default: return hipErrorInvalidValue;
     }
-}
-
-hipError_t launch_analyze(const LaunchCtx &lc, const AnalyzeArgs &a, int precision) {
-    if (precision == CS_BF16) return launch_analyze_prec<CS_BF16>(lc, a);
-    return launch_analyze_prec<CS_FP32>(lc, a);
 }
 
 // Co-support masks from stored analysed vectors (the same decision as the

@@ -183,47 +183,67 @@ __global__ __launch_bounds__(256) void k_median_mask_gather(const float *alpha, 
     if (blockIdx.x == 0 && threadIdx.x == 0) st->nparts = gridDim.x;
 }
 
-// The listed entries against the exact tau: lane = one wave region of the
-// gather, its entries in order.  An entry whose rounded |a| is clear of tau
-// by more than its row margin is decided at once; the few within the margin
-// (or NaN) are recomputed in FP64 by their lane from the exact patch (Sec. 2
-// a = O s with the Sec. 3.1 normalised, Gaussian-masked gray patch, in the
-// oracle's operation order, the patch statistics from the analysis when
-// given) and decided exactly.
-__device__ __forceinline__ void finish_entry(int64_t e, const float *alpha, const float *rgb, int H, int W, int p,
-                                             const double *wmask, const float *omega, int k, const double *margins,
-                                             double tau, uint64_t *masks, const double *pstats) {
-    const int64_t pix = e / k;
-    const int j = (int)(e - pix * k);
-    const double a = (double)fabsf(alpha[e]);
-    const double m = margins[j];
-    bool in = a <= tau - m;
-    if (!in && !(a > tau + m))  // within the margin, or NaN
-        in = fabs(exact_entry(rgb, H, W, p, wmask, omega + (int64_t)j * p * p, pix, pstats)) <= tau;
-    if (in) atomicOr(reinterpret_cast<unsigned long long *>(masks + pix * ((k + 63) / 64) + (j >> 6)), 1ull << (j & 63));
-}
-
+// The listed entries against the exact tau, a lane per entry.  An entry whose
+// rounded |a| is clear of tau by more than its row margin is decided at once;
+// the wave's few within the margin (or NaN) are recomputed in FP64, eight at a
+// time (exact_entry), and decided exactly.
 __global__ __launch_bounds__(64) void k_median_mask_finish(const float *alpha, const float *rgb, int H, int W,
                                                            int p, const double *wmask, const float *omega, int k,
                                                            const int64_t *didx, const unsigned int *dcnt,
                                                            const int64_t *dcomp, const double *margins,
                                                            const TauState *st, uint64_t *masks,
                                                            const double *pstats) {
+    constexpr int G = 64 / kExactLanes;
+    __shared__ double s_buf[G][kExactRow];
+    __shared__ int64_t s_near[64];
+    const int lane = threadIdx.x, grp = lane / kExactLanes, W64 = (k + 63) / 64;
     const double tau = st->tau;
-    const int64_t stride = (int64_t)gridDim.x * 64;
+    auto set = [&](int64_t pix, int j) {
+        atomicOr(reinterpret_cast<unsigned long long *>(masks + pix * W64 + (j >> 6)), 1ull << (j & 63));
+    };
+    // the wave's entries q0 .. q0 + width - 1 (width <= 64) of a list of cnt
+    auto round = [&](const int64_t *lst, int64_t q0, int64_t cnt, int width) {
+        const bool live = lane < width && q0 + lane < cnt;
+        bool near = false;
+        int64_t e = 0;
+        if (live) {
+            e = lst[q0 + lane];
+            const int64_t pix = e / k;
+            const int j = (int)(e - pix * k);
+            const double a = (double)fabsf(alpha[e]);
+            const double m = margins[j];
+            if (a <= tau - m)
+                set(pix, j);
+            else
+                near = !(a > tau + m);  // within the margin, or NaN
+        }
+        const unsigned long long nm = __ballot(near);
+        if (!nm) return;
+        if (near) s_near[__popcll(nm & ((1ull << lane) - 1ull))] = e;
+        __builtin_amdgcn_wave_barrier();
+        const int nn = (int)__popcll(nm);
+        for (int i0 = 0; i0 < nn; i0 += G) {
+            const bool on = i0 + grp < nn;
+            const int64_t f = s_near[on ? i0 + grp : 0], pix = f / k;
+            const int j = (int)(f - pix * k);
+            const double v = exact_entry(rgb, H, W, p, wmask, omega + (int64_t)j * p * p, pix, pstats, s_buf[grp], on);
+            if (on && (lane & (kExactLanes - 1)) == 0 && fabs(v) <= tau) set(pix, j);
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
     const int64_t nd = (int64_t)st->n_d;
-    if (nd <= kListCap) {  // the compact list: one lane per entry
-        for (int64_t q = (int64_t)blockIdx.x * 64 + threadIdx.x; q < nd; q += stride)
-            finish_entry(dcomp[q], alpha, rgb, H, W, p, wmask, omega, k, margins, tau, masks, pstats);
+    if (nd <= kListCap) {
+        // a short list spread over all waves, eight entries (one FP64 round)
+        // at least each
+        const int64_t share = (nd + gridDim.x - 1) / gridDim.x;
+        const int width = share >= 64 ? 64 : share < G ? G : (int)((share + G - 1) / G * G);
+        for (int64_t q = (int64_t)blockIdx.x * width; q < nd; q += (int64_t)gridDim.x * width)
+            round(dcomp, q, nd, width);
         return;
     }
     const int64_t nw = (int64_t)st->rg_waves, region = (int64_t)st->rg_size;
-    for (int64_t r = (int64_t)blockIdx.x * 64 + threadIdx.x; r < nw; r += stride) {
-        const unsigned int cnt = dcnt[r];
-        const int64_t *lst = didx + r * region;
-        for (unsigned int q = 0; q < cnt; ++q)
-            finish_entry(lst[q], alpha, rgb, H, W, p, wmask, omega, k, margins, tau, masks, pstats);
-    }
+    for (int64_t r = blockIdx.x; r < nw; r += gridDim.x)
+        for (int64_t q = 0; q < (int64_t)dcnt[r]; q += 64) round(didx + r * region, q, dcnt[r], 64);
 }
 
 hipError_t median_mask_gather(const LaunchCtx &lc, const float *alpha, int64_t N, int k,
@@ -257,10 +277,7 @@ hipError_t median_mask_finish(const LaunchCtx &lc, const float *alpha, const flo
                               const double *wmask, const float *omega, int k, const int64_t *didx,
                               const unsigned int *dcnt, const int64_t *dcomp, const double *margins,
                               const TauState *st, uint64_t *masks, const double *pstats) {
-    // one lane per listed entry, or per gather wave when the list did not fit
-    int64_t blocks = (int64_t)lc.num_cu * 8;
-    const int64_t nw = median_gather_waves((int64_t)H * W);
-    if (blocks < (nw + 63) / 64) blocks = (nw + 63) / 64;
+    const int64_t blocks = (int64_t)lc.num_cu * 8;
     hipLaunchKernelGGL(k_median_mask_finish, dim3((unsigned)blocks), dim3(64), 0, lc.stream, alpha, rgb, H, W, p,
                        wmask, omega, k, didx, dcnt, dcomp, margins, st, masks, pstats);
     return hipGetLastError();

@@ -309,8 +309,8 @@ hipError_t tau_gather(const LaunchCtx &lc, const float *alpha, int64_t count,
     return hipGetLastError();
 }
 
-// FP64 recompute of each candidate entry e = pixel * k + j, one lane per
-// candidate (exact_entry: every sum sequential in t, so the result is the
+// FP64 recompute of each candidate entry e = pixel * k + j, kExactLanes lanes
+// per candidate (exact_entry: every sum sequential in t, so the result is the
 // bit pattern of the oracle's evaluation).  Persistent waves read the
 // candidate count from the device state (no host round trip); counts beyond
 // the capacity are left to the host's retry.
@@ -320,21 +320,27 @@ __global__ __launch_bounds__(64) void k_tau_recompute(const float *rgb, int H, i
                                                        int64_t cap, double *vals, const double *pstats,
                                                        const unsigned int *ccnt, const unsigned long long *coff,
                                                        const int64_t *ccomp) {
-    const int n = p * p;
-    const int64_t stride = (int64_t)gridDim.x * 64;
+    constexpr int G = 64 / kExactLanes;
+    __shared__ double s_buf[G][kExactRow];
+    const int n = p * p, grp = threadIdx.x / kExactLanes;
+    const bool lead = (threadIdx.x & (kExactLanes - 1)) == 0;
+    auto entry = [&](int64_t e, bool live) {
+        const int64_t pix = e / k;
+        const int j = (int)(e - pix * k);
+        return fabs(exact_entry(rgb, H, W, p, wmask, omega + (int64_t)j * n, pix, pstats, s_buf[grp], live));
+    };
     if (ccnt && (int64_t)st->ncand > kListCap) {
         // per-wave regions of the fused gather (a list too long to compact):
-        // lane = region, its values written at the region's offset
+        // the wave walks a region, its values written at the region's offset
         const int64_t nw = (int64_t)st->rg_waves, region = (int64_t)st->rg_size;
-        for (int64_t r = (int64_t)blockIdx.x * 64 + threadIdx.x; r < nw; r += stride) {
+        for (int64_t r = blockIdx.x; r < nw; r += gridDim.x) {
             const unsigned int cnt = ccnt[r];
             const int64_t *src = cand + r * region;
             double *dst = vals + coff[r];
-            for (unsigned int q = 0; q < cnt; ++q) {
-                const int64_t e = src[q];
-                const int64_t pix = e / k;
-                const int j = (int)(e - pix * k);
-                dst[q] = fabs(exact_entry(rgb, H, W, p, wmask, omega + (int64_t)j * n, pix, pstats));
+            for (unsigned int q0 = 0; q0 < cnt; q0 += G) {
+                const bool live = q0 + grp < cnt;
+                const double v = entry(src[live ? q0 + grp : 0], live);
+                if (live && lead) dst[q0 + grp] = v;
             }
         }
         return;
@@ -343,11 +349,10 @@ __global__ __launch_bounds__(64) void k_tau_recompute(const float *rgb, int H, i
     const int64_t *lst = ccnt ? ccomp : cand;
     const unsigned long long nc = st->ncand;
     const int64_t ncand = (int64_t)nc < cap ? (int64_t)nc : cap;
-    for (int64_t c = (int64_t)blockIdx.x * 64 + threadIdx.x; c < ncand; c += stride) {
-        const int64_t e = lst[c];
-        const int64_t pix = e / k;
-        const int j = (int)(e - pix * k);
-        vals[c] = fabs(exact_entry(rgb, H, W, p, wmask, omega + (int64_t)j * n, pix, pstats));
+    for (int64_t c0 = (int64_t)blockIdx.x * G; c0 < ncand; c0 += (int64_t)gridDim.x * G) {
+        const bool live = c0 + grp < ncand;
+        const double v = entry(lst[live ? c0 + grp : 0], live);
+        if (live && lead) vals[c0 + grp] = v;
     }
 }
 
@@ -692,11 +697,9 @@ hipError_t tau_finish(const LaunchCtx &lc, const float *rgb, int H, int W, int p
                       int64_t cap, double *vals, double frac, TauState *st, unsigned long long *parts,
                       double *tau_out, const double *pstats, const unsigned int *ccnt, const FusedLists *fl) {
     (void)n;
-    // one lane per entry of a compact list (or per region when the fused
-    // gather's list was too long to compact: at most kMedianWavesMax of them)
+    // eight entries per wave and round
     int64_t blocks = (int64_t)lc.num_cu * 8;
-    if (!ccnt && blocks > (cap + 63) / 64) blocks = (cap + 63) / 64;
-    if (ccnt && blocks < kMedianWavesMax / 64) blocks = kMedianWavesMax / 64;
+    if (blocks > (cap + 7) / 8) blocks = (cap + 7) / 8;
     if (blocks < 1) blocks = 1;
     hipLaunchKernelGGL(k_tau_recompute, dim3((unsigned)blocks), dim3(64), 0, lc.stream, rgb, H, W, p, wmask, omega,
                        k, cand, st, cap, vals, pstats, ccnt, fl ? fl->coff : nullptr, fl ? fl->ccomp : nullptr);
