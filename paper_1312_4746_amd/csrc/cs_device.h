@@ -157,8 +157,8 @@ __device__ __forceinline__ void tau_pick_digit(const unsigned int *hist, int shi
 
 // Set-up of a folded selection by one 256-thread workgroup: per-row margins
 // and their maximum, the state (digit 0: empty prefix, the target rank) and
-// three cleared histograms.
-__device__ __forceinline__ void tau_setup(TauState *st, unsigned int *hist3, const float *omega, int k, int n,
+// the cleared histograms.
+__device__ __forceinline__ void tau_setup(TauState *st, unsigned int *hist3, int hist_words, const float *omega, int k, int n,
                                           double coef, unsigned long long rank0, double *margins,
                                           double *max_margin) {
     __shared__ double red[4];
@@ -171,7 +171,7 @@ __device__ __forceinline__ void tau_setup(TauState *st, unsigned int *hist3, con
     }
     for (int off = 1; off < 64; off <<= 1) m = fmax(m, __shfl_xor(m, off));
     if ((t & 63) == 0) red[t >> 6] = m;
-    for (int i = t; i < 3 * kHistBins; i += 256) hist3[i] = 0u;
+    for (int i = t; i < hist_words; i += 256) hist3[i] = 0u;
     __syncthreads();
     if (t == 0) {
         *max_margin = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
@@ -188,6 +188,7 @@ __device__ __forceinline__ void tau_setup(TauState *st, unsigned int *hist3, con
         st->n_d = 0;
         st->n_r = 0;
         st->lo = st->hi = 0.0;
+        st->br_valid = st->br_ok = 0;
         st->median = 0.0;
         st->tau = 0.0;
     }

@@ -731,7 +731,9 @@ int cs_cosupport_median(cs_ctx *ctx, const float *rgb, int H, int W, int p, doub
         TauWs tw;
         tw.carve(cv);
         const size_t o_marg = cv.take(sizeof(double) * k);
-        const size_t o_hist3 = cv.take(sizeof(unsigned int) * 3 * kHistBins);
+        const bool bracket = count >= kBracketMin && count < ((int64_t)1 << 40);
+        const int hist_words = 3 * kHistBins + (bracket ? kBracketBins + kBracketFine : 0);
+        const size_t o_hist3 = cv.take(sizeof(unsigned int) * hist_words);
         const bool stats = p > kPatchMax;  // exact patch statistics from the analysis
         const size_t o_pst = stats ? cv.take(sizeof(double) * 2 * (size_t)H * W) : 0;
         // per-wave list counts of the gather and the candidate regions' offsets
@@ -776,12 +778,18 @@ int cs_cosupport_median(cs_ctx *ctx, const float *rgb, int H, int W, int p, doub
             a.pstats = pst;
             a.tau_st = st;
             a.tau_hist3 = hist3;
+            a.tau_hist_words = hist_words;
             a.tau_margins = marg;
             a.tau_max_margin = mmax;
             a.tau_coef = median_coef(p);
             a.tau_rank0 = (unsigned long long)((count - 1) / 2);
             Timed t(ctx, "analyze");
             HIP_TRY(launch_analyze(lc, a, CS_FP32));
+        }
+        if (bracket) {
+            Timed t(ctx, "cosupport");
+            HIP_TRY(median_bracket(lc, a32, (int64_t)H * W, k, mmax, marg, frac, st, (uint64_t *)vals, cand, ccnt, parts,
+                                   didx, dcnt, masks, hist3 + 3 * kHistBins));
         }
         {
             Timed t(ctx, "tau_select");

@@ -86,7 +86,8 @@ struct AnalyzeArgs {
     // follows (state, the three digit histograms, per-row margins); null st:
     // none
     struct TauState *tau_st;
-    unsigned int *tau_hist3;       // 3 x kHistBins, cleared
+    unsigned int *tau_hist3;       // tau_hist_words bins, cleared
+    int tau_hist_words;
     double *tau_margins;           // k per-row bounds
     double *tau_max_margin;        // their maximum
     double tau_coef;
@@ -154,12 +155,18 @@ struct TauState {
     // of the candidate and deferred lists (wave w writes from w * rg_size on)
     unsigned int rg_waves;
     long long rg_size;
+    // selection from a sampled bracket (kBracketMin): the bracket as float bits
+    // [br_lo, br_hi] and the shift of its bins; 1 in br_valid once they are
+    // set, 1 in br_ok once the median is known to lie inside (the passes of the
+    // general selection then return at once)
+    unsigned int br_lo, br_hi, br_shift, br_dbase;
+    int br_valid, br_ok;
 };
 // Upper bound of the workgroups of a candidate gather (per-workgroup counts);
 // the counts array is followed by kTauRank words for the ranks of short
 // candidate lists.
 constexpr int kTauParts = 1 << 16;
-constexpr int kTauRank = 1 << 14;
+constexpr int kTauRank = 1 << 12;
 // Radix select of the float |alpha| of the target rank; the first kernel also
 // writes the largest per-row error bound (coef) of the rows of omega, and the
 // per-row bounds to margins when non-null.
@@ -223,11 +230,25 @@ hipError_t launch_check_finite(const LaunchCtx &lc, const float *p, int64_t n, i
 // Each wave lists its candidates and the other undecided entries in its own
 // region of cand and didx (both with room for N*k entries; counts in ccnt and
 // dcnt, kMedianWavesMax words each), so the pass takes no global atomics.
-constexpr int kMedianWavesMax = 4 * kTauParts;
+constexpr int kGatherBlocks = 1024, kMedianWavesMax = 4 * kGatherBlocks;
 hipError_t median_mask_gather(const LaunchCtx &lc, const float *alpha, int64_t N, int k,
                               const double *max_margin, const double *margins, double frac, TauState *st,
                               int64_t *cand, unsigned int *ccnt, unsigned long long *parts, int64_t *didx,
                               unsigned int *dcnt, uint64_t *masks, const unsigned int *hist3);
+// The same from a sampled bracket of the median instead of its digits, for
+// calls of at least kBracketMin entries: br_hist holds kBracketBins +
+// kBracketFine cleared bins, blist room for N*k packed entries.  Afterwards
+// st->br_ok tells whether the bracket held; where it did not, the passes over
+// the digits and median_mask_gather, which return at once otherwise, have to
+// follow.
+constexpr int kBracketBins = 8192, kBracketFine = 1024;
+// (7 x 7, k = 98, whole call, digits / bracket: 8.5 M entries 121 / 125 us, 12.7 M
+// 141 / 138 us, 15.1 M 154 / 148 us, 48 M 326 / 276 us, 103 M 733 / 559 us)
+constexpr int64_t kBracketMin = (int64_t)12 << 20;
+hipError_t median_bracket(const LaunchCtx &lc, const float *alpha, int64_t N, int k, const double *max_margin,
+                          const double *margins, double frac, TauState *st, uint64_t *blist, int64_t *cand,
+                          unsigned int *ccnt, unsigned long long *parts, int64_t *didx, unsigned int *dcnt,
+                          uint64_t *masks, unsigned int *br_hist);
 // After the exact tau: the listed entries, decided in one launch (the rounded
 // value where it is clear of tau by the row margin, else in FP64).
 hipError_t median_mask_finish(const LaunchCtx &lc, const float *alpha, const float *rgb, int H, int W, int p,

@@ -22,13 +22,245 @@
 #include "cs_internal.h"
 #include "cs_device.h"
 
+// lane l of old replaced by v
+__device__ int write_lane(int v, int l, int old) __asm("llvm.amdgcn.writelane.i32");
+
 namespace cs {
 
 namespace {
 constexpr int kPx = 8;  // pixels per wave and round in the pixel-major pass
 constexpr int kRoundsPerWave = 4;
+// comparison predicates of the wave-mask builtins (LLVM's numbers)
+constexpr int kUlt = 36, kUle = 37, kOgt = 2, kOle = 5;
 
+// Listed entries of a bracket: entry in the low bits, key less a base above
+// (kPackMax: the key does not fit).
+constexpr int kPackShift = 40;
+constexpr uint32_t kPackMax = (1u << 24) - 1u;
+
+// Candidate window [v_lo - 2m, v_hi + 2m] as float bit patterns (non-negative
+// floats order like their bit patterns): an entry below it is exactly below
+// the exact median, one above it exactly above.
+__device__ __forceinline__ void candidate_window(double vlo, double vhi, double mm, TauState *st, bool record,
+                                                 uint32_t &blo, uint32_t &bhi) {
+    const double wlo = vlo - 2.0 * mm, whi = vhi + 2.0 * mm;
+    if (record) {
+        st->lo = wlo;
+        st->hi = whi;
+    }
+    float flo = (float)wlo, fhi = (float)whi;
+    if ((double)flo < wlo) flo = nextafterf(flo, INFINITY);
+    if ((double)fhi > whi) fhi = nextafterf(fhi, -INFINITY);
+    blo = wlo <= 0.0 ? 0u : __float_as_uint(flo);
+    bhi = __float_as_uint(fhi);
+}
 }  // namespace
+
+// ---- selection from a sampled bracket ----
+// For long vectors the two digit passes are left out: the median's place is
+// bracketed from a sample (2^17 entries spread over the vectors by the golden
+// ratio, ranks 0.5 +- 1/128, 5.6 deviations of independent samples), the gather
+// pass counts the entries below the bracket and lists those inside (some 1.6 %),
+// and the median's bin is picked from the list.  Where the bracket turns out
+// not to hold the median or its window (entries that the sample does not
+// represent, as rows of very different norm at a k that the spread favours), the digit passes and their gather run after all.
+// 1024 x 1024, 11 x 11, k = 242 (254 M entries): 730 us for the digit passes and
+// the gather, 336 us for sample, pass, pick and window.
+
+// Bins of the sample: 32 octaves below 2 of 256 each.
+constexpr int kSampleBlocks = 32, kSample = kSampleBlocks * 4096;
+constexpr uint32_t kBinBase = (127u - 31u) << 8;
+__global__ __launch_bounds__(1024) void k_bracket_sample(const float *alpha, int64_t count, unsigned int *hist) {
+    __shared__ unsigned int h[kBracketBins];
+    for (int i = threadIdx.x; i < kBracketBins; i += 1024) h[i] = 0u;
+    __syncthreads();
+    float v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const uint64_t i = (uint64_t)blockIdx.x * 4096 + u * 1024 + threadIdx.x;
+        const uint64_t f = i * 0x9E3779B97F4A7C15ull;  // i times the golden ratio, mod 1
+        v[u] = alpha[(int64_t)__umul64hi(f, (uint64_t)count)];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const uint32_t b = (__float_as_uint(v[u]) & 0x7FFFFFFFu) >> 15;
+        const uint32_t c = b < kBinBase ? 0u : b - kBinBase;
+        atomicAdd(&h[c < kBracketBins ? c : kBracketBins - 1], 1u);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kBracketBins; i += 1024)
+        if (h[i]) atomicAdd(&hist[i], h[i]);
+}
+
+// The bracket: the bins of the sample's ranks 0.5 -+ 1/128, widened by three
+// margins.
+__global__ __launch_bounds__(1024) void k_bracket_pick(const unsigned int *hist, const double *max_margin,
+                                                       TauState *st) {
+    constexpr int per = kBracketBins / 1024;
+    __shared__ unsigned int s_w[16], s_bin[2];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    unsigned int loc[per], sum = 0;
+#pragma unroll
+    for (int i = 0; i < per; ++i) {
+        loc[i] = hist[t * per + i];
+        sum += loc[i];
+    }
+    unsigned int incl = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const unsigned int a = __shfl_up(incl, off);
+        if (lane >= off) incl += a;
+    }
+    if (lane == 63) s_w[wave] = incl;
+    __syncthreads();
+    unsigned int before = incl - sum;
+    for (int w = 0; w < wave; ++w) before += s_w[w];
+    constexpr unsigned int r[2] = {kSample / 2 - kSample / 128, kSample / 2 + kSample / 128};
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        unsigned int acc = before;
+#pragma unroll
+        for (int i = 0; i < per; ++i) {
+            if (r[e] >= acc && r[e] < acc + loc[i]) s_bin[e] = t * per + i;
+            acc += loc[i];
+        }
+    }
+    __syncthreads();
+    if (t == 0) {
+        const unsigned int b0 = s_bin[0], b1 = s_bin[1];
+        // the outer bins hold what lies past them too
+        const double m3 = 3.0 * *max_margin;
+        const double lo = (double)__uint_as_float((b0 + kBinBase) << 15) - m3;
+        const double hi = (double)__uint_as_float((b1 + 1 + kBinBase) << 15) + m3;
+        const uint32_t blo = __float_as_uint((float)lo), bhi = __float_as_uint((float)hi);
+        const bool ok = b0 > 0 && b1 < kBracketBins - 1 && lo > 0.0 && hi < 4.0 && bhi - blo < kPackMax;
+        st->br_valid = ok ? 1 : 0;
+        if (ok) {
+            int shift = 0;
+            while (((bhi - blo) >> shift) >= (uint32_t)kBracketFine) ++shift;
+            st->br_lo = blo;
+            st->br_hi = bhi;
+            st->br_shift = shift;
+        }
+    }
+}
+
+// Histogram of the listed entries' keys within the bracket.
+__global__ __launch_bounds__(1024) void k_bracket_hist(const uint64_t *blist, const unsigned int *bcnt,
+                                                       const TauState *st, unsigned int *fine) {
+    __shared__ unsigned int h[kBracketFine];
+    if (!st->br_valid) return;
+    for (int i = threadIdx.x; i < kBracketFine; i += 1024) h[i] = 0u;
+    __syncthreads();
+    const int lane = threadIdx.x & 63, nw = (int)st->rg_waves, shift = kPackShift + (int)st->br_shift;
+    for (int r = blockIdx.x * 16 + (threadIdx.x >> 6); r < nw; r += gridDim.x * 16) {
+        const uint64_t *src = blist + r * (int64_t)st->rg_size;
+        const int n = (int)bcnt[r];
+        for (int q0 = lane; q0 < n; q0 += 4 * 64) {
+            uint64_t v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = src[q0 + 64 * u < n ? q0 + 64 * u : q0];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (q0 + 64 * u < n) atomicAdd(&h[v[u] >> shift], 1u);
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kBracketFine; i += 1024)
+        if (h[i]) atomicAdd(&fine[i], h[i]);
+}
+
+// The median's bin, the candidate window around it and its entries from the
+// list (regions as the list's); st->br_ok when the bracket holds the window.
+__global__ __launch_bounds__(256) void k_bracket_window(const uint64_t *blist, const unsigned int *bcnt,
+                                                        const unsigned int *fine, const double *max_margin,
+                                                        TauState *st, unsigned long long *parts, int nb,
+                                                        int64_t *cand, unsigned int *ccnt) {
+    __shared__ unsigned long long s_w[2][4];
+    __shared__ int s_bin;
+    if (!st->br_valid) return;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    // entries below the bracket, and the rank left inside it
+    unsigned long long below = 0, sum = 0;
+    for (int i = t; i < nb; i += 256) below += parts[i];
+    unsigned int loc[kBracketFine / 256];
+#pragma unroll
+    for (int i = 0; i < kBracketFine / 256; ++i) {
+        loc[i] = fine[t * (kBracketFine / 256) + i];
+        sum += loc[i];
+    }
+    unsigned long long incl = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const unsigned long long a = __shfl_up(incl, off);
+        if (lane >= off) incl += a;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) below += __shfl_xor(below, off);
+    if (lane == 63) {
+        s_w[0][wave] = incl;
+        s_w[1][wave] = below;
+    }
+    if (t == 0) s_bin = -1;
+    __syncthreads();
+    below = s_w[1][0] + s_w[1][1] + s_w[1][2] + s_w[1][3];
+    unsigned long long before = incl - sum;
+    for (int w = 0; w < wave; ++w) before += s_w[0][w];
+    const unsigned long long r0 = st->rank0;
+    if (r0 >= below) {
+        const unsigned long long r = r0 - below;
+        unsigned long long acc = before;
+#pragma unroll
+        for (int i = 0; i < kBracketFine / 256; ++i) {
+            if (r >= acc && r < acc + loc[i]) s_bin = t * (kBracketFine / 256) + i;
+            acc += loc[i];
+        }
+    }
+    __syncthreads();
+    const int bin = s_bin;
+    if (bin < 0) return;  // outside the bracket
+    const uint32_t blo = st->br_lo, bhi = st->br_hi, shift = st->br_shift;
+    const uint32_t klo = blo + ((uint32_t)bin << shift), khi = min(klo + (1u << shift) - 1u, bhi);
+    uint32_t wlo, whi;
+    const bool first = blockIdx.x == 0 && t == 0;
+    candidate_window((double)__uint_as_float(klo), (double)__uint_as_float(khi), *max_margin, st, first, wlo, whi);
+    if (wlo < blo || whi > bhi) return;
+    if (first) {
+        st->br_ok = 1;
+        st->nparts = nb + gridDim.x;
+    }
+    const uint32_t clo = wlo - blo, chi = whi - blo;
+    const unsigned long long lt = (1ull << lane) - 1ull;
+    const int nw = (int)st->rg_waves;
+    unsigned int low = 0;
+    for (int r = blockIdx.x * 4 + wave; r < nw; r += gridDim.x * 4) {
+        const int64_t at = r * (int64_t)st->rg_size;
+        const int n = (int)bcnt[r];
+        unsigned int nc = 0;
+        for (int q0 = 0; q0 < n; q0 += 4 * 64) {
+            uint64_t v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = blist[at + min(q0 + 64 * u + lane, n - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const bool live = q0 + 64 * u + lane < n;
+                const uint32_t d = (uint32_t)(v[u] >> kPackShift);
+                low += live && d < clo ? 1u : 0u;
+                const bool in = live && d >= clo && d <= chi;
+                const unsigned long long m = __ballot(in);
+                if (in) cand[at + nc + __popcll(m & lt)] = (int64_t)(v[u] & ((1ull << kPackShift) - 1ull));
+                nc += (unsigned int)__popcll(m);
+            }
+        }
+        if (lane == 0) ccnt[r] = nc;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) low += __shfl_xor(low, off);
+    __syncthreads();  // s_w is read above
+    if (lane == 0) s_w[0][wave] = low;
+    __syncthreads();
+    if (t == 0) parts[nb + blockIdx.x] = s_w[0][0] + s_w[0][1] + s_w[0][2] + s_w[0][3];
+}
 
 // The gather pass.  Each wave takes a contiguous run of rounds of kPx
 // consecutive pixels (about kRoundsPerWave of them, the loads of the next in
@@ -37,41 +269,50 @@ constexpr int kRoundsPerWave = 4;
 // which starts at its first entry (so it can never overflow), counted in
 // ccnt and dcnt: no global atomics.  Per workgroup the count of entries below
 // the candidate window goes to parts[blockIdx.x].
-template <int W64>
+//
+// Bound by the one reading of the vectors: 254 M entries (k = 242) in 266 us, 3.8
+// TB/s; 411 M of k = 98, a quarter of whose lanes have no row, in 522 us.  The
+// comparisons are wave masks in scalar registers, counted there, and the mask
+// words are written into their lanes: with a ballot per test and a lane compare
+// per word, vector instructions and spilled masks bound it (380 and 642 us).
+//
+// BR: the window is the whole sampled bracket [br_lo, br_hi] instead, the
+// median's bin within it being picked afterwards from the listed entries; they
+// and the undecided ones are listed with their keys (kPackShift).
+template <int W64, bool BR>
 __global__ __launch_bounds__(256) void k_median_mask_gather(const float *alpha, int64_t N, int k,
                                                             const double *max_margin, const double *margins,
                                                             double frac, TauState *st, int64_t *cand,
                                                             unsigned int *ccnt, unsigned long long *parts,
                                                             int64_t *didx, unsigned int *dcnt, uint64_t *masks,
                                                             const unsigned int *hist3) {
+    if (BR ? !st->br_valid : st->br_ok) return;
     static_assert(kPx * W64 <= 64, "one mask word per lane");
-    __shared__ unsigned long long red[256];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    // the second digit, from its complete histogram: the target rank's rounded
-    // |a| has the top 22 bits prefix, so it lies in [v_lo, v_hi] (workgroup 0
-    // records the digit)
-    unsigned int prefix;
-    unsigned long long rank;
-    tau_pick_digit(hist3 + kHistBins, 10, st->pfx[1], st->rk[1], prefix, rank);
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        st->pfx[2] = st->prefix = prefix;
-        st->rk[2] = st->rank = rank;
-    }
-    // candidate window [v_lo - 2m, v_hi + 2m] as float bit patterns
-    // (non-negative floats order like their bit patterns): an entry below it
-    // is exactly below the exact median, one above it exactly above
-    const double vlo = (double)__uint_as_float(prefix), vhi = (double)__uint_as_float(prefix | 0x3FFu);
+    __shared__ unsigned long long red[4];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const double mm = *max_margin;
-    const double wlo = vlo - 2.0 * mm, whi = vhi + 2.0 * mm;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        st->lo = wlo;
-        st->hi = whi;
+    uint32_t blo, bhi, dbase = 0;
+    double vlo, vhi;
+    if constexpr (BR) {
+        blo = st->br_lo;
+        bhi = st->br_hi;
+        vlo = (double)__uint_as_float(blo);
+        vhi = (double)__uint_as_float(bhi);
+    } else {
+        // the second digit, from its complete histogram: the target rank's
+        // rounded |a| has the top 22 bits prefix, so it lies in [v_lo, v_hi]
+        // (workgroup 0 records the digit)
+        unsigned int prefix;
+        unsigned long long rank;
+        tau_pick_digit(hist3 + kHistBins, 10, st->pfx[1], st->rk[1], prefix, rank);
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            st->pfx[2] = st->prefix = prefix;
+            st->rk[2] = st->rank = rank;
+        }
+        vlo = (double)__uint_as_float(prefix);
+        vhi = (double)__uint_as_float(prefix | 0x3FFu);
+        candidate_window(vlo, vhi, mm, st, blockIdx.x == 0 && threadIdx.x == 0, blo, bhi);
     }
-    float flo = (float)wlo, fhi = (float)whi;
-    if ((double)flo < wlo) flo = nextafterf(flo, INFINITY);
-    if ((double)fhi > whi) fhi = nextafterf(fhi, -INFINITY);
-    const uint32_t blo = wlo <= 0.0 ? 0u : __float_as_uint(flo);
-    const uint32_t bhi = __float_as_uint(fhi);
     // tau = fl(frac * median) is monotone in the median, which lies in
     // [v_lo - m, v_hi + m]; both ends are widened by the rounding of the bounds
     double mlo = vlo - mm;
@@ -79,6 +320,14 @@ __global__ __launch_bounds__(256) void k_median_mask_gather(const float *alpha, 
     const double mhi = nextafter(vhi + mm, INFINITY);
     const double tlo = mlo > 0.0 ? nextafter(frac * mlo, 0.0) : 0.0;
     const double thi = nextafter(frac * mhi, INFINITY);
+    if constexpr (BR) {
+        // the keys of the undecided entries are listed from below every row's t_in
+        const double a = tlo - mm;
+        float fa = (float)a;
+        if ((double)fa > a) fa = nextafterf(fa, -INFINITY);
+        dbase = fa > 0.0f ? __float_as_uint(fa) : 0u;
+        if (blockIdx.x == 0 && threadIdx.x == 0) st->br_dbase = dbase;
+    }
     float tin[W64], tout[W64];
 #pragma unroll
     for (int w = 0; w < W64; ++w) {
@@ -93,7 +342,7 @@ __global__ __launch_bounds__(256) void k_median_mask_gather(const float *alpha, 
         tin[w] = fa;
         tout[w] = fb;
     }
-    unsigned long long below = 0;
+    unsigned int below = 0;  // wave-uniform (a wave's entries are fewer than 2^32)
     const int64_t nrounds = (N + kPx - 1) / kPx;
     const int64_t nw = (int64_t)gridDim.x * 4;
     const int64_t R = (nrounds + nw - 1) / nw;  // rounds per wave
@@ -106,9 +355,18 @@ __global__ __launch_bounds__(256) void k_median_mask_gather(const float *alpha, 
     }
     int64_t *creg = cand + gw * region, *dreg = didx + gw * region;
     unsigned int nc_w = 0, nd_w = 0;  // wave-uniform counts
-    const unsigned long long lt = (1ull << lane) - 1ull;
+    auto prefix = [](unsigned long long m) {  // set bits of lower lanes
+        return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    };
+    // entry base + lane (base wave-uniform) at place `at` of a region, d above it
+    auto put = [&](int64_t *reg, uint32_t at, int64_t base, uint32_t d) {
+        const uint64_t e = (uint64_t)base + (uint32_t)lane;
+        *reinterpret_cast<uint64_t *>(reinterpret_cast<char *>(reg) + 8u * at) = e | (uint64_t)d << kPackShift;
+    };
+    const bool row_live = 64 * (W64 - 1) + lane < k;
+    const uint32_t key_and = row_live ? 0x7FFFFFFFu : 0u, key_or = row_live ? 0u : 0x7F800000u;
     // the keys of a round, loaded unconditionally (clamped indices: the loads
-    // are in flight together; padding is replaced when the round is used)
+    // are in flight together; padding is replaced when the entry is used)
     auto load = [&](int64_t rd, uint32_t (&kk)[kPx][W64]) {
         const int64_t p0 = rd * kPx;
 #pragma unroll
@@ -126,43 +384,39 @@ __global__ __launch_bounds__(256) void k_median_mask_gather(const float *alpha, 
     for (; rd < r_end; ++rd) {
         const int64_t p0 = rd * kPx;
         if (rd + 1 < r_end) load(rd + 1, nkey);  // next round in flight
-#pragma unroll
-        for (int i = 0; i < kPx; ++i)
-#pragma unroll
-            for (int w = 0; w < W64; ++w)
-                key[i][w] = (64 * w + lane < k && p0 + i < N) ? (key[i][w] & 0x7FFFFFFFu) : 0x7F800000u;
-        // lane l < kPx * W64 stores word (l / W64, l % W64), picked up as the
+        // lane l < kPx * W64 stores word (l / W64, l % W64), put there as the
         // words are formed (no array of ballots held in scalar registers)
         const int li = lane / W64, lw = lane - li * W64;
-        uint64_t outw = 0;
+        int out_lo = 0, out_hi = 0;
 #pragma unroll
-        for (int i = 0; i < kPx; ++i)
+        for (int i = 0; i < kPx; ++i) {
+            if (p0 + i >= N) break;
 #pragma unroll
             for (int w = 0; w < W64; ++w) {
-                // rows past k and pixels past N hold the key of +inf, which
-                // every test below rejects (not below, no candidate, not in,
-                // not deferred), so no separate liveness mask is needed
-                const uint32_t x = key[i][w];
-                below += x < blo ? 1ull : 0ull;
-                const bool is_cand = x >= blo && x <= bhi;
-                const unsigned long long cm = __ballot(is_cand);
+                // rows past k get the key of +inf, which every test below
+                // rejects (not below, no candidate, not in, not deferred)
+                const uint32_t x = w < W64 - 1 ? key[i][w] & 0x7FFFFFFFu : (key[i][w] & key_and) | key_or, d = x - blo;
+                below += (unsigned int)__popcll(__builtin_amdgcn_uicmp(x, blo, kUlt));
+                const unsigned long long cm = __builtin_amdgcn_uicmp(d, bhi - blo, kUle);
                 if (cm) {
-                    if (is_cand) creg[nc_w + __popcll(cm & lt)] = (p0 + i) * k + 64 * w + lane;
+                    if (__builtin_amdgcn_inverse_ballot_w64(cm)) put(creg, nc_w + prefix(cm), (p0 + i) * k + 64 * w, BR ? d : 0u);
                     nc_w += (unsigned int)__popcll(cm);
                 }
                 const float f = __uint_as_float(x);
-                const uint64_t inb = __ballot(f <= tin[w]);
-                if (li == i && lw == w) outw = inb;
-                const bool defer = !(f <= tin[w]) && !(f > tout[w]);  // NaN: deferred
-                const unsigned long long dm = __ballot(defer);
+                const uint64_t inb = __builtin_amdgcn_fcmpf(f, tin[w], kOle);
+                out_lo = write_lane((int)(uint32_t)inb, i * W64 + w, out_lo);
+                out_hi = write_lane((int)(uint32_t)(inb >> 32), i * W64 + w, out_hi);
+                const unsigned long long dm = ~(inb | __builtin_amdgcn_fcmpf(f, tout[w], kOgt));  // NaN: deferred
                 if (dm) {
-                    if (defer) dreg[nd_w + __popcll(dm & lt)] = (p0 + i) * k + 64 * w + lane;
+                    if (__builtin_amdgcn_inverse_ballot_w64(dm)) put(dreg, nd_w + prefix(dm), (p0 + i) * k + 64 * w, BR ? min(x - dbase, kPackMax) : 0u);
                     nd_w += (unsigned int)__popcll(dm);
                 }
                 // one entry at a time: keeps the ballots from piling up in
                 // scalar registers
                 __builtin_amdgcn_sched_barrier(0);
             }
+        }
+        const uint64_t outw = (uint64_t)(uint32_t)out_hi << 32 | (uint32_t)out_lo;
         if (lane < kPx * W64 && p0 + li < N) masks[(p0 + li) * W64 + lw] = outw;
 #pragma unroll
         for (int i = 0; i < kPx; ++i)
@@ -173,14 +427,10 @@ __global__ __launch_bounds__(256) void k_median_mask_gather(const float *alpha, 
         ccnt[gw] = nc_w;
         dcnt[gw] = nd_w;
     }
-    red[threadIdx.x] = below;
+    if (lane == 0) red[wave] = below;
     __syncthreads();
-    for (int s2 = 128; s2 > 0; s2 >>= 1) {
-        if ((int)threadIdx.x < s2) red[threadIdx.x] += red[threadIdx.x + s2];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) parts[blockIdx.x] = red[0];
-    if (blockIdx.x == 0 && threadIdx.x == 0) st->nparts = gridDim.x;
+    if (threadIdx.x == 0) parts[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+    if (!BR && blockIdx.x == 0 && threadIdx.x == 0) st->nparts = gridDim.x;
 }
 
 // The listed entries against the exact tau, a lane per entry.  An entry whose
@@ -198,6 +448,8 @@ __global__ __launch_bounds__(64) void k_median_mask_finish(const float *alpha, c
     __shared__ int64_t s_near[64];
     const int lane = threadIdx.x, grp = lane / kExactLanes, W64 = (k + 63) / 64;
     const double tau = st->tau;
+    const bool packed = st->br_ok != 0;  // the list carries the keys
+    const uint32_t dbase = st->br_dbase;
     auto set = [&](int64_t pix, int j) {
         atomicOr(reinterpret_cast<unsigned long long *>(masks + pix * W64 + (j >> 6)), 1ull << (j & 63));
     };
@@ -208,11 +460,18 @@ __global__ __launch_bounds__(64) void k_median_mask_finish(const float *alpha, c
         int64_t e = 0;
         if (live) {
             e = lst[q0 + lane];
+            uint32_t d = 0;
+            if (packed) {
+                d = (uint32_t)((uint64_t)e >> kPackShift);
+                e &= ((int64_t)1 << kPackShift) - 1;
+            }
             const int64_t pix = e / k;
             const int j = (int)(e - pix * k);
-            const double a = (double)fabsf(alpha[e]);
+            const double a = packed ? (double)__uint_as_float(dbase + d) : (double)fabsf(alpha[e]);
             const double m = margins[j];
-            if (a <= tau - m)
+            if (packed && d == kPackMax)
+                near = true;
+            else if (a <= tau - m)
                 set(pix, j);
             else
                 near = !(a > tau + m);  // within the margin, or NaN
@@ -255,7 +514,7 @@ hipError_t median_mask_gather(const LaunchCtx &lc, const float *alpha, int64_t N
     // the per-workgroup counts would not fit
     const int64_t blocks = median_gather_waves(N) / 4;
 #define CS_MG_LAUNCH(WW)                                                                                    \
-    hipLaunchKernelGGL(k_median_mask_gather<WW>, dim3((unsigned)blocks), dim3(256), 0, lc.stream, alpha, N, \
+    hipLaunchKernelGGL((k_median_mask_gather<WW, false>), dim3((unsigned)blocks), dim3(256), 0, lc.stream, alpha, N, \
                        k, max_margin, margins, frac, st, cand, ccnt, parts, didx, dcnt, masks, hist3)
     switch ((k + 63) / 64) {
         case 1: CS_MG_LAUNCH(1); break;
@@ -267,9 +526,34 @@ hipError_t median_mask_gather(const LaunchCtx &lc, const float *alpha, int64_t N
     return hipGetLastError();
 }
 
+hipError_t median_bracket(const LaunchCtx &lc, const float *alpha, int64_t N, int k, const double *max_margin,
+                          const double *margins, double frac, TauState *st, uint64_t *blist, int64_t *cand,
+                          unsigned int *ccnt, unsigned long long *parts, int64_t *didx, unsigned int *dcnt,
+                          uint64_t *masks, unsigned int *br_hist) {
+    const int blocks = (int)(median_gather_waves(N) / 4);
+    unsigned int *fine = br_hist + kBracketBins;
+    hipLaunchKernelGGL(k_bracket_sample, dim3(kSampleBlocks), dim3(1024), 0, lc.stream, alpha, N * k, br_hist);
+    hipLaunchKernelGGL(k_bracket_pick, dim3(1), dim3(1024), 0, lc.stream, br_hist, max_margin, st);
+#define CS_BR_LAUNCH(WW)                                                                                           \
+    hipLaunchKernelGGL((k_median_mask_gather<WW, true>), dim3((unsigned)blocks), dim3(256), 0, lc.stream, alpha, N, k, \
+                       max_margin, margins, frac, st, (int64_t *)blist, ccnt, parts, didx, dcnt, masks, nullptr)
+    switch ((k + 63) / 64) {
+        case 1: CS_BR_LAUNCH(1); break;
+        case 2: CS_BR_LAUNCH(2); break;
+        case 3: CS_BR_LAUNCH(3); break;
+        default: CS_BR_LAUNCH(4); break;
+    }
+#undef CS_BR_LAUNCH
+    hipLaunchKernelGGL(k_bracket_hist, dim3((unsigned)(lc.num_cu / 2)), dim3(1024), 0, lc.stream, blist, ccnt, st, fine);
+    // (the list's counts are read and replaced by the wave that owns the region)
+    hipLaunchKernelGGL(k_bracket_window, dim3((unsigned)lc.num_cu), dim3(256), 0, lc.stream, blist, ccnt, fine,
+                       max_margin, st, parts, blocks, cand, ccnt);
+    return hipGetLastError();
+}
+
 int64_t median_gather_waves(int64_t N) {
     int64_t blocks = (N + 4 * kPx * kRoundsPerWave - 1) / (4 * kPx * kRoundsPerWave);
-    if (blocks > kTauParts) blocks = kTauParts;
+    if (blocks > kGatherBlocks) blocks = kGatherBlocks;
     return 4 * blocks;
 }
 

@@ -45,6 +45,7 @@ __global__ __launch_bounds__(256) void k_tau_init(TauState *st, unsigned long lo
         st->n_d = 0;
         st->n_r = 0;
         st->lo = st->hi = 0.0;
+        st->br_valid = st->br_ok = 0;
         st->median = 0.0;
         st->tau = 0.0;
     }
@@ -64,6 +65,7 @@ __global__ __launch_bounds__(256) void k_tau_hist(const float *alpha, int64_t co
                                                    unsigned int *hist, const unsigned int *pick_hist,
                                                    int pick_shift, int pick_d) {
     __shared__ unsigned int lh[SUB * kHistBins];
+    if (st->br_ok) return;  // selected from a bracket already
     unsigned int prefix = st->prefix;
     if (pick_hist) {
         unsigned long long rank;
@@ -358,112 +360,84 @@ __global__ __launch_bounds__(64) void k_tau_recompute(const float *rgb, int H, i
 
 // Offsets of the fused gather's per-wave regions in the compact lists
 // (exclusive scans of their candidate and undecided-entry counts) and the two
-// totals.  One workgroup per chunk of kScanChunk counts: it first adds up the
-// counts of the chunks before its own (eight 16-byte loads per thread in
-// flight, four of each count array),
-// then scans its chunk through LDS (coalesced loads, each thread scanning 8
-// consecutive counts); the last workgroup writes the totals.  (One workgroup
-// walking every chunk in turn took 0.22 ms at 2048 x 2048.)
-constexpr int kScanChunk = 8192;
+// totals.  One workgroup, four consecutive counts of each array per thread.
+static_assert(kMedianWavesMax == 4 * 1024, "four counts per thread");
 __global__ __launch_bounds__(1024) void k_list_scan(const unsigned int *ccnt, const unsigned int *dcnt,
                                                     TauState *st, unsigned long long *coff,
                                                     unsigned long long *doff) {
-    __shared__ unsigned int lc[kScanChunk], ld[kScanChunk];
-    __shared__ unsigned long long s[2][1024];
-    __shared__ unsigned long long s_carry[2];
+    __shared__ unsigned long long s_w[2][16];
     const int nw = (int)st->rg_waves;
-    const int t = threadIdx.x;
-    const int base = blockIdx.x * kScanChunk;
-    if (base >= nw) return;  // workgroup-uniform
-    // counts of the chunks before this one, four per 16-byte load (base is a
-    // multiple of kScanChunk, the arrays 256-byte aligned)
-    unsigned long long pc = 0, pd = 0;
-    const uint4 *c4 = reinterpret_cast<const uint4 *>(ccnt), *d4 = reinterpret_cast<const uint4 *>(dcnt);
-    for (int i0 = 0; i0 < base / 4; i0 += 4 * 1024) {
-        uint4 vc[4], vd[4];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    unsigned int vc[4], vd[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int r = i0 + u * 1024 + t;
-            vc[u] = r < base / 4 ? c4[r] : make_uint4(0u, 0u, 0u, 0u);
-            vd[u] = r < base / 4 ? d4[r] : make_uint4(0u, 0u, 0u, 0u);
-        }
+    for (int u = 0; u < 4; ++u) {
+        vc[u] = 4 * t + u < nw ? ccnt[4 * t + u] : 0u;
+        vd[u] = 4 * t + u < nw ? dcnt[4 * t + u] : 0u;
+    }
+    const unsigned long long sc = (unsigned long long)vc[0] + vc[1] + vc[2] + vc[3];
+    const unsigned long long sd = (unsigned long long)vd[0] + vd[1] + vd[2] + vd[3];
+    unsigned long long ic = sc, id = sd;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            pc += (unsigned long long)vc[u].x + vc[u].y + vc[u].z + vc[u].w;
-            pd += (unsigned long long)vd[u].x + vd[u].y + vd[u].z + vd[u].w;
+    for (int off = 1; off < 64; off <<= 1) {
+        const unsigned long long a = __shfl_up(ic, off), b = __shfl_up(id, off);
+        if (lane >= off) {
+            ic += a;
+            id += b;
         }
     }
-    if (t == 0) s_carry[0] = s_carry[1] = 0ull;
-    for (int i = t; i < kScanChunk; i += 1024) {
-        const int r = base + i;
-        lc[i] = r < nw ? ccnt[r] : 0u;
-        ld[i] = r < nw ? dcnt[r] : 0u;
+    if (lane == 63) {
+        s_w[0][wave] = ic;
+        s_w[1][wave] = id;
     }
     __syncthreads();
-    if (pc) atomicAdd(&s_carry[0], pc);
-    if (pd) atomicAdd(&s_carry[1], pd);
-    unsigned long long sc = 0, sd = 0;
+    unsigned long long bc = ic - sc, bd = id - sd;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        sc += lc[8 * t + u];
-        sd += ld[8 * t + u];
-    }
-    s[0][t] = sc;
-    s[1][t] = sd;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        const unsigned long long vc = t >= off ? s[0][t - off] : 0ull, vd = t >= off ? s[1][t - off] : 0ull;
-        __syncthreads();
-        s[0][t] += vc;
-        s[1][t] += vd;
-        __syncthreads();
-    }
-    const unsigned long long carry_c = s_carry[0], carry_d = s_carry[1];
-    unsigned long long bc = carry_c + s[0][t] - sc, bd = carry_d + s[1][t] - sd;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int r = base + 8 * t + u;
-        if (r < nw) {
-            coff[r] = bc;
-            doff[r] = bd;
+    for (int w = 0; w < 16; ++w)
+        if (w < wave) {
+            bc += s_w[0][w];
+            bd += s_w[1][w];
         }
-        bc += lc[8 * t + u];
-        bd += ld[8 * t + u];
+    if (t == 1023) {
+        st->ncand = bc + sc;
+        st->n_d = bd + sd;
     }
-    if (t == 0 && base + kScanChunk >= nw) {
-        st->ncand = carry_c + s[0][1023];
-        st->n_d = carry_d + s[1][1023];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        if (4 * t + u < nw) {
+            coff[4 * t + u] = bc;
+            doff[4 * t + u] = bd;
+        }
+        bc += vc[u];
+        bd += vd[u];
     }
 }
 
-// Both lists of the fused gather into compact form (lane = region), each only
-// when its total fits kListCap; otherwise its consumer walks the regions.
+// Both lists of the fused gather into compact form (a wave per region), each
+// only when its total fits kListCap; otherwise its consumer walks the regions.
 __global__ __launch_bounds__(64) void k_list_compact(const int64_t *cand, const unsigned int *ccnt,
                                                      const unsigned long long *coff, const int64_t *didx,
                                                      const unsigned int *dcnt, const unsigned long long *doff,
                                                      const TauState *st, int64_t *ccomp, int64_t *dcomp) {
-    const int64_t nw = (int64_t)st->rg_waves, region = (int64_t)st->rg_size;
+    const int64_t r = blockIdx.x, region = (int64_t)st->rg_size;
     const bool cfit = (int64_t)st->ncand <= kListCap, dfit = (int64_t)st->n_d <= kListCap;
-    for (int64_t r = (int64_t)blockIdx.x * 64 + threadIdx.x; r < nw; r += (int64_t)gridDim.x * 64) {
-        if (cfit) {
-            const unsigned int n = ccnt[r];
-            const int64_t *src = cand + r * region;
-            int64_t *dst = ccomp + coff[r];
-            for (unsigned int q = 0; q < n; ++q) dst[q] = src[q];
-        }
-        if (dfit) {
-            const unsigned int n = dcnt[r];
-            const int64_t *src = didx + r * region;
-            int64_t *dst = dcomp + doff[r];
-            for (unsigned int q = 0; q < n; ++q) dst[q] = src[q];
-        }
+    if (cfit) {
+        const unsigned int n = ccnt[r];
+        const int64_t *src = cand + r * region;
+        int64_t *dst = ccomp + coff[r];
+        for (unsigned int q = threadIdx.x; q < n; q += 64) dst[q] = src[q];
+    }
+    if (dfit) {
+        const unsigned int n = dcnt[r];
+        const int64_t *src = didx + r * region;
+        int64_t *dst = dcomp + doff[r];
+        for (unsigned int q = threadIdx.x; q < n; q += 64) dst[q] = src[q];
     }
 }
 
 // Short candidate lists (up to kRankMax): the rank of every candidate by
 // comparison with all of them, one wave per candidate (lanes split the list),
 // stored as (less, equal) for the selection below.  Longer lists are left to
-// its radix select.
+// its radix select (16384 candidates: 303 us here, 40 us there).
 constexpr int kRankMax = kTauRank;
 __global__ __launch_bounds__(64) void k_tau_rank(const double *vals, int64_t cap, const TauState *st,
                                                   unsigned long long *rk) {
@@ -685,10 +659,9 @@ __global__ __launch_bounds__(1024) void k_tau_select(const double *vals, int64_t
 
 hipError_t list_compact(const LaunchCtx &lc, int64_t nw, const int64_t *cand, const unsigned int *ccnt,
                         const int64_t *didx, const unsigned int *dcnt, TauState *st, FusedLists fl) {
-    hipLaunchKernelGGL(k_list_scan, dim3((unsigned)((nw + kScanChunk - 1) / kScanChunk)), dim3(1024), 0, lc.stream,
-                       ccnt, dcnt, st, fl.coff, fl.doff);
-    hipLaunchKernelGGL(k_list_compact, dim3((unsigned)((nw + 63) / 64)), dim3(64), 0, lc.stream, cand, ccnt, fl.coff,
-                       didx, dcnt, fl.doff, st, fl.ccomp, fl.dcomp);
+    hipLaunchKernelGGL(k_list_scan, dim3(1), dim3(1024), 0, lc.stream, ccnt, dcnt, st, fl.coff, fl.doff);
+    hipLaunchKernelGGL(k_list_compact, dim3((unsigned)nw), dim3(64), 0, lc.stream, cand, ccnt, fl.coff, didx, dcnt,
+                       fl.doff, st, fl.ccomp, fl.dcomp);
     return hipGetLastError();
 }
 

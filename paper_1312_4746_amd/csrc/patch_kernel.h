@@ -474,7 +474,8 @@ void k_patch(AnalyzeArgs a, int tiles_x, int ntiles) {
     }
     // the set-up of the median selection that follows this kernel
     if (a.tau_st && blockIdx.x == 0)
-        tau_setup(a.tau_st, a.tau_hist3, a.omega, a.k, n, a.tau_coef, a.tau_rank0, a.tau_margins, a.tau_max_margin);
+        tau_setup(a.tau_st, a.tau_hist3, a.tau_hist_words, a.omega, a.k, n, a.tau_coef, a.tau_rank0, a.tau_margins,
+                  a.tau_max_margin);
 }
 
 template <int P, int JB, int PREC, int OUT>
