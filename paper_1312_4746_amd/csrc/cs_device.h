@@ -9,6 +9,9 @@
 
 #include "cs_internal.h"
 
+// lane l of old replaced by v
+__device__ int write_lane(int v, int l, int old) __asm("llvm.amdgcn.writelane.i32");
+
 namespace cs {
 
 // Symmetric border reflection that repeats the edge pixel: -1 -> 0, n -> n-1.
@@ -107,6 +110,45 @@ __device__ __forceinline__ double row_margin(const float *omega, int j, int n, d
     return coef * sqrt(ss) * (1.0 + 0x1p-20) + 0x1p-100;
 }
 
+// Co-support at tau = frac * median|a| while the median is only known to lie in
+// [v_lo, v_hi] up to the largest row margin mm: tau = fl(frac * median) is
+// monotone in the median, so it lies in [tlo, thi] (both ends widened by the
+// rounding of the bounds).
+__device__ __forceinline__ void tau_interval(double vlo, double vhi, double mm, double frac, double &tlo,
+                                             double &thi) {
+    double mlo = vlo - mm;
+    mlo = mlo > 0.0 ? nextafter(mlo, 0.0) : 0.0;
+    const double mhi = nextafter(vhi + mm, INFINITY);
+    tlo = mlo > 0.0 ? nextafter(frac * mlo, 0.0) : 0.0;
+    thi = nextafter(frac * mhi, INFINITY);
+}
+// A row of margin m: rounded |a| <= tin is in, > tout is out, the rest is
+// decided once tau is known.
+__device__ __forceinline__ void tau_row_interval(double tlo, double thi, double m, float &tin, float &tout) {
+    const double a = tlo - m, b = thi + m;
+    tin = (float)a;
+    if ((double)tin > a) tin = nextafterf(tin, -INFINITY);
+    tout = (float)b;
+    if ((double)tout < b) tout = nextafterf(tout, INFINITY);
+}
+// Float bits at or below every row's undecided entries.
+__device__ __forceinline__ uint32_t tau_defer_base(double tlo, double mm) {
+    const double a = tlo - mm;
+    float fa = (float)a;
+    if ((double)fa > a) fa = nextafterf(fa, -INFINITY);
+    return fa > 0.0f ? __float_as_uint(fa) : 0u;
+}
+// Listed entries of a bracket: entry in the low bits, key less a base above
+// (kPackMax: the key does not fit).
+constexpr int kPackShift = 40;
+constexpr uint32_t kPackMax = (1u << 24) - 1u;
+// comparison predicates of the wave-mask builtins (LLVM's numbers)
+constexpr int kUlt = 36, kUle = 37, kSgt = 38, kOgt = 2, kOle = 5;
+// the set bits of m in lower lanes
+__device__ __forceinline__ uint32_t lane_prefix(uint64_t m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
 // Radix selection helpers (256-thread workgroups).
 // The digit holding the remaining rank in a complete kHistBins-bin histogram
 // (parallel prefix over the bins): the prefix with that digit set and the
@@ -155,26 +197,29 @@ __device__ __forceinline__ void tau_pick_digit(const unsigned int *hist, int shi
     rank_out = s_rank;
 }
 
-// Set-up of a folded selection by one 256-thread workgroup: per-row margins
-// and their maximum, the state (digit 0: empty prefix, the target rank) and
-// the cleared histograms.
-__device__ __forceinline__ void tau_setup(TauState *st, unsigned int *hist3, int hist_words, const float *omega, int k, int n,
-                                          double coef, unsigned long long rank0, double *margins,
-                                          double *max_margin) {
-    __shared__ double red[4];
+// Set-up of a folded selection: per-row margins and their maximum (by one
+// workgroup of nt threads, at least 256) ...
+__device__ __forceinline__ void tau_setup_margins(const float *omega, int k, int n, double coef, double *margins,
+                                                  double *max_margin, int nt) {
+    __shared__ double red[16];
     const int t = threadIdx.x;
     double m = 0.0;
-    for (int j = t; j < k; j += 256) {
-        const double mj = row_margin(omega, j, n, -1.0, coef);
-        margins[j] = mj;
-        m = fmax(m, mj);
-    }
+    if (t < k) margins[t] = m = row_margin(omega, t, n, -1.0, coef);
     for (int off = 1; off < 64; off <<= 1) m = fmax(m, __shfl_xor(m, off));
     if ((t & 63) == 0) red[t >> 6] = m;
-    for (int i = t; i < hist_words; i += 256) hist3[i] = 0u;
     __syncthreads();
     if (t == 0) {
-        *max_margin = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+        for (int w = 1; w < nt / 64; ++w) m = fmax(m, red[w]);
+        *max_margin = m;
+    }
+}
+// ... and the state (digit 0: empty prefix, the target rank) and the cleared
+// histograms.
+__device__ __forceinline__ void tau_setup_state(TauState *st, unsigned int *hist3, int hist_words,
+                                                unsigned long long rank0, int nt) {
+    const int t = threadIdx.x;
+    for (int i = t; i < hist_words; i += nt) hist3[i] = 0u;
+    if (t == 0) {
         st->rank0 = rank0;
         st->rank = rank0;
         st->prefix = 0;
@@ -188,12 +233,19 @@ __device__ __forceinline__ void tau_setup(TauState *st, unsigned int *hist3, int
         st->n_d = 0;
         st->n_r = 0;
         st->lo = st->hi = 0.0;
-        st->br_valid = st->br_ok = 0;
+        st->br_valid = st->br_ok = st->br_over = 0;
         st->median = 0.0;
         st->tau = 0.0;
     }
 }
 
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+// Two values to BF16, to nearest even, by the conversion instruction (the bits
+// of bf16_rne for every finite value).
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{a, b}), bf16x2_t));
+}
 __device__ __forceinline__ short bf16_rne(float f) {
     uint32_t u = __float_as_uint(f);
     u += 0x7FFFu + ((u >> 16) & 1u);

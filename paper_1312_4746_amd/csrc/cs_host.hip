@@ -763,30 +763,52 @@ int cs_cosupport_median(cs_ctx *ctx, const float *rgb, int H, int W, int p, doub
         double *vals = (double *)(ctx->cand + (size_t)count * 8);
         int64_t *didx = (int64_t *)(ctx->cand + (size_t)count * 16);
         unsigned int *hist3 = (unsigned int *)(ctx->ws + o_hist3);
+        // patches up to kPatchSelMax: the pass over the bracket inside the analysis
+        // (BF16: with the BF16 vectors in the same kernel)
+        const bool fused = bracket && p <= kPatchSelMax, fused16 = fused && precision == CS_BF16;
+        AnalyzeArgs a{};
+        a.rgb = rgb;
+        a.H = H;
+        a.W = W;
+        a.p = p;
+        a.n = n;
+        a.n_pad = n_pad_of(n);
+        a.k = k;
+        a.wmask = ctx->wmask;
+        a.omega = omega;
         {
-            AnalyzeArgs a{};
-            a.rgb = rgb;
-            a.H = H;
-            a.W = W;
-            a.p = p;
-            a.n = n;
-            a.n_pad = n_pad_of(n);
-            a.k = k;
-            a.wmask = ctx->wmask;
-            a.omega = omega;
-            a.alpha = a32;
-            a.pstats = pst;
-            a.tau_st = st;
-            a.tau_hist3 = hist3;
-            a.tau_hist_words = hist_words;
-            a.tau_margins = marg;
-            a.tau_max_margin = mmax;
-            a.tau_coef = median_coef(p);
-            a.tau_rank0 = (unsigned long long)((count - 1) / 2);
+            AnalyzeArgs f = a;
+            f.alpha = fused16 ? alpha : a32;
+            f.pstats = pst;
+            f.tau_st = st;
+            f.tau_hist3 = hist3;
+            f.tau_hist_words = hist_words;
+            f.tau_margins = marg;
+            f.tau_max_margin = mmax;
+            f.tau_coef = median_coef(p);
+            f.tau_rank0 = (unsigned long long)((count - 1) / 2);
             Timed t(ctx, "analyze");
-            HIP_TRY(launch_analyze(lc, a, CS_FP32));
+            if (fused) {
+                f.masks = masks;
+                f.sel_frac = frac;
+                f.sel_blist = (uint64_t *)vals;
+                f.sel_dlist = (uint64_t *)didx;
+                f.sel_bcnt = ccnt;
+                f.sel_dcnt = dcnt;
+                f.sel_parts = parts;
+                HIP_TRY(median_bracket_analyze(lc, f, fused16 ? CS_BF16 : CS_FP32, hist3 + 3 * kHistBins, cand));
+                if (fused16) {
+                    // the FP32 vectors, for the digits where the bracket missed
+                    AnalyzeArgs b = a;
+                    b.alpha = a32;
+                    b.skip = st;
+                    HIP_TRY(launch_analyze(lc, b, CS_FP32));
+                }
+            } else {
+                HIP_TRY(launch_analyze(lc, f, CS_FP32));
+            }
         }
-        if (bracket) {
+        if (bracket && !fused) {
             Timed t(ctx, "cosupport");
             HIP_TRY(median_bracket(lc, a32, (int64_t)H * W, k, mmax, marg, frac, st, (uint64_t *)vals, cand, ccnt, parts,
                                    didx, dcnt, masks, hist3 + 3 * kHistBins));
@@ -799,7 +821,8 @@ int cs_cosupport_median(cs_ctx *ctx, const float *rgb, int H, int W, int p, doub
             Timed t(ctx, "cosupport");
             HIP_TRY(median_mask_gather(lc, a32, (int64_t)H * W, k, mmax, marg, frac, st, cand, ccnt, parts, didx,
                                        dcnt, masks, hist3));
-            HIP_TRY(list_compact(lc, median_gather_waves((int64_t)H * W), cand, ccnt, didx, dcnt, st, fl));
+            HIP_TRY(list_compact(lc, fused ? kMedianWavesMax : median_gather_waves((int64_t)H * W), cand, ccnt, didx,
+                                 dcnt, st, fl));
         }
         {
             Timed t(ctx, "tau_exact");
@@ -811,17 +834,7 @@ int cs_cosupport_median(cs_ctx *ctx, const float *rgb, int H, int W, int p, doub
             HIP_TRY(median_mask_finish(lc, a32, rgb, H, W, p, ctx->wmask, omega, k, didx, dcnt, fl.dcomp, marg, st,
                                        masks, pst));
         }
-        if (precision == CS_BF16) {
-            AnalyzeArgs a{};
-            a.rgb = rgb;
-            a.H = H;
-            a.W = W;
-            a.p = p;
-            a.n = n;
-            a.n_pad = n_pad_of(n);
-            a.k = k;
-            a.wmask = ctx->wmask;
-            a.omega = omega;
+        if (precision == CS_BF16 && !fused16) {
             a.alpha = alpha;
             Timed t(ctx, "analyze_bf16");
             HIP_TRY(launch_analyze(lc, a, CS_BF16));

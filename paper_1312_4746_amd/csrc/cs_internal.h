@@ -92,11 +92,29 @@ struct AnalyzeArgs {
     double *tau_max_margin;        // their maximum
     double tau_coef;
     unsigned long long tau_rank0;  // target rank
+    // optional (p <= kPatchSelMax): the pass over a sampled bracket of the median
+    // made by the analysis itself (sel_st, whose br_valid tells whether there
+    // is one): masks decided, entries counted and listed as by the gather pass;
+    // each wave's region of the lists takes sel_region entries
+    struct TauState *sel_st;
+    double sel_frac;
+    uint64_t *sel_blist, *sel_dlist;
+    unsigned int *sel_bcnt, *sel_dcnt;
+    unsigned long long *sel_parts;
+    int64_t sel_region;
+    const struct TauState *skip;  // the call does nothing where its br_ok is set, or null
 };
 hipError_t launch_analyze(const LaunchCtx &lc, const AnalyzeArgs &a, int precision);
 // Patches up to kPatchMax (patch_kernel.h, one file per size); launch_analyze
 // takes these for them.
 constexpr int kPatchMax = 11;
+// Those up to kPatchSelMax also make the pass over a bracket of the median, BF16
+// vectors with the FP32 products in one kernel.  (Whole calls, 2048 x 2048, pass
+// apart / within: 7 x 7, k = 98 FP32 1484 / 1348 us, BF16 2017 / 1290 us; 5 x 5, k =
+// 50 883 / 738 and 1216 / 734 us; 1024 x 1024, 9 x 9, k = 240 1011 / 1001 and 1299 /
+// 1084 us.  11 x 11, k = 128 710 / 815, k = 242 1218 / 1248 us: the operator leaves
+// the tests no registers there.)
+constexpr int kPatchSelMax = 9;
 // 16-product pieces of an MFMA chain, and the roundings that a product of the
 // FP32 contraction can pass: its chain's and the sums of the chains.
 __host__ __device__ constexpr int patch_chain_quads(int p) { return p <= 7 ? 1 : 2; }
@@ -161,6 +179,7 @@ struct TauState {
     // general selection then return at once)
     unsigned int br_lo, br_hi, br_shift, br_dbase;
     int br_valid, br_ok;
+    int br_over;  // a list region of the fused analysis was too short
 };
 // Upper bound of the workgroups of a candidate gather (per-workgroup counts);
 // the counts array is followed by kTauRank words for the ranks of short
@@ -249,6 +268,14 @@ hipError_t median_bracket(const LaunchCtx &lc, const float *alpha, int64_t N, in
                           const double *margins, double frac, TauState *st, uint64_t *blist, int64_t *cand,
                           unsigned int *ccnt, unsigned long long *parts, int64_t *didx, unsigned int *dcnt,
                           uint64_t *masks, unsigned int *br_hist);
+// Its steps after the pass over the entries.
+hipError_t median_bracket_list(const LaunchCtx &lc, const double *max_margin, TauState *st, const uint64_t *blist,
+                               int64_t *cand, unsigned int *ccnt, unsigned long long *parts, unsigned int *br_hist);
+// The analysis (p <= kPatchSelMax) with that pass in it: the
+// set-up a.tau_*, a bracket from sampled pixels, the vectors, masks and lists
+// (a.sel_*), and the steps after the pass.
+hipError_t median_bracket_analyze(const LaunchCtx &lc, const AnalyzeArgs &a, int precision, unsigned int *br_hist,
+                                  int64_t *cand);
 // After the exact tau: the listed entries, decided in one launch (the rounded
 // value where it is clear of tau by the row margin, else in FP64).
 hipError_t median_mask_finish(const LaunchCtx &lc, const float *alpha, const float *rgb, int H, int W, int p,

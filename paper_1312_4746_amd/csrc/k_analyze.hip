@@ -284,9 +284,10 @@ __global__ __launch_bounds__(256) void k_analyze(AnalyzeArgs a) {
         if (a.recomputed && lane == 0 && nrecomp) atomicAdd(a.recomputed, nrecomp);
     }
     // the set-up of the median selection that follows this kernel
-    if (a.tau_st && blockIdx.x == 0 && blockIdx.y == 0)
-        tau_setup(a.tau_st, a.tau_hist3, a.tau_hist_words, a.omega, a.k, n, a.tau_coef, a.tau_rank0, a.tau_margins,
-                  a.tau_max_margin);
+    if (a.tau_st && blockIdx.x == 0 && blockIdx.y == 0) {
+        tau_setup_state(a.tau_st, a.tau_hist3, a.tau_hist_words, a.tau_rank0, 256);
+        tau_setup_margins(a.omega, a.k, n, a.tau_coef, a.tau_margins, a.tau_max_margin, 256);
+    }
 }
 
 template <int PREC, int P>

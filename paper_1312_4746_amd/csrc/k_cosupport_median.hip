@@ -22,22 +22,11 @@
 #include "cs_internal.h"
 #include "cs_device.h"
 
-// lane l of old replaced by v
-__device__ int write_lane(int v, int l, int old) __asm("llvm.amdgcn.writelane.i32");
-
 namespace cs {
 
 namespace {
 constexpr int kPx = 8;  // pixels per wave and round in the pixel-major pass
 constexpr int kRoundsPerWave = 4;
-// comparison predicates of the wave-mask builtins (LLVM's numbers)
-constexpr int kUlt = 36, kUle = 37, kOgt = 2, kOle = 5;
-
-// Listed entries of a bracket: entry in the low bits, key less a base above
-// (kPackMax: the key does not fit).
-constexpr int kPackShift = 40;
-constexpr uint32_t kPackMax = (1u << 24) - 1u;
-
 // Candidate window [v_lo - 2m, v_hi + 2m] as float bit patterns (non-negative
 // floats order like their bit patterns): an entry below it is exactly below
 // the exact median, one above it exactly above.
@@ -90,6 +79,77 @@ __global__ __launch_bounds__(1024) void k_bracket_sample(const float *alpha, int
     __syncthreads();
     for (int i = threadIdx.x; i < kBracketBins; i += 1024)
         if (h[i]) atomicAdd(&hist[i], h[i]);
+}
+
+// The same before any vector is there: kSample / 8 pixels spread by the golden
+// ratio, eight rows of each chosen by a hash, in FP32 (a wave per pixel: its
+// lanes form the patch, then eight take a row each).  On textured images with
+// noise its median's rank was off by 0.11 % (one deviation, 12 images).
+// One workgroup more computes the rows' margins.
+constexpr int kPatchSampleBlocks = 256;
+__global__ __launch_bounds__(1024) void k_patch_sample(AnalyzeArgs a, unsigned int *hist) {
+    __shared__ unsigned int h[kBracketBins];
+    __shared__ float s_p[16][128];
+    if (blockIdx.x == kPatchSampleBlocks) {
+        tau_setup_margins(a.omega, a.k, a.n, a.tau_coef, a.tau_margins, a.tau_max_margin, 1024);
+        return;
+    }
+    const float *const rgb = a.rgb, *const omega = a.omega;
+    const double *const wmask = a.wmask;
+    const int H = a.H, W = a.W, p = a.p, k = a.k;
+    for (int i = threadIdx.x; i < kBracketBins; i += 1024) h[i] = 0u;
+    __syncthreads();
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = p * p, hp = (p - 1) / 2;
+    const int64_t N = (int64_t)H * W;
+    constexpr int per = kSample / 8 / (kPatchSampleBlocks * 16);
+    float *const sp = s_p[wave];
+    const int t1 = lane + 64;
+    const double w0 = lane < n ? wmask[lane] : 0.0, w1 = t1 < n ? wmask[t1] : 0.0;
+    const int u0 = lane / p, v0 = lane - u0 * p, u1 = t1 / p, v1 = t1 - u1 * p;
+    auto place = [&](int row, int col, int u, int v) {
+        return (int64_t)reflect_idx(row + u - hp, H) * W + reflect_idx(col + v - hp, W);
+    };
+#pragma unroll
+    for (int it = 0; it < per; ++it) {
+        const uint64_t i = ((uint64_t)blockIdx.x * 16 + wave) * per + it;
+        const int64_t pix = (int64_t)__umul64hi(i * 0x9E3779B97F4A7C15ull, (uint64_t)N);
+        const int row = (int)(pix / W), col = (int)(pix - (int64_t)row * W);
+        const double q0 = lane < n ? w0 * gray64(rgb, N, place(row, col, u0, v0)) : 0.0;
+        const double q1 = t1 < n ? w1 * gray64(rgb, N, place(row, col, u1, v1)) : 0.0;
+        double sum = q0 + q1;
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d);
+        const double mu = sum / n;
+        const float z0 = lane < n ? (float)(q0 - mu) : 0.0f, z1 = t1 < n ? (float)(q1 - mu) : 0.0f;
+        float nu2 = z0 * z0 + z1 * z1;
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) nu2 += __shfl_xor(nu2, d);
+        const float ri = nu2 > 0.0f ? 1.0f / sqrtf(nu2) : 0.0f;
+        __builtin_amdgcn_wave_barrier();
+        sp[lane] = z0 * ri;
+        sp[t1] = z1 * ri;
+        __builtin_amdgcn_wave_barrier();  // a wave's LDS accesses complete in order
+        // row of this group of eight lanes
+        uint64_t x = (i * 8 + (lane >> 3) + 1) * 0xD1B54A32D192ED03ull;
+        x ^= x >> 32;
+        const int j = (int)__umul64hi(x * 0x9E3779B97F4A7C15ull, (uint64_t)k);
+        const float *om = omega + (int64_t)j * n;
+        float acc = 0.0f;
+        for (int t = lane & 7; t < n; t += 8) acc += om[t] * sp[t];
+        acc += __shfl_xor(acc, 1);
+        acc += __shfl_xor(acc, 2);
+        acc += __shfl_xor(acc, 4);
+        const uint32_t b = (__float_as_uint(acc) & 0x7FFFFFFFu) >> 15;
+        const uint32_t c = b < kBinBase ? 0u : b - kBinBase;
+        if ((lane & 7) == 0) atomicAdd(&h[c < kBracketBins ? c : kBracketBins - 1], 1u);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kBracketBins; i += 1024)
+        if (h[i]) atomicAdd(&hist[i], h[i]);
+}
+
+__global__ __launch_bounds__(1024) void k_select_setup(AnalyzeArgs a) {
+    tau_setup_state(a.tau_st, a.tau_hist3, a.tau_hist_words, a.tau_rank0, 1024);
 }
 
 // The bracket: the bins of the sample's ranks 0.5 -+ 1/128, widened by three
@@ -174,12 +234,13 @@ __global__ __launch_bounds__(1024) void k_bracket_hist(const uint64_t *blist, co
 // list (regions as the list's); st->br_ok when the bracket holds the window.
 __global__ __launch_bounds__(256) void k_bracket_window(const uint64_t *blist, const unsigned int *bcnt,
                                                         const unsigned int *fine, const double *max_margin,
-                                                        TauState *st, unsigned long long *parts, int nb,
-                                                        int64_t *cand, unsigned int *ccnt) {
+                                                        TauState *st, unsigned long long *parts, int64_t *cand,
+                                                        unsigned int *ccnt) {
     __shared__ unsigned long long s_w[2][4];
     __shared__ int s_bin;
-    if (!st->br_valid) return;
+    if (!st->br_valid || st->br_over) return;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int nb = (int)(st->rg_waves / 4);  // workgroups of the pass before
     // entries below the bracket, and the rank left inside it
     unsigned long long below = 0, sum = 0;
     for (int i = t; i < nb; i += 256) below += parts[i];
@@ -313,34 +374,17 @@ __global__ __launch_bounds__(256) void k_median_mask_gather(const float *alpha, 
         vhi = (double)__uint_as_float(prefix | 0x3FFu);
         candidate_window(vlo, vhi, mm, st, blockIdx.x == 0 && threadIdx.x == 0, blo, bhi);
     }
-    // tau = fl(frac * median) is monotone in the median, which lies in
-    // [v_lo - m, v_hi + m]; both ends are widened by the rounding of the bounds
-    double mlo = vlo - mm;
-    mlo = mlo > 0.0 ? nextafter(mlo, 0.0) : 0.0;
-    const double mhi = nextafter(vhi + mm, INFINITY);
-    const double tlo = mlo > 0.0 ? nextafter(frac * mlo, 0.0) : 0.0;
-    const double thi = nextafter(frac * mhi, INFINITY);
+    double tlo, thi;
+    tau_interval(vlo, vhi, mm, frac, tlo, thi);
     if constexpr (BR) {
-        // the keys of the undecided entries are listed from below every row's t_in
-        const double a = tlo - mm;
-        float fa = (float)a;
-        if ((double)fa > a) fa = nextafterf(fa, -INFINITY);
-        dbase = fa > 0.0f ? __float_as_uint(fa) : 0u;
+        dbase = tau_defer_base(tlo, mm);
         if (blockIdx.x == 0 && threadIdx.x == 0) st->br_dbase = dbase;
     }
     float tin[W64], tout[W64];
 #pragma unroll
     for (int w = 0; w < W64; ++w) {
         const int j = 64 * w + lane;
-        const bool jv = j < k;
-        const double m = jv ? margins[j] : 0.0;
-        const double a = tlo - m, b = thi + m;
-        float fa = (float)a;
-        if ((double)fa > a) fa = nextafterf(fa, -INFINITY);
-        float fb = (float)b;
-        if ((double)fb < b) fb = nextafterf(fb, INFINITY);
-        tin[w] = fa;
-        tout[w] = fb;
+        tau_row_interval(tlo, thi, j < k ? margins[j] : 0.0, tin[w], tout[w]);
     }
     unsigned int below = 0;  // wave-uniform (a wave's entries are fewer than 2^32)
     const int64_t nrounds = (N + kPx - 1) / kPx;
@@ -355,9 +399,6 @@ __global__ __launch_bounds__(256) void k_median_mask_gather(const float *alpha, 
     }
     int64_t *creg = cand + gw * region, *dreg = didx + gw * region;
     unsigned int nc_w = 0, nd_w = 0;  // wave-uniform counts
-    auto prefix = [](unsigned long long m) {  // set bits of lower lanes
-        return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-    };
     // entry base + lane (base wave-uniform) at place `at` of a region, d above it
     auto put = [&](int64_t *reg, uint32_t at, int64_t base, uint32_t d) {
         const uint64_t e = (uint64_t)base + (uint32_t)lane;
@@ -399,7 +440,7 @@ __global__ __launch_bounds__(256) void k_median_mask_gather(const float *alpha, 
                 below += (unsigned int)__popcll(__builtin_amdgcn_uicmp(x, blo, kUlt));
                 const unsigned long long cm = __builtin_amdgcn_uicmp(d, bhi - blo, kUle);
                 if (cm) {
-                    if (__builtin_amdgcn_inverse_ballot_w64(cm)) put(creg, nc_w + prefix(cm), (p0 + i) * k + 64 * w, BR ? d : 0u);
+                    if (__builtin_amdgcn_inverse_ballot_w64(cm)) put(creg, nc_w + lane_prefix(cm), (p0 + i) * k + 64 * w, BR ? d : 0u);
                     nc_w += (unsigned int)__popcll(cm);
                 }
                 const float f = __uint_as_float(x);
@@ -408,7 +449,7 @@ __global__ __launch_bounds__(256) void k_median_mask_gather(const float *alpha, 
                 out_hi = write_lane((int)(uint32_t)(inb >> 32), i * W64 + w, out_hi);
                 const unsigned long long dm = ~(inb | __builtin_amdgcn_fcmpf(f, tout[w], kOgt));  // NaN: deferred
                 if (dm) {
-                    if (__builtin_amdgcn_inverse_ballot_w64(dm)) put(dreg, nd_w + prefix(dm), (p0 + i) * k + 64 * w, BR ? min(x - dbase, kPackMax) : 0u);
+                    if (__builtin_amdgcn_inverse_ballot_w64(dm)) put(dreg, nd_w + lane_prefix(dm), (p0 + i) * k + 64 * w, BR ? min(x - dbase, kPackMax) : 0u);
                     nd_w += (unsigned int)__popcll(dm);
                 }
                 // one entry at a time: keeps the ballots from piling up in
@@ -531,7 +572,6 @@ hipError_t median_bracket(const LaunchCtx &lc, const float *alpha, int64_t N, in
                           unsigned int *ccnt, unsigned long long *parts, int64_t *didx, unsigned int *dcnt,
                           uint64_t *masks, unsigned int *br_hist) {
     const int blocks = (int)(median_gather_waves(N) / 4);
-    unsigned int *fine = br_hist + kBracketBins;
     hipLaunchKernelGGL(k_bracket_sample, dim3(kSampleBlocks), dim3(1024), 0, lc.stream, alpha, N * k, br_hist);
     hipLaunchKernelGGL(k_bracket_pick, dim3(1), dim3(1024), 0, lc.stream, br_hist, max_margin, st);
 #define CS_BR_LAUNCH(WW)                                                                                           \
@@ -544,11 +584,31 @@ hipError_t median_bracket(const LaunchCtx &lc, const float *alpha, int64_t N, in
         default: CS_BR_LAUNCH(4); break;
     }
 #undef CS_BR_LAUNCH
+    return median_bracket_list(lc, max_margin, st, blist, cand, ccnt, parts, br_hist);
+}
+
+hipError_t median_bracket_list(const LaunchCtx &lc, const double *max_margin, TauState *st, const uint64_t *blist,
+                               int64_t *cand, unsigned int *ccnt, unsigned long long *parts, unsigned int *br_hist) {
+    unsigned int *fine = br_hist + kBracketBins;
     hipLaunchKernelGGL(k_bracket_hist, dim3((unsigned)(lc.num_cu / 2)), dim3(1024), 0, lc.stream, blist, ccnt, st, fine);
     // (the list's counts are read and replaced by the wave that owns the region)
     hipLaunchKernelGGL(k_bracket_window, dim3((unsigned)lc.num_cu), dim3(256), 0, lc.stream, blist, ccnt, fine,
-                       max_margin, st, parts, blocks, cand, ccnt);
+                       max_margin, st, parts, cand, ccnt);
     return hipGetLastError();
+}
+
+hipError_t median_bracket_analyze(const LaunchCtx &lc, const AnalyzeArgs &a, int precision, unsigned int *br_hist,
+                                  int64_t *cand) {
+    hipLaunchKernelGGL(k_select_setup, dim3(1), dim3(1024), 0, lc.stream, a);
+    hipLaunchKernelGGL(k_patch_sample, dim3(kPatchSampleBlocks + 1), dim3(1024), 0, lc.stream, a, br_hist);
+    hipLaunchKernelGGL(k_bracket_pick, dim3(1), dim3(1024), 0, lc.stream, br_hist, a.tau_max_margin, a.tau_st);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    AnalyzeArgs b = a;
+    b.sel_st = a.tau_st;
+    b.tau_st = nullptr;
+    if ((e = launch_analyze(lc, b, precision)) != hipSuccess) return e;
+    return median_bracket_list(lc, a.tau_max_margin, a.tau_st, a.sel_blist, cand, a.sel_bcnt, a.sel_parts, br_hist);
 }
 
 int64_t median_gather_waves(int64_t N) {

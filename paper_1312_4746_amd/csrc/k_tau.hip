@@ -45,7 +45,7 @@ __global__ __launch_bounds__(256) void k_tau_init(TauState *st, unsigned long lo
         st->n_d = 0;
         st->n_r = 0;
         st->lo = st->hi = 0.0;
-        st->br_valid = st->br_ok = 0;
+        st->br_valid = st->br_ok = st->br_over = 0;
         st->median = 0.0;
         st->tau = 0.0;
     }
@@ -419,6 +419,7 @@ __global__ __launch_bounds__(64) void k_list_compact(const int64_t *cand, const 
                                                      const unsigned int *dcnt, const unsigned long long *doff,
                                                      const TauState *st, int64_t *ccomp, int64_t *dcomp) {
     const int64_t r = blockIdx.x, region = (int64_t)st->rg_size;
+    if (r >= (int64_t)st->rg_waves) return;
     const bool cfit = (int64_t)st->ncand <= kListCap, dfit = (int64_t)st->n_d <= kListCap;
     if (cfit) {
         const unsigned int n = ccnt[r];

@@ -1,7 +1,8 @@
 // Patch analysis for patches up to 11 x 11 on gfx950 (instantiated per patch
 // size by the k_patch*.hip files; larger patches: k_analyze.hip): normalised
 // Gaussian-masked gray patches (Sec. 3.1), the contraction a = O s on MFMA
-// (Sec. 2) and its output, FP32 vectors or co-support masks.
+// (Sec. 2) and its output: FP32 vectors, co-support masks, or (kPatchSelect)
+// vectors and, of the FP32 products, the masks and lists of a median's bracket.
 //
 // Bound by the FP32 matrix units at large k (11 x 11, k = 242: two thirds of a
 // tile's time; the halo, the statistics and the patches take the rest) and by
@@ -9,6 +10,10 @@
 // (BF16 products: 634 -> 340 us); 2048 x 2048, 7 x 7, k = 98: 964 -> 823 us
 // (BF16 628 -> 538 us, 3.1 TB/s of stores); 481 x 321, 11 x 11, k = 242: 180 ->
 // 136 us (before: one workgroup per tile, the operator read by each).
+// kPatchSelect is bound by its vector instructions (some 20 per 64 entries for the
+// tests and lists): 2048 x 2048, 7 x 7, k = 98, FP32 and BF16 products 1173 us,
+// where the two analyses and a pass over the FP32 vectors took 1870 us; without
+// listing anything 1090 us.
 //
 // Persistent workgroups of four waves walk tiles of TP pixels of one image
 // row.  Wave w keeps the operator rows of the 16-row blocks w, w + 4, ... in
@@ -57,7 +62,7 @@ struct PatchTile {
     static constexpr int hw = TP + 2 * h, halo = P * hw, halo_it = (halo + 255) / 256;
 };
 
-enum { kPatchAlpha = 0, kPatchMasks = 1 };
+enum { kPatchAlpha = 0, kPatchMasks = 1, kPatchSelect = 2 };
 
 // LDS of the mask output: the tile's co-support pieces (pixel major), its
 // entries in between (one word of pixels per operator row), and the hand-offs
@@ -190,13 +195,26 @@ __device__ __noinline__ void resolve_near(const float *omega, const double *wmas
 // Workgroups per compute unit (waves per SIMD) that the operator fragments
 // leave registers for.
 constexpr int patch_waves(int p, int jb) { return jb * ((p * p + 3) / 4) <= 32 ? 4 : jb * ((p * p + 3) / 4) <= 64 ? 3 : 2; }
+// The same for kPatchSelect, from an estimate of its registers (at 7 x 7, k = 98,
+// BF16, four waves with 15 registers spilled: 1173 us, three without: 1227 us).
+constexpr int patch_sel_regs(int p, int jb, bool bf16) {
+    const int rs = ((p * p + 3) / 4 + 3) / 4 * 4;
+    return 40 + 4 * ((p * (64 + p - 1) + 255) / 256) + jb * (rs + 14) + 18 + (bf16 ? jb * rs / 2 : 0);
+}
+constexpr int patch_waves_of(int p, int jb, int prec, int out) {
+    if (out != kPatchSelect) return patch_waves(p, jb);
+    const int r = patch_sel_regs(p, jb, prec == CS_BF16);
+    return r <= 150 ? 4 : r <= 200 ? 3 : 2;
+}
 
 template <int P, int JB, int PREC, int OUT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(patch_waves(P, JB))))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(patch_waves_of(P, JB, PREC, OUT))))
 void k_patch(AnalyzeArgs a, int tiles_x, int ntiles) {
     using T = PatchTile<P>;
     constexpr int h = T::h, n = T::n, KF = T::KF, RS = T::RS, ss = T::ss, TP = T::TP, hw = T::hw;
-    constexpr bool kF32 = PREC == CS_FP32;
+    constexpr bool kSel = OUT == kPatchSelect;
+    constexpr bool kB16 = PREC == CS_BF16, kF32 = !kB16 || kSel;  // the selection runs on the FP32 vectors
+    if (a.skip && a.skip->br_ok) return;
     __shared__ double gh2[2][T::halo];  // this tile's gray halo and the next one's
     __shared__ double s_c1[hw], s_c2[hw];
     __shared__ double s_mu[TP], s_ri[TP];  // mu and 1 / nu (0 for a zero patch)
@@ -226,7 +244,7 @@ void k_patch(AnalyzeArgs a, int tiles_x, int ntiles) {
     // operator fragments: row 16 (jw + 4 u) + jl, run g (rows past k repeat
     // the last, their outputs are not used; entries past n are 0)
     float bf[kF32 ? JB : 1][kF32 ? RS : 1];
-    s16x4 bb[kF32 ? 1 : JB][kF32 ? 1 : RS / 4];
+    s16x4 bb[kB16 ? JB : 1][kB16 ? RS / 4 : 1];
 #pragma unroll
     for (int u = 0; u < JB; ++u) {
         const int j = 16 * (jw + 4 * u) + jl;
@@ -244,10 +262,8 @@ void k_patch(AnalyzeArgs a, int tiles_x, int ntiles) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const float x = 4 * q + i < KF ? v[i] : 0.0f;
-                if constexpr (kF32)
-                    bf[u][4 * q + i] = x;
-                else
-                    bb[u][q][i] = bf16_rne(x);
+                if constexpr (kF32) bf[u][4 * q + i] = x;
+                if constexpr (kB16) bb[u][q][i] = bf16_rne(x);
             }
         }
     }
@@ -261,6 +277,43 @@ void k_patch(AnalyzeArgs a, int tiles_x, int ntiles) {
         }
     }
     unsigned long long nrecomp = 0;
+    // kPatchSelect: the bracket, the rows' undecided intervals, the masks of
+    // this tile and the last, this wave's list regions
+    __shared__ float s_tin[kSel ? 256 : 1], s_tout[kSel ? 256 : 1];
+    __shared__ uint64_t s_mk[2][kSel ? TP * 4 : 1];
+    uint32_t blo = 0xFFFFFFFFu, bspan = 0, dbase = 0;
+    uint64_t *breg = nullptr, *dreg = nullptr;
+    uint32_t nb_w = 0, nd_w = 0, below = 0, region = 0, over = 0;  // wave-uniform
+    uint64_t jvm[kSel ? JB : 1];  // the lanes that have a row
+    if constexpr (kSel) {
+        float ti = INFINITY, to = INFINITY;  // no bracket: nothing is listed
+        if (a.sel_st->br_valid) {
+            const double mm = *a.tau_max_margin;
+            double tlo, thi;
+            blo = a.sel_st->br_lo;
+            bspan = a.sel_st->br_hi - blo;
+            tau_interval((double)__uint_as_float(blo), (double)__uint_as_float(blo + bspan), mm, a.sel_frac, tlo, thi);
+            dbase = tau_defer_base(tlo, mm);
+            tau_row_interval(tlo, thi, tid < a.k ? a.tau_margins[tid] : 0.0, ti, to);
+        }
+        s_tin[tid] = ti;
+        s_tout[tid] = to;
+        s_mk[0][tid] = s_mk[1][tid] = 0;
+        // what may be listed before a block that may list all its entries
+        region = (uint32_t)a.sel_region > 256u * JB ? (uint32_t)a.sel_region - 256u * JB : 0u;
+#pragma unroll
+        for (int u = 0; u < JB; ++u) jvm[u] = __ballot(16 * (jw + 4 * u) + jl < a.k);
+        const int64_t at = ((int64_t)blockIdx.x * 4 + wave) * a.sel_region;
+        breg = a.sel_blist + at;
+        dreg = a.sel_dlist + at;
+    }
+    // entry base + place (base wave-uniform) at `at` of a region, d above it
+    auto put = [](uint64_t *reg, uint32_t at, uint64_t base, uint32_t place, uint32_t d) {
+        const uint64_t e = base + place;
+        uint32_t *o = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(reg) + 8u * at);
+        const uint2 v = make_uint2((uint32_t)e, d << (kPackShift - 32) | (uint32_t)(e >> 32));
+        *reinterpret_cast<uint2 *>(o) = v;
+    };
 
     // places of this thread's halo entries, (row << 16) | column (32-bit
     // offsets from wave-uniform bases throughout: the operator fragments leave
@@ -301,6 +354,8 @@ void k_patch(AnalyzeArgs a, int tiles_x, int ntiles) {
         request(tile);
         arrive(tile, gh2[0]);
     }
+    int64_t last_pix = 0;  // kPatchSelect: the last tile's masks, still in LDS
+    int last_words = 0;
     for (; tile < ntiles; tile += gridDim.x, par ^= 1) {
         const double *gh = gh2[par];
         const int row = tile / tiles_x, c0 = (tile - row * tiles_x) * TP;
@@ -311,7 +366,8 @@ void k_patch(AnalyzeArgs a, int tiles_x, int ntiles) {
         }
         __syncthreads();
         // 2. statistics: column sums, then each pixel's P columns
-        if (wave < (hw + 63) / 64) {  // whole waves: a lane's weight is read from lanes past the last column too
+        static_assert(hw <= 128, "columns of two waves");
+        if (wave < 2) {  // whole waves: a lane's weight is read from lanes past the last column too
             const int c = tid < hw ? tid : hw - 1;
             double c1 = 0.0, c2 = 0.0;
 #pragma unroll
@@ -324,6 +380,8 @@ void k_patch(AnalyzeArgs a, int tiles_x, int ntiles) {
                 s_c1[c] = c1;
                 s_c2[c] = c2;
             }
+        } else if constexpr (kSel) {
+            for (int idx = tid - 128; idx < last_words; idx += 128) a.masks[last_pix * W64 + idx] = s_mk[par ^ 1][idx];
         }
         __syncthreads();
         if (tid < TP) {
@@ -376,9 +434,10 @@ void k_patch(AnalyzeArgs a, int tiles_x, int ntiles) {
         // 4. a = O s
         const int64_t pix0 = (int64_t)row * a.W + c0;
         const int nrb = (valid_px + 15) / 16;
+        const int left = valid_px - 4 * g;
         auto block = [&](int rb, auto first) __attribute__((always_inline)) {
             const f32x4 *sr = reinterpret_cast<const f32x4 *>(s + (rb * 16 + jl) * ss + g * RS);
-            f32x4 tot[JB];
+            f32x4 tot[kF32 ? JB : 1];
             if constexpr (kF32) {
 #pragma unroll
                 for (int q0 = 0; q0 < RS / 4; q0 += T::CQ) {
@@ -400,22 +459,80 @@ void k_patch(AnalyzeArgs a, int tiles_x, int ntiles) {
                     for (int u = 0; u < JB; ++u) tot[u] = q0 == 0 ? acc[u] : tot[u] + acc[u];
                     __builtin_amdgcn_sched_barrier(0);  // one chain's accumulators at a time
                 }
-            } else {
+            }
+            f32x4 hot[kB16 ? JB : 1];  // the BF16 products
+            if constexpr (kB16) {
 #pragma unroll
-                for (int u = 0; u < JB; ++u) tot[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int u = 0; u < JB; ++u) hot[u] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int q = 0; q < RS / 4; ++q) {
                     const f32x4 av = sr[q];
-                    s16x4 ab;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) ab[i] = bf16_rne(av[i]);
+                    const s16x4 ab = __builtin_bit_cast(
+                        s16x4, make_uint2(bf16_pair(av[0], av[1]), bf16_pair(av[2], av[3])));
 #pragma unroll
                     for (int u = 0; u < JB; ++u)
-                        tot[u] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ab, bb[u][q], tot[u], 0, 0, 0);
+                        hot[u] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ab, bb[u][q], hot[u], 0, 0, 0);
                 }
             }
             // the next tile's halo arrives ahead of this one's stores
             if (first.value && more) arrive(tile + gridDim.x, gh2[par ^ 1]);
+            if constexpr (kSel) {
+                // a list that is nearly full starts again: its call ends in the
+                // general selection
+                if (nb_w > region || nd_w > region) {
+                    over = 1;
+                    nb_w = nd_w = 0;
+                }
+                float ti[JB], to[JB];
+#pragma unroll
+                for (int u = 0; u < JB; ++u) {
+                    ti[u] = s_tin[16 * (jw + 4 * u) + jl];
+                    to[u] = s_tout[16 * (jw + 4 * u) + jl];
+                }
+                int col = 0;  // lane 8 u + 2 r + h: the mask pieces of pixels 8 h + r and 8 h + 4 + r
+                uint64_t first_e = (uint64_t)(pix0 + rb * 16) * (uint64_t)a.k + 16 * jw;  // wave-uniform
+#pragma unroll
+                for (int r = 0; r < 4; ++r, first_e += a.k) {
+                    const uint64_t pvm = __builtin_amdgcn_sicmp(left, rb * 16 + r, kSgt);
+#pragma unroll
+                    for (int u = 0; u < JB; ++u) {
+                        if (jw + 4 * u >= nblk) break;
+                        const uint64_t live = pvm & jvm[u];
+                        const uint64_t e0 = first_e + 64 * u;
+                        if (__builtin_amdgcn_inverse_ballot_w64(live)) {
+                            float *out = a.alpha + e0 + lane_off;
+                            if constexpr (kB16)
+                                *out = hot[u][r];
+                            else
+                                *out = tot[u][r];
+                        }
+                        // rows past k and pixels past the row end get the key of
+                        // +inf, which every test rejects
+                        const float f = __builtin_amdgcn_inverse_ballot_w64(live) ? fabsf(tot[u][r]) : INFINITY;
+                        const uint32_t x = __float_as_uint(f), d = x - blo;
+                        below += (uint32_t)__popcll(__builtin_amdgcn_uicmp(x, blo, kUlt));
+                        const uint64_t cm = __builtin_amdgcn_uicmp(d, bspan, kUle);
+                        if (__builtin_amdgcn_inverse_ballot_w64(cm)) put(breg, nb_w + lane_prefix(cm), e0, lane_off, d);
+                        nb_w += (uint32_t)__popcll(cm);
+                        const uint64_t inb = __builtin_amdgcn_fcmpf(f, ti[u], kOle);
+                        col = write_lane((int)(uint32_t)inb, u * 8 + r * 2, col);
+                        col = write_lane((int)(uint32_t)(inb >> 32), u * 8 + r * 2 + 1, col);
+                        const uint64_t dm = ~(inb | __builtin_amdgcn_fcmpf(f, to[u], kOgt));  // NaN: undecided
+                        if (__builtin_amdgcn_inverse_ballot_w64(dm))
+                            put(dreg, nd_w + lane_prefix(dm), e0, lane_off, min(x - dbase, kPackMax));
+                        nd_w += (uint32_t)__popcll(dm);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+                const int jb = jw + 4 * (lane >> 3);
+                if (lane < 8 * JB && jb < nblk) {
+                    uint16_t *mk = reinterpret_cast<uint16_t *>(s_mk[par]) + jb;
+                    const int il = rb * 16 + 8 * (lane & 1) + (lane >> 1 & 3);
+                    mk[il * 4 * W64] = (uint16_t)col;
+                    mk[(il + 4) * 4 * W64] = (uint16_t)((uint32_t)col >> 16);
+                }
+                return;
+            }
 #pragma unroll
             for (int u = 0; u < JB; ++u) {
                 const int jb = jw + 4 * u;
@@ -428,9 +545,19 @@ void k_patch(AnalyzeArgs a, int tiles_x, int ntiles) {
                     const bool pv = rb * 16 + 4 * g + r < valid_px;
                     if constexpr (OUT == kPatchAlpha) {
                         float *out = a.alpha + ((pix0 + rb * 16 + r) * a.k + 16 * jb);  // wave-uniform
-                        if (pv && jv) out[lane_off] = tot[u][r];
-                    } else {
-                        const float av = fabsf(tot[u][r]);
+                        if (pv && jv) {
+                            if constexpr (kB16)
+                                out[lane_off] = hot[u][r];
+                            else
+                                out[lane_off] = tot[u][r];
+                        }
+                    }
+                    if constexpr (OUT == kPatchMasks) {
+                        float av;
+                        if constexpr (kB16)
+                            av = fabsf(hot[u][r]);
+                        else
+                            av = fabsf(tot[u][r]);
                         const bool in = av <= tin[u] && pv && jv;
                         if (!(av <= tin[u]) && !(av > tout[u]) && pv && jv) in_between |= 1u << r;
                         const unsigned long long bits = __ballot(in);
@@ -465,7 +592,31 @@ void k_patch(AnalyzeArgs a, int tiles_x, int ntiles) {
                                 (lds_ptr<double>)s_ri, (lds_ptr<PatchNear>)nr);
             for (int idx = tid; idx < valid_px * W64; idx += 256) a.masks[pix0 * W64 + idx] = nr->mk[idx];
         }
+        if constexpr (kSel) {
+            last_pix = pix0;
+            last_words = valid_px * W64;
+        }
         __syncthreads();
+    }
+    if constexpr (kSel) {
+        for (int idx = tid; idx < last_words; idx += 256) a.masks[last_pix * W64 + idx] = s_mk[par ^ 1][idx];
+        __shared__ uint32_t s_below[4];
+        if (lane == 0) {
+            const int w = blockIdx.x * 4 + wave;
+            a.sel_bcnt[w] = nb_w;
+            a.sel_dcnt[w] = nd_w;
+            if (over) a.sel_st->br_over = 1;
+            s_below[wave] = below;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            a.sel_parts[blockIdx.x] = (unsigned long long)s_below[0] + s_below[1] + s_below[2] + s_below[3];
+            if (blockIdx.x == 0) {
+                a.sel_st->rg_waves = 4 * gridDim.x;
+                a.sel_st->rg_size = (long long)a.sel_region;
+                a.sel_st->br_dbase = dbase;
+            }
+        }
     }
     if constexpr (OUT == kPatchMasks) {
 #pragma unroll
@@ -473,9 +624,10 @@ void k_patch(AnalyzeArgs a, int tiles_x, int ntiles) {
         if (a.recomputed && lane == 0 && nrecomp) atomicAdd(a.recomputed, nrecomp);
     }
     // the set-up of the median selection that follows this kernel
-    if (a.tau_st && blockIdx.x == 0)
-        tau_setup(a.tau_st, a.tau_hist3, a.tau_hist_words, a.omega, a.k, n, a.tau_coef, a.tau_rank0, a.tau_margins,
-                  a.tau_max_margin);
+    if (a.tau_st && blockIdx.x == 0) {
+        tau_setup_state(a.tau_st, a.tau_hist3, a.tau_hist_words, a.tau_rank0, 256);
+        tau_setup_margins(a.omega, a.k, n, a.tau_coef, a.tau_margins, a.tau_max_margin, 256);
+    }
 }
 
 template <int P, int JB, int PREC, int OUT>
@@ -484,9 +636,19 @@ hipError_t launch_patch_k(const LaunchCtx &lc, const AnalyzeArgs &a) {
     const int tiles_x = (a.W + T::TP - 1) / T::TP;
     const int64_t ntiles = (int64_t)tiles_x * a.H;
     // as many workgroups as run at once: one wave per SIMD each
-    const int64_t cap = (int64_t)lc.num_cu * patch_waves(P, JB);
-    hipLaunchKernelGGL((k_patch<P, JB, PREC, OUT>), dim3((unsigned)(ntiles < cap ? ntiles : cap)), dim3(256), 0,
-                       lc.stream, a, tiles_x, (int)ntiles);
+    const int64_t cap = (int64_t)lc.num_cu * patch_waves_of(P, JB, PREC, OUT);
+    int64_t blocks = ntiles < cap ? ntiles : cap;
+    if constexpr (OUT == kPatchSelect) {
+        if (blocks > kGatherBlocks) blocks = kGatherBlocks;
+        // the waves' regions share the lists, which have a place per entry
+        AnalyzeArgs b = a;
+        b.sel_region = (int64_t)a.H * a.W * a.k / (4 * blocks);
+        hipLaunchKernelGGL((k_patch<P, JB, PREC, OUT>), dim3((unsigned)blocks), dim3(256), 0, lc.stream, b, tiles_x,
+                           (int)ntiles);
+    } else {
+        hipLaunchKernelGGL((k_patch<P, JB, PREC, OUT>), dim3((unsigned)blocks), dim3(256), 0, lc.stream, a, tiles_x,
+                           (int)ntiles);
+    }
     return hipGetLastError();
 }
 
@@ -502,6 +664,12 @@ hipError_t launch_patch_j(const LaunchCtx &lc, const AnalyzeArgs &a) {
 
 template <int P>
 hipError_t launch_patch_p(const LaunchCtx &lc, const AnalyzeArgs &a, int precision) {
+    if (a.sel_st) {
+        if constexpr (P <= kPatchSelMax)
+            return precision == CS_BF16 ? launch_patch_j<P, CS_BF16, kPatchSelect>(lc, a)
+                                        : launch_patch_j<P, CS_FP32, kPatchSelect>(lc, a);
+        return hipErrorInvalidValue;
+    }
     if (a.masks)
         return precision == CS_BF16 ? launch_patch_j<P, CS_BF16, kPatchMasks>(lc, a)
                                     : launch_patch_j<P, CS_FP32, kPatchMasks>(lc, a);

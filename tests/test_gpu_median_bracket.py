@@ -11,13 +11,15 @@ from test_gpu_parity import ctx, dev  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 
-def _check(ctx, rgb, p, om):
-    a, m, tau = ctx.cosupport_median(rgb, p, 1.5, om, 0.3)
-    a2 = ctx.analyze_patches(rgb, p, 1.5, om)
-    assert torch.equal(a.view(torch.int32), a2.view(torch.int32))
-    tau2 = ctx.tau_median(rgb, p, 1.5, om, a2, 0.3)
-    assert float(tau) == tau2
-    assert torch.equal(m, ctx.cosupport(rgb, p, 1.5, om, tau2, alpha=a2))
+def _check(ctx, rgb, p, om, precisions=("fp32", "bf16")):
+    for prec in precisions:
+        a, m, tau = ctx.cosupport_median(rgb, p, 1.5, om, 0.3, precision=prec)
+        a2 = ctx.analyze_patches(rgb, p, 1.5, om, precision=prec)
+        assert torch.equal(a.view(torch.int32), a2.view(torch.int32))
+        a2 = ctx.analyze_patches(rgb, p, 1.5, om)
+        tau2 = ctx.tau_median(rgb, p, 1.5, om, a2, 0.3)
+        assert float(tau) == tau2
+        assert torch.equal(m, ctx.cosupport(rgb, p, 1.5, om, tau2, alpha=a2))
 
 
 def _image(H, W, seed):
@@ -31,10 +33,11 @@ def _operator(k, p, seed):
     return (om / om.norm(dim=1, keepdim=True)).cuda()
 
 
-@pytest.mark.parametrize("H,W,p,k", [(725, 727, 3, 64), (600, 601, 5, 98), (513, 515, 7, 130), (449, 451, 11, 242),
-                                     (400, 401, 3, 256), (641, 643, 13, 100)])
+@pytest.mark.parametrize("H,W,p,k", [(900, 1001, 3, 16), (700, 705, 5, 31), (725, 727, 3, 64), (600, 601, 5, 98),
+                                     (513, 515, 7, 130), (400, 447, 7, 242), (300, 287, 9, 160), (280, 321, 9, 256),
+                                     (449, 451, 11, 242), (400, 401, 3, 256), (641, 643, 13, 100)])
 def test_shapes(ctx, H, W, p, k):  # noqa: F811
-    assert H * W * k >= 1 << 25
+    assert H * W * k >= 12 << 20
     _check(ctx, _image(H, W, k), p, _operator(k, p, p))
 
 
@@ -50,6 +53,16 @@ def test_sample_favours_rows(ctx):  # noqa: F811
     om = _operator(k, 3, 5)
     om[rare] *= 0.25
     _check(ctx, _image(H, W, 6), 3, om)
+    _check(ctx, _image(H, W, 6), 13, torch.cat([om.repeat(1, 18), om[:, :7]], 1).contiguous(), ("fp32",))
+
+
+def test_ties_fill_a_list(ctx):  # noqa: F811
+    # few distinct patches: one magnitude holds the median and a large share of
+    # the entries, more than the places of the waves that meet them
+    H, W, k = 900, 900, 17
+    rgb = _image(2, 2, 12).repeat(1, H // 2, W // 2).contiguous()
+    om = _operator(1, 3, 13).repeat(k, 1).contiguous()
+    _check(ctx, rgb, 3, om)
 
 
 def test_median_zero_and_gap(ctx):  # noqa: F811
