@@ -235,9 +235,11 @@ hipError_t tau_finish(const LaunchCtx &lc, const float *rgb, int H, int W, int p
                       double *tau_out, const double *pstats, const unsigned int *ccnt = nullptr,
                       const FusedLists *fl = nullptr);
 // Device counters of a context that are zero between calls (each use resets
-// its own): [kCtrSampleCount] the sample-count workgroups done,
+// its own): [kCtrSampleCount] the groups of sample-count workgroups done, those
+// done of group g at kCtrGroup0 + g kCtrStride from there (a cache line each),
 // [kCtrNonFinite] the flag of the optional finite check of the inputs.
-constexpr int kCtrSampleCount = 0, kCtrNonFinite = 1, kCtrWords = 64;
+constexpr int kCtrSampleCount = 0, kCtrNonFinite = 1;
+constexpr int kCtrGroups = 16, kCtrStride = 32, kCtrGroup0 = 64, kCtrWords = kCtrGroup0 + kCtrGroups * kCtrStride;
 // Sets *flag (device, zero before) to 1 when any of the n floats at p is a NaN
 // or an infinity.
 hipError_t launch_check_finite(const LaunchCtx &lc, const float *p, int64_t n, int levels, unsigned int *flag);

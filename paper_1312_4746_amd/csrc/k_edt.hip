@@ -9,15 +9,28 @@
 //     own segment both ways (lanes own adjacent columns, so loads coalesce);
 //  2. rows: one workgroup per (label, row) stages f(q) = squared column
 //     distance of every column q in LDS, and the smallest f over blocks of 16
-//     columns; each thread owns columns c and walks outward block by block,
-//     keeping the best (c - q)^2 + f(q).  A block is scanned only when its
-//     nearest column and its smallest f could still beat the best, and the walk
-//     stops once the nearest column of the next blocks is at least that far.
+//     columns and over runs of kWalk blocks; each thread owns columns c and
+//     walks outward block by block, keeping the best (c - q)^2 + f(q).  A block
+//     is scanned only when its nearest column and its smallest f could still
+//     beat the best, a run is passed over when none of its blocks could, and
+//     the walk stops once the nearest column of the next blocks is at least
+//     that far.
+//
+// The row pass is bound by its vector instructions.  1024 x 1024, 16 labels: 495 ->
+// 298 us with the runs (most of a walk passes far blocks of other labels' samples)
+// and a multiply-add per column scanned; 481 x 321: 33 -> 28 us.  The listed form
+// waits for its loads: 2048 x 2048, 1171 -> 594 us with kWalkAhead minima and whole
+// blocks requested together (runs, or an upper bound from the minima before the
+// first scan, measured 624 and 657 us).  The column pass likewise: 220 -> 80 us
+// with kSegAhead segments at a time.
 #include "cs_internal.h"
 
 namespace cs {
 
 constexpr int kSegRows = 16;
+constexpr int kSegAhead = 8;  // segments of a column read together in the search for the nearest seed row
+constexpr int kWalk = 8;       // blocks of a row, on each side, that the row pass passes over together
+constexpr int kWalkAhead = 4;  // ... and whose minima the listed pass reads together
 constexpr int kNoSeed = -1;
 constexpr int kRowBlk = 16;  // columns per block of the row pass
 constexpr int32_t kInf = 0x3FFFFFFF;
@@ -54,20 +67,20 @@ __global__ __launch_bounds__(64) void k_edt_col_fill(const uint8_t *seeds, int H
     const int64_t N = (int64_t)H * W;
     const int64_t sbase = (int64_t)l * nseg * W + c;
     int above = kNoSeed;  // last seed row in the segments above
-    for (int s = seg - 1; s >= 0; --s) {
-        const int v = last[sbase + (int64_t)s * W];
-        if (v >= 0) {
-            above = v;
-            break;
-        }
+    for (int s0 = seg - 1; s0 >= 0 && above < 0; s0 -= kSegAhead) {
+        int v[kSegAhead];
+#pragma unroll
+        for (int i = 0; i < kSegAhead; ++i) v[i] = last[sbase + (int64_t)max(s0 - i, 0) * W];
+#pragma unroll
+        for (int i = kSegAhead - 1; i >= 0; --i) above = v[i] >= 0 ? v[i] : above;
     }
     int below = kNoSeed;  // first seed row in the segments below
-    for (int s = seg + 1; s < nseg; ++s) {
-        const int v = first[sbase + (int64_t)s * W];
-        if (v >= 0) {
-            below = v;
-            break;
-        }
+    for (int s0 = seg + 1; s0 < nseg && below < 0; s0 += kSegAhead) {
+        int v[kSegAhead];
+#pragma unroll
+        for (int i = 0; i < kSegAhead; ++i) v[i] = first[sbase + (int64_t)min(s0 + i, nseg - 1) * W];
+#pragma unroll
+        for (int i = kSegAhead - 1; i >= 0; --i) below = v[i] >= 0 ? v[i] : below;
     }
     const uint8_t *sd = seeds + (int64_t)l * N + c;
     int32_t *cr = colrow + (int64_t)l * N + c;
@@ -98,28 +111,47 @@ __global__ __launch_bounds__(64) void k_edt_col_fill(const uint8_t *seeds, int H
     }
 }
 
+// Smallest (c - q)^2 + f(q) over the columns q = q0 + i of a block from g_i = f(q0
+// + i) + i^2: with e = c - q0 it is e^2 + min (g_i - 2 e i), one multiply-add per
+// column and half a three-way minimum.
+__device__ __forceinline__ int block_best(const int (&g)[kRowBlk], int e) {
+    const int e2 = -2 * e;
+    int m = g[0];
+#pragma unroll
+    for (int i = 1; i < kRowBlk; ++i) m = min(m, __mul24(e2, i) + g[i]);
+    return __mul24(e, e) + m;
+}
+
 __global__ __launch_bounds__(1024) void k_edt_rows(const int32_t *colrow, int H, int W,
                                                     int32_t *d2, int32_t *nearest) {
     extern __shared__ int32_t lds[];
     const int nb = (W + kRowBlk - 1) / kRowBlk;
-    // f: squared column distance, kInf where the column has no seed, padded to
+    // f: squared column distance plus the square of the column's place in its
+    // block, kInf instead of the distance where the column has no seed, padded to
     // whole blocks with kInf (16-byte aligned: blocks are read as int4)
     int32_t *f = lds;
     int32_t *rowof = lds + nb * kRowBlk;      // nearest seed row of each column
     int32_t *fmin = lds + 2 * nb * kRowBlk;   // smallest f over each block
+    int32_t *wmin = fmin + nb;                // smallest f over it and the kWalk - 1 blocks after it
     const int r = blockIdx.x, l = blockIdx.y;
     const int64_t N = (int64_t)H * W;
     const int32_t *cr = colrow + (int64_t)l * N + (int64_t)r * W;
     for (int c = threadIdx.x; c < nb * kRowBlk; c += blockDim.x) {
         const int q = c < W ? cr[c] : -1;
         rowof[c] = q;
-        f[c] = q < 0 ? kInf : (r - q) * (r - q);
+        f[c] = (q < 0 ? kInf : (r - q) * (r - q)) + (c % kRowBlk) * (c % kRowBlk);
     }
     __syncthreads();
     for (int b = threadIdx.x; b < nb; b += blockDim.x) {
         int m = kInf;
-        for (int q = b * kRowBlk; q < b * kRowBlk + kRowBlk; ++q) m = min(m, f[q]);
+        for (int i = 0; i < kRowBlk; ++i) m = min(m, f[b * kRowBlk + i] - i * i);
         fmin[b] = m;
+    }
+    __syncthreads();
+    for (int b = threadIdx.x; b < nb; b += blockDim.x) {
+        int m = kInf;
+        for (int u = 0; u < kWalk; ++u) m = min(m, fmin[min(b + u, nb - 1)]);
+        wmin[b] = m;
     }
     __syncthreads();
     int32_t *dd = d2 + (int64_t)l * N + (int64_t)r * W;
@@ -130,44 +162,45 @@ __global__ __launch_bounds__(1024) void k_edt_rows(const int32_t *colrow, int H,
         // that block, the first in ascending order with the smallest value.
         // Ties go as in a one-by-one scan: the own column first, then the
         // blocks in walk order, then ascending columns.
-        int best = f[c], bb = -1;
+        const int cb = c / kRowBlk, ci = c - cb * kRowBlk;
+        int best = f[c] - ci * ci, bb = -1;
         auto scan = [&](int b) {
             const int4 *f4 = reinterpret_cast<const int4 *>(f + b * kRowBlk);
             const int4 v0 = f4[0], v1 = f4[1], v2 = f4[2], v3 = f4[3];
-            const int fv[16] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w,
-                                v2.x, v2.y, v2.z, v2.w, v3.x, v3.y, v3.z, v3.w};
-            int m = best;
-#pragma unroll
-            for (int i = 0; i < kRowBlk; ++i) {
-                const int d = c - (b * kRowBlk + i);
-                m = min(m, __mul24(d, d) + fv[i]);
-            }
+            const int g[kRowBlk] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w,
+                                    v2.x, v2.y, v2.z, v2.w, v3.x, v3.y, v3.z, v3.w};
+            const int m = block_best(g, c - b * kRowBlk);
             if (m < best) {
                 best = m;
                 bb = b;
             }
         };
-        const int cb = c / kRowBlk;
         scan(cb);  // own block, every column
         // blocks outward on both sides; a block is scanned only if its
         // nearest column and smallest f could beat the best so far, and the
         // walk stops once the nearest column of the next blocks is too far
-        for (int db = 1;; ++db) {
-            const int bl = cb - db, br = cb + db;
-            const int gl = c - (bl * kRowBlk + kRowBlk - 1);  // distance to the left block's last column
-            const int gr = br * kRowBlk - c;                     // distance to the right block's first column
-            const bool lok = bl >= 0 && gl * gl < best;
-            const bool rok = br < nb && gr * gr < best;
-            if (!lok && !rok) break;
-            if (lok && gl * gl + fmin[bl] < best) scan(bl);
-            if (rok && gr * gr + fmin[br] < best) scan(br);
+        for (int d0 = 1;; d0 += kWalk) {
+            const int g0l = c - (cb - d0) * kRowBlk - (kRowBlk - 1), g0r = (cb + d0) * kRowBlk - c;
+            const bool lok0 = cb - d0 >= 0 && g0l * g0l < best, rok0 = cb + d0 < nb && g0r * g0r < best;
+            if (!lok0 && !rok0) break;
+            // nothing within the next kWalk blocks on either side
+            const bool lt = lok0 && g0l * g0l + wmin[max(cb - d0 - (kWalk - 1), 0)] < best;
+            const bool rt = rok0 && g0r * g0r + wmin[cb + d0] < best;
+            if (!lt && !rt) continue;
+            for (int u = 0; u < kWalk; ++u) {
+                const int bl = cb - d0 - u, br = cb + d0 + u;
+                const int gl = c - (bl * kRowBlk + kRowBlk - 1);  // distance to the left block's last column
+                const int gr = br * kRowBlk - c;                     // distance to the right block's first column
+                if (lt && bl >= 0 && gl * gl + fmin[bl] < best) scan(bl);
+                if (rt && br < nb && gr * gr + fmin[br] < best) scan(br);
+            }
         }
         int bq = c;
         if (bb >= 0) {
-            for (int i = kRowBlk - 1; i >= 0; --i) {
-                const int q = bb * kRowBlk + i, d = c - q;
-                if (__mul24(d, d) + f[q] == best) bq = q;
-            }
+            const int e = c - bb * kRowBlk, rest = best - __mul24(e, e);
+#pragma unroll
+            for (int i = kRowBlk - 1; i >= 0; --i)
+                if (__mul24(-2 * e, i) + f[bb * kRowBlk + i] == rest) bq = bb * kRowBlk + i;
         }
         if (best >= kInf) {  // no seed of this label anywhere (rejected before launch)
             dd[c] = -1;
@@ -220,48 +253,67 @@ __global__ __launch_bounds__(256) void k_edt_rows_list(const int32_t *colrow, co
     const int nb = (W + kRowBlk - 1) / kRowBlk;
     const int32_t *cr = colrow + (int64_t)l * N + (int64_t)r * W;
     const int32_t *fm = bmin + ((int64_t)l * H + r) * nb;
-    auto fval = [&](int q) {
-        const int s = cr[q];
-        return s < 0 ? kInf : (r - s) * (r - s);
+    // f(q) + i^2 of a block's columns q = q0 + i (16-byte loads, which need no
+    // alignment beyond the element's; past the row end, as in the full pass, kInf)
+    auto block = [&](int b, int (&g)[kRowBlk]) {
+        int rows[kRowBlk];
+        if (b * kRowBlk + kRowBlk <= W) {
+            __builtin_memcpy(rows, cr + b * kRowBlk, sizeof(rows));
+        } else {
+#pragma unroll
+            for (int i = 0; i < kRowBlk; ++i) {
+                const int q = b * kRowBlk + i;
+                rows[i] = cr[min(q, W - 1)];
+                if (q >= W) rows[i] = kNoSeed;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kRowBlk; ++i) g[i] = (rows[i] < 0 ? kInf : __mul24(r - rows[i], r - rows[i])) + i * i;
     };
-    int best = fval(c), bb = -1;
+    const int cb = c / kRowBlk;
+    const int own = cr[c];
+    int best = own < 0 ? kInf : (r - own) * (r - own), bb = -1;
     auto scan = [&](int b) {
-        int fv[kRowBlk];
-#pragma unroll
-        for (int i = 0; i < kRowBlk; ++i) {
-            const int q = b * kRowBlk + i;
-            fv[i] = q < W ? fval(q) : kInf;  // the full pass pads with kInf
-        }
-        int m = best;
-#pragma unroll
-        for (int i = 0; i < kRowBlk; ++i) {
-            const int d = c - (b * kRowBlk + i);
-            m = min(m, __mul24(d, d) + fv[i]);
-        }
+        int g[kRowBlk];
+        block(b, g);
+        const int m = block_best(g, c - b * kRowBlk);
         if (m < best) {
             best = m;
             bb = b;
         }
     };
-    const int cb = c / kRowBlk;
     scan(cb);
-    for (int db = 1;; ++db) {
-        const int bl = cb - db, br = cb + db;
-        const int gl = c - (bl * kRowBlk + kRowBlk - 1);
-        const int gr = br * kRowBlk - c;
-        const bool lok = bl >= 0 && gl * gl < best;
-        const bool rok = br < nb && gr * gr < best;
-        if (!lok && !rok) break;
-        const int ml = lok ? fm[bl] : kInf, mr = rok ? fm[br] : kInf;
-        if (lok && gl * gl + ml < best) scan(bl);
-        if (rok && gr * gr + mr < best) scan(br);
+    bool more = true;
+    for (int d0 = 1; more; d0 += kWalkAhead) {
+        int ml[kWalkAhead], mr[kWalkAhead];
+#pragma unroll
+        for (int u = 0; u < kWalkAhead; ++u) {
+            ml[u] = fm[max(cb - d0 - u, 0)];
+            mr[u] = fm[min(cb + d0 + u, nb - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < kWalkAhead; ++u) {
+            const int bl = cb - d0 - u, br = cb + d0 + u;
+            const int gl = c - (bl * kRowBlk + kRowBlk - 1);
+            const int gr = br * kRowBlk - c;
+            const bool lok = bl >= 0 && gl * gl < best;
+            const bool rok = br < nb && gr * gr < best;
+            if (!lok && !rok) {
+                more = false;
+                break;
+            }
+            if (lok && gl * gl + ml[u] < best) scan(bl);
+            if (rok && gr * gr + mr[u] < best) scan(br);
+        }
     }
     int bq = c;
     if (bb >= 0) {
-        for (int i = kRowBlk - 1; i >= 0; --i) {
-            const int q = bb * kRowBlk + i, d = c - q;
-            if (q < W && __mul24(d, d) + fval(q) == best) bq = q;
-        }
+        int g[kRowBlk];
+        block(bb, g);
+        const int e = c - bb * kRowBlk;
+#pragma unroll
+        for (int i = kRowBlk - 1; i >= 0; --i)
+            if (__mul24(e, e) + __mul24(-2 * e, i) + g[i] == best) bq = bb * kRowBlk + i;
     }
     const int64_t o = (int64_t)l * N + pix;
     if (best >= kInf) {
@@ -304,7 +356,7 @@ hipError_t launch_edt(const LaunchCtx &lc, const uint8_t *seeds, int H, int W, i
         return hipGetLastError();
     }
     const size_t nbk = (size_t)(W + kRowBlk - 1) / kRowBlk;
-    const size_t lds = sizeof(int32_t) * (2 * nbk * kRowBlk + nbk);
+    const size_t lds = sizeof(int32_t) * (2 * nbk * kRowBlk + 2 * nbk);
     hipError_t e = hipFuncSetAttribute((const void *)k_edt_rows,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
