@@ -1031,35 +1031,6 @@ static int label_loglik(cs_ctx *ctx, const float *rgb, int H, int W, const uint6
         segs.seg[l + 1] = segs.seg[l] + counts[l];
         segs.pseg[l + 1] = segs.pseg[l] + (counts[l] + kStreamChunk - 1) / kStreamChunk * kStreamChunk;
     }
-    if (fast) {
-        Timed t(ctx, "stream");
-        const float cscale = (float)std::sqrt(1.4426950408889634 / (2.0 * prm->sigma_c * prm->sigma_c));
-        PrepArgs pr{};
-        pr.recs = recs;
-        pr.k = k;
-        pr.KP = KP;
-        pr.L = L;
-        pr.segs = segs;
-        pr.Mpad = segs.pseg[L];
-        pr.cscale = cscale;
-        pr.levels = prm->colour_levels;
-        pr.feat = (uint8_t *)(ctx->ws + o_feat);
-        pr.rec = (float *)(ctx->ws + o_srec);
-        pr.rgb = rgb;
-        pr.masks = masks;
-        pr.H = H;
-        pr.W = W;
-        pr.tiles_x = tiles_x;
-        pr.ntiles = (int)ntiles;
-        pr.ksteps = KP / 128;
-        pr.ntiles_pad = ntiles_pad;
-        pr.list = listed ? pix_subset : nullptr;
-        pr.nlist = listed ? npix : 0;
-        pr.pix4 = (float4 *)(ctx->ws + o_pix4);
-        pr.aop = (uint32_t *)(ctx->ws + o_aop);
-        pr.abf = (uint4 *)(ctx->ws + o_abf);
-        HIP_TRY(launch_prep(lc, pr));
-    }
     unsigned int *fcnt = ctx->lstats;
     ParzenArgs pa{};
     pa.rgb = rgb;
@@ -1122,7 +1093,35 @@ static int label_loglik(cs_ctx *ctx, const float *rgb, int H, int W, const uint6
     pa.tiles_x = tiles_x;
     pa.ntiles_real = (int)ntiles;
     pa.ntiles_pad = (int)ntiles_pad;
-    {
+    if (fast) {
+        Timed t(ctx, "stream");
+        const float cscale = (float)std::sqrt(1.4426950408889634 / (2.0 * prm->sigma_c * prm->sigma_c));
+        PrepArgs pr{};
+        pr.recs = recs;
+        pr.k = k;
+        pr.KP = KP;
+        pr.L = L;
+        pr.segs = segs;
+        pr.Mpad = segs.pseg[L];
+        pr.cscale = cscale;
+        pr.levels = prm->colour_levels;
+        pr.feat = (uint8_t *)(ctx->ws + o_feat);
+        pr.rec = (float *)(ctx->ws + o_srec);
+        pr.rgb = rgb;
+        pr.masks = masks;
+        pr.H = H;
+        pr.W = W;
+        pr.tiles_x = tiles_x;
+        pr.ntiles = (int)ntiles;
+        pr.ksteps = KP / 128;
+        pr.ntiles_pad = ntiles_pad;
+        pr.list = listed ? pix_subset : nullptr;
+        pr.nlist = listed ? npix : 0;
+        pr.pix4 = (float4 *)(ctx->ws + o_pix4);
+        pr.aop = (uint32_t *)(ctx->ws + o_aop);
+        pr.abf = (uint4 *)(ctx->ws + o_abf);
+        HIP_TRY(launch_prep(lc, pr, pa, coef));
+    } else {
         Timed t(ctx, "coef");
         HIP_TRY(launch_coef(lc, pa, coef));
     }

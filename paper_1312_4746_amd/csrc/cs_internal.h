@@ -449,9 +449,10 @@ struct PrepArgs {
     uint4 *abf;
     // set by launch_prep
     int64_t nslots, nthreads;
-    int b_stream, b_tiles;
+    int b_stream, b_tiles, b_coef;
 };
-hipError_t launch_prep(const LaunchCtx &lc, PrepArgs a);
+// ... and the coefficients (pa, tiled layout) to coef.
+hipError_t launch_prep(const LaunchCtx &lc, PrepArgs a, const ParzenArgs &pa, float4 *coef);
 hipError_t launch_parzen_mfma(const LaunchCtx &lc, const ParzenFastArgs &a);
 // Pixel records of the full-image path (nslots = padded tiles x kTilePix).
 // MFMA pixel operands of the full-image path (ntiles_pad tiles).

@@ -57,31 +57,11 @@ __global__ __launch_bounds__(64) void k_edt_col_summary(const uint8_t *seeds, in
     last[o] = la;
 }
 
-// Nearest seed row in the column for every pixel of the segment.
-__global__ __launch_bounds__(64) void k_edt_col_fill(const uint8_t *seeds, int H, int W, int nseg,
-                                                      const int32_t *first, const int32_t *last,
-                                                      int32_t *colrow) {
-    const int c = blockIdx.x * 64 + threadIdx.x;
-    const int seg = blockIdx.y, l = blockIdx.z;
-    if (c >= W) return;
+// Nearest seed row in the column for every pixel of a segment, given the last
+// seed row in the segments above it and the first in those below.
+__device__ __forceinline__ void fill_segment(const uint8_t *seeds, int H, int W, int c, int seg, int l, int above,
+                                             int below, int32_t *colrow) {
     const int64_t N = (int64_t)H * W;
-    const int64_t sbase = (int64_t)l * nseg * W + c;
-    int above = kNoSeed;  // last seed row in the segments above
-    for (int s0 = seg - 1; s0 >= 0 && above < 0; s0 -= kSegAhead) {
-        int v[kSegAhead];
-#pragma unroll
-        for (int i = 0; i < kSegAhead; ++i) v[i] = last[sbase + (int64_t)max(s0 - i, 0) * W];
-#pragma unroll
-        for (int i = kSegAhead - 1; i >= 0; --i) above = v[i] >= 0 ? v[i] : above;
-    }
-    int below = kNoSeed;  // first seed row in the segments below
-    for (int s0 = seg + 1; s0 < nseg && below < 0; s0 += kSegAhead) {
-        int v[kSegAhead];
-#pragma unroll
-        for (int i = 0; i < kSegAhead; ++i) v[i] = first[sbase + (int64_t)min(s0 + i, nseg - 1) * W];
-#pragma unroll
-        for (int i = kSegAhead - 1; i >= 0; --i) below = v[i] >= 0 ? v[i] : below;
-    }
     const uint8_t *sd = seeds + (int64_t)l * N + c;
     int32_t *cr = colrow + (int64_t)l * N + c;
     const int r0 = seg * kSegRows, r1 = min(H, r0 + kSegRows);
@@ -109,6 +89,67 @@ __global__ __launch_bounds__(64) void k_edt_col_fill(const uint8_t *seeds, int H
         if (nextr >= 0 && (a < 0 || nextr - r < r - a)) best = nextr;
         cr[(int64_t)r * W] = best;
     }
+}
+
+__global__ __launch_bounds__(64) void k_edt_col_fill(const uint8_t *seeds, int H, int W, int nseg,
+                                                      const int32_t *first, const int32_t *last,
+                                                      int32_t *colrow) {
+    const int c = blockIdx.x * 64 + threadIdx.x;
+    const int seg = blockIdx.y, l = blockIdx.z;
+    if (c >= W) return;
+    const int64_t sbase = (int64_t)l * nseg * W + c;
+    int above = kNoSeed;  // last seed row in the segments above
+    for (int s0 = seg - 1; s0 >= 0 && above < 0; s0 -= kSegAhead) {
+        int v[kSegAhead];
+#pragma unroll
+        for (int i = 0; i < kSegAhead; ++i) v[i] = last[sbase + (int64_t)max(s0 - i, 0) * W];
+#pragma unroll
+        for (int i = kSegAhead - 1; i >= 0; --i) above = v[i] >= 0 ? v[i] : above;
+    }
+    int below = kNoSeed;  // first seed row in the segments below
+    for (int s0 = seg + 1; s0 < nseg && below < 0; s0 += kSegAhead) {
+        int v[kSegAhead];
+#pragma unroll
+        for (int i = 0; i < kSegAhead; ++i) v[i] = first[sbase + (int64_t)min(s0 + i, nseg - 1) * W];
+#pragma unroll
+        for (int i = kSegAhead - 1; i >= 0; --i) below = v[i] >= 0 ? v[i] : below;
+    }
+    fill_segment(seeds, H, W, c, seg, l, above, below, colrow);
+}
+
+// Both steps in one launch for up to kColSegs segments: a workgroup has all
+// segments of kColWidth columns, a thread one of them, and hands the summaries
+// over in LDS (64 x 64: 7.9 -> 4.5 us, 481 x 321: 11.2 -> 9.6 us).
+constexpr int kColWidth = 32, kColSegs = 1024 / kColWidth;
+__global__ __launch_bounds__(1024) void k_edt_cols(const uint8_t *seeds, int H, int W, int nseg, int32_t *colrow) {
+    __shared__ int16_t s_first[kColSegs][kColWidth], s_last[kColSegs][kColWidth];
+    const int x = threadIdx.x % kColWidth, seg = threadIdx.x / kColWidth, l = blockIdx.y;
+    const int c = blockIdx.x * kColWidth + x;
+    const bool live = c < W;
+    const int r0 = seg * kSegRows, r1 = min(H, r0 + kSegRows);
+    int f = kNoSeed, la = kNoSeed;
+    if (live) {
+        const uint8_t *sd = seeds + (int64_t)l * H * W + c;
+        bool sv[kSegRows];
+#pragma unroll
+        for (int i = 0; i < kSegRows; ++i) sv[i] = sd[(int64_t)min(r0 + i, H - 1) * W] != 0;
+#pragma unroll
+        for (int i = 0; i < kSegRows; ++i)
+            if (r0 + i < r1 && sv[i]) {
+                if (f < 0) f = r0 + i;
+                la = r0 + i;
+            }
+    }
+    s_first[seg][x] = (int16_t)f;
+    s_last[seg][x] = (int16_t)la;
+    __syncthreads();
+    if (!live) return;
+    int above = kNoSeed, below = kNoSeed;
+    for (int s = 0; s < nseg; ++s) {
+        if (s < seg && s_last[s][x] >= 0) above = s_last[s][x];
+        if (s > seg && below < 0) below = s_first[s][x];
+    }
+    fill_segment(seeds, H, W, c, seg, l, above, below, colrow);
 }
 
 // Smallest (c - q)^2 + f(q) over the columns q = q0 + i of a block from g_i = f(q0
@@ -339,10 +380,14 @@ hipError_t launch_edt(const LaunchCtx &lc, const uint8_t *seeds, int H, int W, i
                       const int32_t *list, int64_t npix) {
     const int nseg = (H + kSegRows - 1) / kSegRows;
     int32_t *first = scratch, *last = scratch + (size_t)L * nseg * W;
-    dim3 g1((W + 63) / 64, nseg, L);
-    hipLaunchKernelGGL(k_edt_col_summary, g1, dim3(64), 0, lc.stream, seeds, H, W, nseg, first, last);
-    hipLaunchKernelGGL(k_edt_col_fill, g1, dim3(64), 0, lc.stream, seeds, H, W, nseg, first, last,
-                       colrow);
+    if (nseg <= kColSegs) {
+        hipLaunchKernelGGL(k_edt_cols, dim3((W + kColWidth - 1) / kColWidth, L), dim3(kColWidth * nseg), 0, lc.stream,
+                           seeds, H, W, nseg, colrow);
+    } else {
+        dim3 g1((W + 63) / 64, nseg, L);
+        hipLaunchKernelGGL(k_edt_col_summary, g1, dim3(64), 0, lc.stream, seeds, H, W, nseg, first, last);
+        hipLaunchKernelGGL(k_edt_col_fill, g1, dim3(64), 0, lc.stream, seeds, H, W, nseg, first, last, colrow);
+    }
     // a short list (at most an eighth of the pixels) takes the per-entry row
     // pass; longer ones the full pass, whose rows share their staging
     if (list && npix * 8 <= (int64_t)H * W) {

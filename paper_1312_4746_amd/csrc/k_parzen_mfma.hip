@@ -67,6 +67,7 @@
 #include <type_traits>
 
 #include "cs_internal.h"
+#include "parzen_coef.h"
 
 namespace cs {
 
@@ -354,10 +355,20 @@ __device__ __forceinline__ void pixel_operands(const float *rgb, const uint64_t 
 }
 
 // The per-call preparation of the full-image path in one launch: workgroups
-// [0, b_stream) build the sample stream, the next b_tiles the pixel records,
-// the rest the pixel operands (no dependence between the three).
-__global__ __launch_bounds__(256) void k_prep(PrepArgs a) {
+// [0, b_coef) compute the coefficients (parzen_coef.h; the longest, so they
+// start first), the next b_stream build the sample stream, the next b_tiles
+// the pixel records, the rest the pixel operands (no dependence between the
+// four; 481 x 321: 37 us in two launches, 34 us and one launch less here).
+template <int NW>
+__global__ __launch_bounds__(256) void k_prep(PrepArgs a, ParzenArgs pa, float4 *__restrict__ coef) {
     int b = blockIdx.x;
+    if (b < a.b_coef) {
+        const int per = a.b_tiles;  // workgroups per label
+        const int l = b / per;
+        coef_of<NW>(pa, coef, (int64_t)(b - l * per) * 256 + threadIdx.x, l);
+        return;
+    }
+    b -= a.b_coef;
     if (b < a.b_stream) {
         stream_build(a.recs, a.k, a.KP, a.L, a.segs, a.Mpad, a.cscale, a.levels, a.feat, a.rec, b);
         return;
@@ -373,13 +384,26 @@ __global__ __launch_bounds__(256) void k_prep(PrepArgs a) {
                    a.levels, a.aop, a.abf, b);
 }
 
-hipError_t launch_prep(const LaunchCtx &lc, PrepArgs a) {
+hipError_t launch_prep(const LaunchCtx &lc, PrepArgs a, const ParzenArgs &pa, float4 *coef) {
     a.nslots = a.ntiles_pad * kTilePix;
     a.nthreads = a.ntiles_pad * kParzenRB * 64;
     a.b_stream = (int)((a.Mpad + 255) / 256);
     a.b_tiles = (int)((a.nslots + 255) / 256);
-    const int64_t blocks = a.b_stream + a.b_tiles + (a.nthreads + 255) / 256;
-    hipLaunchKernelGGL(k_prep, dim3((unsigned)blocks), dim3(256), 0, lc.stream, a);
+    a.b_coef = a.b_tiles * a.L;
+    const int64_t blocks = (int64_t)a.b_coef + a.b_stream + a.b_tiles + (a.nthreads + 255) / 256;
+#define CS_PREP_LAUNCH(NW) \
+    hipLaunchKernelGGL(k_prep<NW>, dim3((unsigned)blocks), dim3(256), 0, lc.stream, a, pa, coef)
+    switch (pa.nw32) {
+        case 1: CS_PREP_LAUNCH(1); break;
+        case 2: CS_PREP_LAUNCH(2); break;
+        case 3: CS_PREP_LAUNCH(3); break;
+        case 4: CS_PREP_LAUNCH(4); break;
+        case 5: CS_PREP_LAUNCH(5); break;
+        case 6: CS_PREP_LAUNCH(6); break;
+        case 7: CS_PREP_LAUNCH(7); break;
+        default: CS_PREP_LAUNCH(8); break;
+    }
+#undef CS_PREP_LAUNCH
     return hipGetLastError();
 }
 

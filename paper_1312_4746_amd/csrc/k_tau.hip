@@ -469,9 +469,10 @@ __global__ __launch_bounds__(64) void k_tau_rank(const double *vals, int64_t cap
 // differ are common to all candidates and skipped; the remaining digits are
 // selected 8 bits at a time with an LDS histogram and a one-wave scan.
 constexpr int kSelLds = 4096;  // candidates kept in LDS for the last digits
+constexpr int kSelfRank = 256;  // candidates ranked by the selection itself
 __global__ __launch_bounds__(1024) void k_tau_select(const double *vals, int64_t cap, double frac,
                                                       TauState *st, const unsigned long long *parts,
-                                                      const unsigned long long *rk, double *tau_out) {
+                                                      const unsigned long long *rk, bool ranked, double *tau_out) {
     __shared__ unsigned int hist[256];
     __shared__ unsigned long long s_min, s_max, s_prefix, s_rank, s_below;
     // the candidates left after a digit, once few enough: the later digits
@@ -509,7 +510,28 @@ __global__ __launch_bounds__(1024) void k_tau_select(const double *vals, int64_t
         return;
     }
     const int64_t ncand = (int64_t)nc;
-    if (ncand <= kRankMax) {
+    if (ncand <= kSelfRank) {
+        // the few candidates of a short call, ranked here, one per thread
+        if (tid < (int)ncand) s_keys[tid] = (unsigned long long)__double_as_longlong(vals[tid]);
+        __syncthreads();
+        if (tid < (int)ncand) {
+            const unsigned long long key = s_keys[tid], r = r0 - below;
+            unsigned int less = 0, equal = 0;
+#pragma unroll 4
+            for (int q = 0; q < (int)ncand; ++q) {
+                less += s_keys[q] < key ? 1u : 0u;
+                equal += s_keys[q] == key ? 1u : 0u;
+            }
+            if (r >= less && r < (unsigned long long)less + equal) {
+                const double med = __longlong_as_double((long long)key);
+                st->median = med;
+                st->tau = frac * med;
+                if (tau_out) *tau_out = frac * med;
+            }
+        }
+        return;
+    }
+    if (ranked && ncand <= kRankMax) {
         // ranked by k_tau_rank: the candidate whose rank range [less, less +
         // equal) holds the target (equal keys give the same value)
         const unsigned long long r = r0 - below;
@@ -678,8 +700,12 @@ hipError_t tau_finish(const LaunchCtx &lc, const float *rgb, int H, int W, int p
     hipLaunchKernelGGL(k_tau_recompute, dim3((unsigned)blocks), dim3(64), 0, lc.stream, rgb, H, W, p, wmask, omega,
                        k, cand, st, cap, vals, pstats, ccnt, fl ? fl->coff : nullptr, fl ? fl->ccomp : nullptr);
     unsigned long long *rk = parts + kTauParts;  // kRankMax (less, equal) pairs
-    hipLaunchKernelGGL(k_tau_rank, dim3((unsigned)lc.num_cu * 4), dim3(64), 0, lc.stream, vals, cap, st, rk);
-    hipLaunchKernelGGL(k_tau_select, dim3(1), dim3(1024), 0, lc.stream, vals, cap, frac, st, parts, rk, tau_out);
+    // short calls, which have few candidates, go without the rank launch
+    const bool ranked = cap > ((int64_t)1 << 20);
+    if (ranked)
+        hipLaunchKernelGGL(k_tau_rank, dim3((unsigned)lc.num_cu * 4), dim3(64), 0, lc.stream, vals, cap, st, rk);
+    hipLaunchKernelGGL(k_tau_select, dim3(1), dim3(1024), 0, lc.stream, vals, cap, frac, st, parts, rk, ranked,
+                       tau_out);
     return hipGetLastError();
 }
 

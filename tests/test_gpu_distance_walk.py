@@ -23,7 +23,7 @@ def _case(H, W, M, seed):
     return w
 
 
-@pytest.mark.parametrize("H,W", [(40, 16), (33, 17), (9, 144), (7, 161), (5, 300), (4, 1501), (700, 24)])
+@pytest.mark.parametrize("H,W", [(40, 16), (33, 17), (9, 144), (7, 161), (5, 300), (4, 1501), (512, 20), (513, 20), (700, 24)])
 def test_far_samples(ctx, H, W):  # noqa: F811
     w = _case(H, W, 7, seed=H + W)
     masks, _, _ = oracle.full_masks(w)
