@@ -32,7 +32,7 @@ __device__ __forceinline__ double gray64(const float *rgb, int64_t N, int64_t id
 // kExactLanes lanes: the normalised Gaussian-masked gray patch rebuilt from
 // the image in the oracle's operation order, q_t = w_t g_t, s_t = (q_t - mu) /
 // sqrt(nu2) (0 when nu2 = 0), every sum sequential in t and no contraction.
-// The lanes load and divide in parallel (buf: the group's kExactRow doubles of
+// The lanes load and divide in parallel (buf: the group's n + 1 doubles of
 // LDS), lane 0's sums are the serial part; with one lane per entry the chain of
 // loads took 20 us however few the entries (1024 x 1024, 11 x 11, k = 242: the
 // median's recompute 102 -> 44 us, the masks' last entries 77 -> 31 us).  mu = sum_t q_t / n and nu2 = sum_t
@@ -40,7 +40,12 @@ __device__ __forceinline__ double gray64(const float *rgb, int64_t N, int64_t id
 // exact values, the same operations) when stats is non-null, else they are
 // computed here.  Every lane of the wave takes part (live: the group has an
 // entry); the group's lanes return the same value.
-constexpr int kExactLanes = 8, kExactRow = 15 * 15 + 1;
+constexpr int kExactLanes = 8;
+// LDS of a wave's groups, n + 1 doubles each (an odd stride of banks), and waves
+// per compute unit: sixteen fit up to 11 x 11 patches (with eight, 31000 entries of
+// 121 went in two rounds: 44 us against 35)
+inline size_t exact_lds(int n) { return sizeof(double) * (64 / kExactLanes) * (size_t)(n + 1); }
+constexpr int kExactWaves = 16;
 __device__ __forceinline__ double exact_entry(const float *rgb, int H, int W, int p, const double *wmask,
                                               const float *om, int64_t pix, const double *stats, double *buf,
                                               bool live) {

@@ -545,7 +545,7 @@ int tau_stage(cs_ctx *ctx, const float *rgb, int H, int W, int p, const float *o
     {
         Timed t(ctx, "tau_exact");
         HIP_TRY(tau_finish(lc, rgb, H, W, p, n, ctx->wmask, omega, k, cand, cap, vals, frac, st, parts, tau_out,
-                           pstats));
+                           pstats, nullptr, nullptr, nullptr, mmax));
     }
     return CS_OK;
 }
@@ -827,7 +827,7 @@ int cs_cosupport_median(cs_ctx *ctx, const float *rgb, int H, int W, int p, doub
         {
             Timed t(ctx, "tau_exact");
             HIP_TRY(tau_finish(lc, rgb, H, W, p, n, ctx->wmask, omega, k, cand, count, vals, frac, st, parts,
-                               tau_dev, pst, ccnt, &fl));
+                               tau_dev, pst, ccnt, &fl, hist3 + 2 * kHistBins, mmax));
         }
         {
             Timed t(ctx, "cosupport_fix");

@@ -487,7 +487,7 @@ __global__ __launch_bounds__(64) void k_median_mask_finish(const float *alpha, c
                                                            const TauState *st, uint64_t *masks,
                                                            const double *pstats) {
     constexpr int G = 64 / kExactLanes;
-    __shared__ double s_buf[G][kExactRow];
+    extern __shared__ double s_exact[];  // exact_lds(p * p)
     __shared__ int64_t s_near[64];
     const int lane = threadIdx.x, grp = lane / kExactLanes, W64 = (k + 63) / 64;
     const double tau = st->tau;
@@ -528,7 +528,8 @@ __global__ __launch_bounds__(64) void k_median_mask_finish(const float *alpha, c
             const bool on = i0 + grp < nn;
             const int64_t f = s_near[on ? i0 + grp : 0], pix = f / k;
             const int j = (int)(f - pix * k);
-            const double v = exact_entry(rgb, H, W, p, wmask, omega + (int64_t)j * p * p, pix, pstats, s_buf[grp], on);
+            const double v = exact_entry(rgb, H, W, p, wmask, omega + (int64_t)j * p * p, pix, pstats,
+                                         s_exact + grp * (p * p + 1), on);
             if (on && (lane & (kExactLanes - 1)) == 0 && fabs(v) <= tau) set(pix, j);
         }
         __builtin_amdgcn_wave_barrier();
@@ -623,8 +624,8 @@ hipError_t median_mask_finish(const LaunchCtx &lc, const float *alpha, const flo
                               const double *wmask, const float *omega, int k, const int64_t *didx,
                               const unsigned int *dcnt, const int64_t *dcomp, const double *margins,
                               const TauState *st, uint64_t *masks, const double *pstats) {
-    const int64_t blocks = (int64_t)lc.num_cu * 8;
-    hipLaunchKernelGGL(k_median_mask_finish, dim3((unsigned)blocks), dim3(64), 0, lc.stream, alpha, rgb, H, W, p,
+    const int64_t blocks = (int64_t)lc.num_cu * kExactWaves;
+    hipLaunchKernelGGL(k_median_mask_finish, dim3((unsigned)blocks), dim3(64), exact_lds(p * p), lc.stream, alpha, rgb, H, W, p,
                        wmask, omega, k, didx, dcnt, dcomp, margins, st, masks, pstats);
     return hipGetLastError();
 }
