@@ -662,7 +662,7 @@ def main():
                 "counters": counters}
     avg_an = analyze_ms / 1e3 / max(analyze_n, 1)
     gemm_flops = 2.0 * w.k * w.n * w.N
-    an_prof = counter_profile("k_analyze", w.name)
+    an_prof = counter_profile("k_patch", w.name)
     extra = {
         "analyze_mfma": {"avg_launch_ms": avg_an * 1e3, "achieved_tflops": gemm_flops / avg_an / 1e12,
                          "peak_tflops": PEAK_MFMA[w.precision] / 1e12,
