@@ -57,13 +57,28 @@ __global__ __launch_bounds__(64) void k_edt_col_summary(const uint8_t *seeds, in
     last[o] = la;
 }
 
+// Smallest value of each aligned group of 16 lanes (rotations within it).
+__device__ __forceinline__ int min16(int v) {
+    v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x128, 0xF, 0xF, false));
+    v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x124, 0xF, 0xF, false));
+    v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x122, 0xF, 0xF, false));
+    return min(v, __builtin_amdgcn_update_dpp(v, v, 0x121, 0xF, 0xF, false));
+}
+
 // Nearest seed row in the column for every pixel of a segment, given the last
-// seed row in the segments above it and the first in those below.
+// seed row in the segments above it and the first in those below; MIN: also
+// the smallest f over each block of kRowBlk columns, which an aligned group of as
+// many lanes holds (every lane of the wave takes part, live: it has a column; a
+// pass of its own over the rows took 80 us at 2048 x 2048, 10 labels, 26 more here).
+template <bool MIN>
 __device__ __forceinline__ void fill_segment(const uint8_t *seeds, int H, int W, int c, int seg, int l, int above,
-                                             int below, int32_t *colrow) {
+                                             int below, int32_t *colrow, int32_t *bmin, bool live) {
+    static_assert(kRowBlk == 16, "a block is a group of 16 lanes");
     const int64_t N = (int64_t)H * W;
-    const uint8_t *sd = seeds + (int64_t)l * N + c;
-    int32_t *cr = colrow + (int64_t)l * N + c;
+    const int cc = live ? c : W - 1;
+    const uint8_t *sd = seeds + (int64_t)l * N + cc;
+    int32_t *cr = colrow + (int64_t)l * N + cc;
+    const int nb = (W + kRowBlk - 1) / kRowBlk;
     const int r0 = seg * kSegRows, r1 = min(H, r0 + kSegRows);
     // the segment's seed bytes, loaded unconditionally (rows clamped) so that
     // the loads are in flight together
@@ -82,22 +97,26 @@ __device__ __forceinline__ void fill_segment(const uint8_t *seeds, int H, int W,
 #pragma unroll
     for (int i = kSegRows - 1; i >= 0; --i) {
         const int r = r0 + i;
-        if (r >= r1) continue;
-        if (sv[i]) nextr = r;
+        if (r < r1 && sv[i]) nextr = r;
         const int a = up[i];
         int best = a;
         if (nextr >= 0 && (a < 0 || nextr - r < r - a)) best = nextr;
-        cr[(int64_t)r * W] = best;
+        if (live && r < r1) cr[(int64_t)r * W] = best;
+        if constexpr (MIN) {
+            const int m = min16(live && best >= 0 ? (r - best) * (r - best) : kInf);
+            if (live && r < r1 && c % kRowBlk == 0) bmin[((int64_t)l * H + r) * nb + c / kRowBlk] = m;
+        }
     }
 }
 
+template <bool MIN>
 __global__ __launch_bounds__(64) void k_edt_col_fill(const uint8_t *seeds, int H, int W, int nseg,
                                                       const int32_t *first, const int32_t *last,
-                                                      int32_t *colrow) {
+                                                      int32_t *colrow, int32_t *bmin) {
     const int c = blockIdx.x * 64 + threadIdx.x;
     const int seg = blockIdx.y, l = blockIdx.z;
-    if (c >= W) return;
-    const int64_t sbase = (int64_t)l * nseg * W + c;
+    if (!MIN && c >= W) return;
+    const int64_t sbase = (int64_t)l * nseg * W + min(c, W - 1);
     int above = kNoSeed;  // last seed row in the segments above
     for (int s0 = seg - 1; s0 >= 0 && above < 0; s0 -= kSegAhead) {
         int v[kSegAhead];
@@ -114,14 +133,16 @@ __global__ __launch_bounds__(64) void k_edt_col_fill(const uint8_t *seeds, int H
 #pragma unroll
         for (int i = kSegAhead - 1; i >= 0; --i) below = v[i] >= 0 ? v[i] : below;
     }
-    fill_segment(seeds, H, W, c, seg, l, above, below, colrow);
+    fill_segment<MIN>(seeds, H, W, c, seg, l, above, below, colrow, bmin, c < W);
 }
 
 // Both steps in one launch for up to kColSegs segments: a workgroup has all
 // segments of kColWidth columns, a thread one of them, and hands the summaries
 // over in LDS (64 x 64: 7.9 -> 4.5 us, 481 x 321: 11.2 -> 9.6 us).
 constexpr int kColWidth = 32, kColSegs = 1024 / kColWidth;
-__global__ __launch_bounds__(1024) void k_edt_cols(const uint8_t *seeds, int H, int W, int nseg, int32_t *colrow) {
+template <bool MIN>
+__global__ __launch_bounds__(1024) void k_edt_cols(const uint8_t *seeds, int H, int W, int nseg, int32_t *colrow,
+                                                   int32_t *bmin) {
     __shared__ int16_t s_first[kColSegs][kColWidth], s_last[kColSegs][kColWidth];
     const int x = threadIdx.x % kColWidth, seg = threadIdx.x / kColWidth, l = blockIdx.y;
     const int c = blockIdx.x * kColWidth + x;
@@ -143,13 +164,13 @@ __global__ __launch_bounds__(1024) void k_edt_cols(const uint8_t *seeds, int H, 
     s_first[seg][x] = (int16_t)f;
     s_last[seg][x] = (int16_t)la;
     __syncthreads();
-    if (!live) return;
+    if (!MIN && !live) return;
     int above = kNoSeed, below = kNoSeed;
     for (int s = 0; s < nseg; ++s) {
         if (s < seg && s_last[s][x] >= 0) above = s_last[s][x];
         if (s > seg && below < 0) below = s_first[s][x];
     }
-    fill_segment(seeds, H, W, c, seg, l, above, below, colrow);
+    fill_segment<MIN>(seeds, H, W, c, seg, l, above, below, colrow, bmin, live);
 }
 
 // Smallest (c - q)^2 + f(q) over the columns q = q0 + i of a block from g_i = f(q0
@@ -253,29 +274,6 @@ __global__ __launch_bounds__(1024) void k_edt_rows(const int32_t *colrow, int H,
     }
 }
 
-// Smallest f over each block of kRowBlk columns of every row and label (the
-// block minima of k_edt_rows, for the listed form below): one thread per
-// (row, block, label).
-__global__ __launch_bounds__(256) void k_edt_block_min(const int32_t *colrow, int H, int W, int32_t *bmin) {
-    const int nb = (W + kRowBlk - 1) / kRowBlk;
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int l = blockIdx.y;
-    if (i >= (int64_t)H * nb) return;
-    const int r = (int)(i / nb), b = (int)(i - (int64_t)r * nb);
-    const int32_t *cr = colrow + (int64_t)l * H * W + (int64_t)r * W;
-    int fv[kRowBlk];
-#pragma unroll
-    for (int u = 0; u < kRowBlk; ++u) {
-        const int q = b * kRowBlk + u;
-        const int s = q < W ? cr[q] : -1;
-        fv[u] = s < 0 ? kInf : (r - s) * (r - s);
-    }
-    int m = kInf;
-#pragma unroll
-    for (int u = 0; u < kRowBlk; ++u) m = min(m, fv[u]);
-    bmin[(int64_t)l * H * nb + i] = m;
-}
-
 // The row pass for listed pixels only, one thread per (entry, label): the
 // walk of k_edt_rows for the entry's column, reading f and the block minima
 // from global memory instead of LDS (the same blocks are scanned in the same
@@ -366,13 +364,12 @@ __global__ __launch_bounds__(256) void k_edt_rows_list(const int32_t *colrow, co
     }
 }
 
-// Scratch: first/last summaries, 2 * L * ceil(H/16) * W int32, then (listed
+// Scratch: first/last summaries, 2 * L * ceil(H/16) * W int32, and (listed
 // form) the block minima, L * H * ceil(W/16) int32.
 size_t edt_scratch_bytes(int H, int W, int L) {
     const int nseg = (H + kSegRows - 1) / kSegRows;
     const size_t nb = (size_t)(W + kRowBlk - 1) / kRowBlk;
-    const size_t summaries = 2 * (size_t)L * nseg * W, minima = (size_t)L * H * nb;
-    return sizeof(int32_t) * (summaries > minima ? summaries : minima);
+    return sizeof(int32_t) * (2 * (size_t)L * nseg * W + (size_t)L * H * nb);
 }
 
 hipError_t launch_edt(const LaunchCtx &lc, const uint8_t *seeds, int H, int W, int L,
@@ -380,24 +377,28 @@ hipError_t launch_edt(const LaunchCtx &lc, const uint8_t *seeds, int H, int W, i
                       const int32_t *list, int64_t npix) {
     const int nseg = (H + kSegRows - 1) / kSegRows;
     int32_t *first = scratch, *last = scratch + (size_t)L * nseg * W;
-    if (nseg <= kColSegs) {
-        hipLaunchKernelGGL(k_edt_cols, dim3((W + kColWidth - 1) / kColWidth, L), dim3(kColWidth * nseg), 0, lc.stream,
-                           seeds, H, W, nseg, colrow);
-    } else {
-        dim3 g1((W + 63) / 64, nseg, L);
-        hipLaunchKernelGGL(k_edt_col_summary, g1, dim3(64), 0, lc.stream, seeds, H, W, nseg, first, last);
-        hipLaunchKernelGGL(k_edt_col_fill, g1, dim3(64), 0, lc.stream, seeds, H, W, nseg, first, last, colrow);
-    }
     // a short list (at most an eighth of the pixels) takes the per-entry row
     // pass; longer ones the full pass, whose rows share their staging
-    if (list && npix * 8 <= (int64_t)H * W) {
+    const bool listed = list && npix * 8 <= (int64_t)H * W;
+    int32_t *bmin = listed ? scratch + 2 * (size_t)L * nseg * W : nullptr;
+    if (nseg <= kColSegs) {
+        const dim3 grid((W + kColWidth - 1) / kColWidth, L), block(kColWidth * nseg);
+        if (listed)
+            hipLaunchKernelGGL(k_edt_cols<true>, grid, block, 0, lc.stream, seeds, H, W, nseg, colrow, bmin);
+        else
+            hipLaunchKernelGGL(k_edt_cols<false>, grid, block, 0, lc.stream, seeds, H, W, nseg, colrow, bmin);
+    } else {
+        const dim3 grid((W + 63) / 64, nseg, L);
+        hipLaunchKernelGGL(k_edt_col_summary, grid, dim3(64), 0, lc.stream, seeds, H, W, nseg, first, last);
+        if (listed)
+            hipLaunchKernelGGL(k_edt_col_fill<true>, grid, dim3(64), 0, lc.stream, seeds, H, W, nseg, first, last, colrow, bmin);
+        else
+            hipLaunchKernelGGL(k_edt_col_fill<false>, grid, dim3(64), 0, lc.stream, seeds, H, W, nseg, first, last, colrow, bmin);
+    }
+    if (listed) {
         if (npix == 0) return hipGetLastError();
-        // block minima into the scratch (the column summaries are dead by now)
-        const int64_t nbr = (int64_t)H * ((W + kRowBlk - 1) / kRowBlk);
-        hipLaunchKernelGGL(k_edt_block_min, dim3((unsigned)((nbr + 255) / 256), L), dim3(256), 0, lc.stream,
-                           colrow, H, W, scratch);
         hipLaunchKernelGGL(k_edt_rows_list, dim3((unsigned)((npix + 255) / 256), L), dim3(256), 0, lc.stream,
-                           colrow, scratch, H, W, list, npix, d2, nearest);
+                           colrow, bmin, H, W, list, npix, d2, nearest);
         return hipGetLastError();
     }
     const size_t nbk = (size_t)(W + kRowBlk - 1) / kRowBlk;
