@@ -451,7 +451,7 @@ struct PrepArgs {
     uint4 *abf;
     // set by launch_prep
     int64_t nslots, nthreads;
-    int b_stream, b_tiles, b_coef;
+    int b_stream, b_tiles, b_coef, coef_labels;
 };
 // ... and the coefficients (pa, tiled layout) to coef.
 hipError_t launch_prep(const LaunchCtx &lc, PrepArgs a, const ParzenArgs &pa, float4 *coef);

@@ -29,7 +29,7 @@ namespace cs {
 
 template <int NW>
 __global__ __launch_bounds__(256) void k_coef(ParzenArgs a, float4 *__restrict__ coef) {
-    coef_of<NW>(a, coef, (int64_t)blockIdx.x * 256 + threadIdx.x, blockIdx.y);
+    coef_of<NW>(a, coef, (int64_t)blockIdx.x * 256 + threadIdx.x, blockIdx.y, blockIdx.y + 1);
 }
 
 // The sample records and the outputs are separate restrict-qualified

@@ -358,14 +358,14 @@ __device__ __forceinline__ void pixel_operands(const float *rgb, const uint64_t 
 // [0, b_coef) compute the coefficients (parzen_coef.h; the longest, so they
 // start first), the next b_stream build the sample stream, the next b_tiles
 // the pixel records, the rest the pixel operands (no dependence between the
-// four; 481 x 321: 37 us in two launches, 34 us and one launch less here).
+// four; 481 x 321: 37 us in two launches, 30 us in this one).
 template <int NW>
 __global__ __launch_bounds__(256) void k_prep(PrepArgs a, ParzenArgs pa, float4 *__restrict__ coef) {
     int b = blockIdx.x;
     if (b < a.b_coef) {
-        const int per = a.b_tiles;  // workgroups per label
-        const int l = b / per;
-        coef_of<NW>(pa, coef, (int64_t)(b - l * per) * 256 + threadIdx.x, l);
+        const int per = a.b_tiles;  // workgroups per coef_labels labels
+        const int lg = b / per, l0 = lg * a.coef_labels;
+        coef_of<NW>(pa, coef, (int64_t)(b - lg * per) * 256 + threadIdx.x, l0, min(l0 + a.coef_labels, a.L));
         return;
     }
     b -= a.b_coef;
@@ -389,7 +389,11 @@ hipError_t launch_prep(const LaunchCtx &lc, PrepArgs a, const ParzenArgs &pa, fl
     a.nthreads = a.ntiles_pad * kParzenRB * 64;
     a.b_stream = (int)((a.Mpad + 255) / 256);
     a.b_tiles = (int)((a.nslots + 255) / 256);
-    a.b_coef = a.b_tiles * a.L;
+    // a thread takes four labels of its pixel, read once, where that still fills
+    // the chip (four workgroups per compute unit: 481 x 321, 10 labels 36 -> 30 us,
+    // 1024 x 1024, 16 labels 370 -> 337 us), else one (64 x 64: 6.4 us against 11.3)
+    a.coef_labels = (int64_t)a.b_tiles * ((a.L + 3) / 4) >= 4 * lc.num_cu ? 4 : 1;
+    a.b_coef = a.b_tiles * ((a.L + a.coef_labels - 1) / a.coef_labels);
     const int64_t blocks = (int64_t)a.b_coef + a.b_stream + a.b_tiles + (a.nthreads + 255) / 256;
 #define CS_PREP_LAUNCH(NW) \
     hipLaunchKernelGGL(k_prep<NW>, dim3((unsigned)blocks), dim3(256), 0, lc.stream, a, pa, coef)

@@ -45,7 +45,7 @@ __device__ __forceinline__ float pair_e(float px, float py, float pr, float pg, 
 // fast_slot_row (the tile grid, or entry i of the subset); empty slots get
 // {0, 0, -200, 0} (their terms vanish).
 template <int NW>
-__device__ __forceinline__ void coef_of(const ParzenArgs &a, float4 *__restrict__ coef, int64_t i, int l) {
+__device__ __forceinline__ void coef_of(const ParzenArgs &a, float4 *__restrict__ coef, int64_t i, int l0, int l1) {
     const int64_t nslots = a.coef_tiled ? (int64_t)a.ntiles_pad * kTilePix : a.npix;
     if (i >= nslots) return;
     const int64_t N = (int64_t)a.H * a.W;
@@ -55,7 +55,7 @@ __device__ __forceinline__ void coef_of(const ParzenArgs &a, float4 *__restrict_
         const int t = (int)(i / kTilePix), q = (int)(i - (int64_t)t * kTilePix);
         const int64_t row = fast_slot_row(a.subset, a.npix, a.H, a.W, a.tiles_x, a.ntiles_real, t, q);
         if (row < 0) {
-            coef[(int64_t)l * nslots + i] = make_float4(0.0f, 0.0f, -200.0f, 0.0f);
+            for (int l = l0; l < l1; ++l) coef[(int64_t)l * nslots + i] = make_float4(0.0f, 0.0f, -200.0f, 0.0f);
             return;
         }
         pix = fast_row_pixel(a.subset, row);
@@ -64,43 +64,46 @@ __device__ __forceinline__ void coef_of(const ParzenArgs &a, float4 *__restrict_
     }
     const uint32_t *mask32 = reinterpret_cast<const uint32_t *>(a.masks);
     const float nC = (float)(-kLog2e / (2.0 * a.sigma_c * a.sigma_c));
-    const int d2min = a.d2[(int64_t)l * N + pix];
-    const int64_t nearp = a.nearest[(int64_t)l * N + pix];
-    // FP32 from here (the results are FP32; a few ulps against one rounding)
-    const float fl2 = (float)(a.rho_floor * a.rho_floor);
-    const float dm = fmaxf((float)d2min, fl2);
-    const float rho2 = (float)(a.alpha_rho * a.alpha_rho) * dm;
-    const float rho = sqrtf(rho2);
-    const float nA = -(float)kLog2e / (2.0f * rho2);
-    const float nB = a.texture_in_sum ? -(float)kLog2e / ((float)a.beta_scale * rho) : 0.0f;
-    const float K = (float)a.kconst[l] - logf(rho2);
-    uint32_t mx[NW], nrec[kRecWords];
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        mx[w] = mask32[pix * 2 * W64 + w];
-        nrec[8 + w] = mask32[nearp * 2 * W64 + w];
-    }
-    // (32-bit divisions: an image has fewer than 2^31 pixels)
-    const uint32_t w32 = (uint32_t)a.W, ny = (uint32_t)nearp / w32, y = (uint32_t)pix / w32;
-    nrec[0] = __float_as_uint((float)((uint32_t)nearp - ny * w32));
-    nrec[1] = __float_as_uint((float)ny);
-    nrec[2] = __float_as_uint(a.rgb[nearp]);
-    nrec[3] = __float_as_uint(a.rgb[N + nearp]);
-    nrec[4] = __float_as_uint(a.rgb[2 * N + nearp]);
+    const uint32_t w32 = (uint32_t)a.W, y = (uint32_t)pix / w32;  // (32-bit divisions: an image has fewer than 2^31 pixels)
     const float px = (float)((uint32_t)pix - y * w32), py = (float)y;
     const float pr = a.rgb[pix], pg = a.rgb[N + pix], pb = a.rgb[2 * N + pix];
-    float est = pair_e<NW>(px, py, pr, pg, pb, mx, nrec, nA, nB, nC);
-    // Largest exponent over the nearest sample and an evenly strided subset of
-    // the label's samples: an achieved value close to the maximum.
-    const int s0 = a.seg_off[l], m = a.seg_off[l + 1] - s0;
-    const int nsub = m < kRefSubset ? m : kRefSubset;
-    const uint32_t *recw = reinterpret_cast<const uint32_t *>(a.recs);
-    for (int j = 0; j < nsub; ++j) {
-        const int64_t sidx = s0 + (int64_t)j * m / nsub;
-        est = fmaxf(est, pair_e<NW>(px, py, pr, pg, pb, mx, recw + sidx * kRecWords, nA, nB, nC));
+    uint32_t mx[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) mx[w] = mask32[pix * 2 * W64 + w];
+#pragma unroll 1
+    for (int l = l0; l < l1; ++l) {
+        const int d2min = a.d2[(int64_t)l * N + pix];
+        const int64_t nearp = a.nearest[(int64_t)l * N + pix];
+        // FP32 from here (the results are FP32; a few ulps against one rounding)
+        const float fl2 = (float)(a.rho_floor * a.rho_floor);
+        const float dm = fmaxf((float)d2min, fl2);
+        const float rho2 = (float)(a.alpha_rho * a.alpha_rho) * dm;
+        const float rho = sqrtf(rho2);
+        const float nA = -(float)kLog2e / (2.0f * rho2);
+        const float nB = a.texture_in_sum ? -(float)kLog2e / ((float)a.beta_scale * rho) : 0.0f;
+        const float K = (float)a.kconst[l] - logf(rho2);
+        uint32_t nrec[kRecWords];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) nrec[8 + w] = mask32[nearp * 2 * W64 + w];
+        const uint32_t ny = (uint32_t)nearp / w32;
+        nrec[0] = __float_as_uint((float)((uint32_t)nearp - ny * w32));
+        nrec[1] = __float_as_uint((float)ny);
+        nrec[2] = __float_as_uint(a.rgb[nearp]);
+        nrec[3] = __float_as_uint(a.rgb[N + nearp]);
+        nrec[4] = __float_as_uint(a.rgb[2 * N + nearp]);
+        float est = pair_e<NW>(px, py, pr, pg, pb, mx, nrec, nA, nB, nC);
+        // Largest exponent over the nearest sample and an evenly strided subset of
+        // the label's samples: an achieved value close to the maximum.
+        const int s0 = a.seg_off[l], m = a.seg_off[l + 1] - s0;
+        const int nsub = m < kRefSubset ? m : kRefSubset;
+        const uint32_t *recw = reinterpret_cast<const uint32_t *>(a.recs);
+        for (int j = 0; j < nsub; ++j) {
+            const int64_t sidx = s0 + (int64_t)j * m / nsub;
+            est = fmaxf(est, pair_e<NW>(px, py, pr, pg, pb, mx, recw + sidx * kRecWords, nA, nB, nC));
+        }
+        const float U = nA * (float)d2min;
+        coef[(int64_t)l * nslots + i] = make_float4(nA, nB, -fminf(U, est + kRefMargin), K);
     }
-    const float U = nA * (float)d2min;
-    coef[(int64_t)l * nslots + i] = make_float4(nA, nB, -fminf(U, est + kRefMargin), K);
 }
 
 }  // namespace cs
