@@ -27,8 +27,10 @@
 // 2. mean and squared norm of every masked patch q_t = w_t g_t from column
 //    sums (the Gaussian mask is a product of its row and its column factor):
 //    nu2 = sum q^2 - n mu^2 in FP64.  Where that cancels (nu2 <= 1e-6 sum q^2,
-//    a flat patch under a wide mask; a constant patch has nu2 = 0 exactly) the
-//    sums run entry by entry in the order of the definition;
+//    a flat patch under a wide mask; a constant patch has nu2 = 0 exactly), and
+//    where sum q^2 is so small that its terms may have lost bits below the
+//    normal range (a narrow mask over black pixels), the sums run entry by
+//    entry in the order of the definition;
 // 3. s_t = (q_t - mu) (1 / nu) in FP64, rounded once to FP32, into LDS as four
 //    runs of KF entries per pixel: lane group g of an MFMA operand takes run
 //    g, so its A values are 16-byte aligned pieces of one row;
@@ -393,7 +395,8 @@ void k_patch(AnalyzeArgs a, int tiles_x, int ntiles) {
                 q += w * w * s_c2[tid + v];
             }
             double mu = m / (double)n, nu2 = q - m * mu;
-            if (tid < valid_px && !(nu2 > 1e-6 * q)) {
+            // (a term below the normal range is off by 2^-1074, nothing to a q above 2^-900)
+            if (tid < valid_px && !(nu2 > 1e-6 * q && q > 0x1p-900)) {
                 double sum = 0.0;
                 for (int t = 0; t < n; ++t) sum = sum + a.wmask[t] * gh[(t / P) * hw + tid + t % P];
                 mu = sum / (double)n;
