@@ -155,8 +155,9 @@ __global__ __launch_bounds__(1024) void k_select_setup(AnalyzeArgs a) {
 }
 
 // The bracket: the bins of the sample's ranks 0.5 -+ 1/128, widened by three
-// margins.
-__global__ __launch_bounds__(1024) void k_bracket_pick(const unsigned int *hist, const double *max_margin,
+// margins.  None where a row's undecided interval would reach past FP32 (a huge
+// frac), whose end the passes over the entries give to places without an entry.
+__global__ __launch_bounds__(1024) void k_bracket_pick(const unsigned int *hist, const double *max_margin, double frac,
                                                        TauState *st) {
     constexpr int per = kBracketBins / 1024;
     __shared__ unsigned int s_w[16], s_bin[2];
@@ -195,7 +196,10 @@ __global__ __launch_bounds__(1024) void k_bracket_pick(const unsigned int *hist,
         const double lo = (double)__uint_as_float((b0 + kBinBase) << 15) - m3;
         const double hi = (double)__uint_as_float((b1 + 1 + kBinBase) << 15) + m3;
         const uint32_t blo = __float_as_uint((float)lo), bhi = __float_as_uint((float)hi);
-        const bool ok = b0 > 0 && b1 < kBracketBins - 1 && lo > 0.0 && hi < 4.0 && bhi - blo < kPackMax;
+        double tlo, thi;
+        tau_interval((double)(float)lo, (double)(float)hi, *max_margin, frac, tlo, thi);
+        const bool ok = b0 > 0 && b1 < kBracketBins - 1 && lo > 0.0 && hi < 4.0 && bhi - blo < kPackMax &&
+                        thi + *max_margin < (double)__FLT_MAX__;
         st->br_valid = ok ? 1 : 0;
         if (ok) {
             int shift = 0;
@@ -408,6 +412,7 @@ __global__ __launch_bounds__(256) void k_median_mask_gather(const float *alpha, 
     };
     const bool row_live = 64 * (W64 - 1) + lane < k;
     const uint32_t key_and = row_live ? 0x7FFFFFFFu : 0u, key_or = row_live ? 0u : 0x7F800000u;
+    const uint64_t rows = __ballot(row_live);  // of the last word
     // the keys of a round, loaded unconditionally (clamped indices: the loads
     // are in flight together; padding is replaced when the entry is used)
     auto load = [&](int64_t rd, uint32_t (&kk)[kPx][W64]) {
@@ -436,20 +441,22 @@ __global__ __launch_bounds__(256) void k_median_mask_gather(const float *alpha, 
             if (p0 + i >= N) break;
 #pragma unroll
             for (int w = 0; w < W64; ++w) {
-                // rows past k get the key of +inf, which every test below
-                // rejects (not below, no candidate, not in, not deferred)
+                // rows past k get the key of +inf: not below, and out of every
+                // interval within FP32, as a bracket's are (k_bracket_pick);
+                // an interval that reaches past FP32 would take the key
+                const uint64_t live = BR || w < W64 - 1 ? ~0ull : rows;
                 const uint32_t x = w < W64 - 1 ? key[i][w] & 0x7FFFFFFFu : (key[i][w] & key_and) | key_or, d = x - blo;
                 below += (unsigned int)__popcll(__builtin_amdgcn_uicmp(x, blo, kUlt));
-                const unsigned long long cm = __builtin_amdgcn_uicmp(d, bhi - blo, kUle);
+                const unsigned long long cm = __builtin_amdgcn_uicmp(d, bhi - blo, kUle) & live;
                 if (cm) {
                     if (__builtin_amdgcn_inverse_ballot_w64(cm)) put(creg, nc_w + lane_prefix(cm), (p0 + i) * k + 64 * w, BR ? d : 0u);
                     nc_w += (unsigned int)__popcll(cm);
                 }
                 const float f = __uint_as_float(x);
-                const uint64_t inb = __builtin_amdgcn_fcmpf(f, tin[w], kOle);
+                const uint64_t inb = __builtin_amdgcn_fcmpf(f, tin[w], kOle) & live;
                 out_lo = write_lane((int)(uint32_t)inb, i * W64 + w, out_lo);
                 out_hi = write_lane((int)(uint32_t)(inb >> 32), i * W64 + w, out_hi);
-                const unsigned long long dm = ~(inb | __builtin_amdgcn_fcmpf(f, tout[w], kOgt));  // NaN: deferred
+                const unsigned long long dm = live & ~(inb | __builtin_amdgcn_fcmpf(f, tout[w], kOgt));  // NaN: deferred
                 if (dm) {
                     if (__builtin_amdgcn_inverse_ballot_w64(dm)) put(dreg, nd_w + lane_prefix(dm), (p0 + i) * k + 64 * w, BR ? min(x - dbase, kPackMax) : 0u);
                     nd_w += (unsigned int)__popcll(dm);
@@ -576,7 +583,7 @@ hipError_t median_bracket(const LaunchCtx &lc, const float *alpha, int64_t N, in
                           uint64_t *masks, unsigned int *br_hist) {
     const int blocks = (int)(median_gather_waves(N) / 4);
     hipLaunchKernelGGL(k_bracket_sample, dim3(kSampleBlocks), dim3(1024), 0, lc.stream, alpha, N * k, br_hist);
-    hipLaunchKernelGGL(k_bracket_pick, dim3(1), dim3(1024), 0, lc.stream, br_hist, max_margin, st);
+    hipLaunchKernelGGL(k_bracket_pick, dim3(1), dim3(1024), 0, lc.stream, br_hist, max_margin, frac, st);
 #define CS_BR_LAUNCH(WW)                                                                                           \
     hipLaunchKernelGGL((k_median_mask_gather<WW, true>), dim3((unsigned)blocks), dim3(256), 0, lc.stream, alpha, N, k, \
                        max_margin, margins, frac, st, (int64_t *)blist, ccnt, parts, didx, dcnt, masks, nullptr)
@@ -604,7 +611,8 @@ hipError_t median_bracket_analyze(const LaunchCtx &lc, const AnalyzeArgs &a, int
                                   int64_t *cand) {
     hipLaunchKernelGGL(k_select_setup, dim3(1), dim3(1024), 0, lc.stream, a);
     hipLaunchKernelGGL(k_patch_sample, dim3(kPatchSampleBlocks + 1), dim3(1024), 0, lc.stream, a, br_hist);
-    hipLaunchKernelGGL(k_bracket_pick, dim3(1), dim3(1024), 0, lc.stream, br_hist, a.tau_max_margin, a.tau_st);
+    hipLaunchKernelGGL(k_bracket_pick, dim3(1), dim3(1024), 0, lc.stream, br_hist, a.tau_max_margin,
+                       a.sel_frac, a.tau_st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     AnalyzeArgs b = a;

@@ -510,7 +510,8 @@ void k_patch(AnalyzeArgs a, int tiles_x, int ntiles) {
                                 *out = tot[u][r];
                         }
                         // rows past k and pixels past the row end get the key of
-                        // +inf, which every test rejects
+                        // +inf, which every test rejects (a bracket's intervals
+                        // lie within FP32)
                         const float f = __builtin_amdgcn_inverse_ballot_w64(live) ? fabsf(tot[u][r]) : INFINITY;
                         const uint32_t x = __float_as_uint(f), d = x - blo;
                         below += (uint32_t)__popcll(__builtin_amdgcn_uicmp(x, blo, kUlt));
