@@ -368,10 +368,13 @@ typedef struct {
  *   stats      host out or NULL (energies; non-NULL adds a synchronisation)
  * The context's workspace holds the iteration's planes (about 9 L N values
  * of the working precision, 11 L N with a label cost).  Synchronises once to
- * read gamma back.
+ * read gamma back (an image solved in one launch is waited for until that
+ * launch has begun).
  * Errors: CS_ERR_ARG for null pointers, sizes, L outside 1..64, lambda or nu
  * negative or not finite, iterations outside 0..1000000, an unknown
- * precision, or an undefined edge metric (see cs_edge_weight). */
+ * precision, or an undefined edge metric (see cs_edge_weight); CS_ERR_HIP also
+ * where the parts of a one-launch solve stopped hearing of each other (without
+ * stats, which bring that back, every label is then -1 and u is NaN). */
 int cs_segment(cs_ctx *ctx, const float *rgb, int H, int W, const float *loglik, int L,
                const cs_segment_params *prm, int32_t *labels, float *u, cs_segment_stats *stats);
 

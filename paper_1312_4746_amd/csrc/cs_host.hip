@@ -47,6 +47,12 @@ struct cs_ctx {
     // tag into (a log-likelihood call waits on the tag, not on the stream)
     int32_t *hcounts = nullptr, *hcounts_dev = nullptr;
     int32_t tag = 0;
+    // how long the tiles of the resident segmentation wait for each other: for
+    // their arrival (seconds), beyond which the other form runs, and whether for
+    // the words of tiles that have arrived; the device's wall clock
+    double arrive_s = 0.02;
+    bool wait_words = true;
+    int wall_khz = 0;
     // device counters that are zero between calls (kCtr*)
     unsigned int *dctr = nullptr;
     // Gaussian patch mask of the last (p, sigma)
@@ -123,10 +129,10 @@ hipError_t scratch_address(int device, char **out) {
     return hipSuccess;
 }
 
-// Waits until the sample scan of this call has written `tag` into host memory
-// (the label counts before it are then visible): spins, yields after 2 ms,
-// and after 5 s waits for the stream and looks once more (a failed stream
-// reports its error there).
+// Waits until a kernel of this call has written `tag` into host memory (what it
+// wrote there before, as the label counts, is then visible): spins, yields
+// after 2 ms, and after 5 s waits for the stream and looks once more (a failed
+// stream reports its error there).
 int wait_host_tag(cs_ctx *ctx, int32_t tag) {
     volatile int32_t *t = ctx->hcounts + kHostTag;
     const auto t0 = std::chrono::steady_clock::now();
@@ -135,7 +141,7 @@ int wait_host_tag(cs_ctx *ctx, int32_t tag) {
             const double sec = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
             if (sec > 5.0) {
                 HIP_TRY(hipStreamSynchronize(ctx->stream));
-                if (*t != tag) return fail(ctx, CS_ERR_HIP, "the label counts did not arrive from the device");
+                if (*t != tag) return fail(ctx, CS_ERR_HIP, "a result did not arrive from the device");
                 break;
             }
             if (sec > 2e-3) std::this_thread::yield();
@@ -331,6 +337,7 @@ int cs_create(cs_ctx **out, int device, void *hip_stream) {
     ctx->stream = (hipStream_t)hip_stream;
     hipError_t e = hipSetDevice(device);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&ctx->num_cu, hipDeviceAttributeMultiprocessorCount, device);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&ctx->wall_khz, hipDeviceAttributeWallClockRate, device);
     if (e == hipSuccess) e = hipHostMalloc((void **)&ctx->pinned, kPinnedBytes, hipHostMallocDefault);
     if (e == hipSuccess)
         e = hipHostMalloc((void **)&ctx->hcounts, sizeof(int32_t) * (kHostTag + 1),
@@ -1719,7 +1726,7 @@ int cs_segment(cs_ctx *ctx, const float *rgb, int H, int W, const float *loglik,
     Carve cv;
     const size_t o_mag = cv.take(sizeof(double) * (size_t)N);
     const size_t o_part = cv.take(sizeof(double) * (size_t)nb * (3 + L));
-    const size_t o_small = cv.take(sizeof(double) * 8);  // gamma, energies, labels present
+    const size_t o_small = cv.take(sizeof(double) * 8);  // gamma, energies, labels present, no result
     const size_t o_used = cv.take(sizeof(uint64_t) * (size_t)nb);
     const size_t o_g = cv.take(es * (size_t)N);
     const size_t o_f = cv.take(plane);
@@ -1775,11 +1782,24 @@ int cs_segment(cs_ctx *ctx, const float *rgb, int H, int W, const float *loglik,
         HIP_TRY(launch_pd_init(lc, a, prm->precision, loglik, !tiled || prm->iterations == 0));
     }
     int buf = 0, it = 0;
+    const unsigned int *gave_up = nullptr;
     if (rows) {
-        Timed t(ctx, "pd_iter");
-        if (launch_pd_resident(lc, a, rows) == hipSuccess) {
+        a.arrive_ticks = (int64_t)(ctx->arrive_s * 1e3 * ctx->wall_khz);
+        a.wait_words = ctx->wait_words;
+        a.host_out = ctx->hcounts_dev;
+        a.tag = ctx->tag = ctx->tag >= 0x3FFFFFFF ? 1 : ctx->tag + 1;
+        ctx->hcounts[kHostTag] = 0;
+        bool launched;
+        {
+            Timed t(ctx, "pd_iter");
+            launched = launch_pd_resident(lc, a, rows) == hipSuccess;
+        }
+        // (its tiles arrive within microseconds, or leave: the solve is not waited for)
+        if (launched && (rc = wait_host_tag(ctx, a.tag))) return rc;
+        if (launched && ((volatile int32_t *)ctx->hcounts)[0] == 1) {
             buf = 1;
             it = prm->iterations;
+            gave_up = pd_resident_ctl(a, rows) + kPdCtlGaveUp;
         }
     }
     const bool one_launch = it > 0;
@@ -1794,11 +1814,14 @@ int cs_segment(cs_ctx *ctx, const float *rgb, int H, int W, const float *loglik,
     {
         Timed t(ctx, "pd_finish");
         HIP_TRY(launch_pd_finish(lc, a, prm->precision, buf, labels, u, used, (double *)(ws + o_part),
-                                 stats ? small + 1 : nullptr));
+                                 stats ? small + 1 : nullptr, gave_up));
     }
     if (stats) {
-        HIP_TRY(hipMemcpyAsync(ctx->pinned, small, sizeof(double) * 5, hipMemcpyDeviceToHost, ctx->stream));
+        HIP_TRY(hipMemcpyAsync(ctx->pinned, small, sizeof(double) * 6, hipMemcpyDeviceToHost, ctx->stream));
         HIP_TRY(hipStreamSynchronize(ctx->stream));
+        double lost;
+        std::memcpy(&lost, ctx->pinned + 5 * sizeof(double), sizeof lost);
+        if (lost != 0.0) return fail(ctx, CS_ERR_HIP, "the segmentation's tiles waited for each other in vain");
         double e[4];
         unsigned long long bits;
         std::memcpy(e, ctx->pinned, sizeof(double) * 4);
@@ -1809,6 +1832,15 @@ int cs_segment(cs_ctx *ctx, const float *rgb, int H, int W, const float *loglik,
         stats->binary = e[2] + prm->nu * (double)stats->labels_used;
         stats->dual = e[3];
     }
+    return CS_OK;
+}
+
+// Not part of the interface: the waits of the resident segmentation, for tests
+// (arrive_s below 0: none for the tiles' arrival; wait_words 0: none for words).
+int cs_segment_waits(cs_ctx *ctx, double arrive_s, int wait_words) {
+    if (!ctx) return CS_ERR_ARG;
+    ctx->arrive_s = arrive_s;
+    ctx->wait_words = wait_words != 0;
     return CS_OK;
 }
 

@@ -473,6 +473,16 @@ struct PdArgs {
     double *mval;            // (iters + 1) x L: m^t
     double *msum;            // (iters + 1) x L: sum_x mu^t (zero before)
     uint64_t *exch;          // resident form: the tiles' exchange words (pd_resident_words)
+    // ... its control words (kPdCtl*, cleared by the launch), how long its tiles
+    // wait for each other's arrival (ticks of the device's wall clock, below 0:
+    // not at all), whether they wait for each other's words (tests do without),
+    // and where the host reads whether they have all arrived ({1 yes, 2 no},
+    // then tag at kHostTag)
+    unsigned int *ctl;
+    int64_t arrive_ticks;
+    bool wait_words;
+    volatile int32_t *host_out;
+    int32_t tag;
     double *mpart;           // tile launches with a label cost: 2 x L x tiles sums of mu
 };
 // |grad I| into mag (N doubles), per-workgroup partial sums into part
@@ -484,13 +494,16 @@ hipError_t launch_edge_weight(const LaunchCtx &lc, const float *rgb, int H, int 
 // buffer t & 1, writes the other); then the labels (and u pixel-major into
 // u_out when non-null), the labels present per workgroup (used, ceil(N / 256)
 // words) and, with energies non-null, {primal, binary without label cost,
-// dual, labels present as a bit mask} (part: ceil(N / 256) x (3 + L) doubles
+// dual, labels present as a bit mask, 1 where there is no result} (part: ceil(N / 256) x (3 + L) doubles
 // of scratch).
 hipError_t launch_pd_init(const LaunchCtx &lc, const PdArgs &a, int precision, const float *loglik, bool full);
 hipError_t launch_pd_iter(const LaunchCtx &lc, const PdArgs &a, int precision, int t);
 // buf: the buffer of the state after the last iteration
+// gave_up: device word, or null; where it is set the solve has no result, and
+// the labels are -1 and u is NaN.
 hipError_t launch_pd_finish(const LaunchCtx &lc, const PdArgs &a, int precision, int buf, int32_t *labels,
-                            float *u_out, unsigned long long *used, double *part, double *energies);
+                            float *u_out, unsigned long long *used, double *part, double *energies,
+                            const unsigned int *gave_up);
 // Tile form of the iteration (k_pd_tile.hip), FP32 and at most kPdTileLabels
 // labels: iterations t .. t + steps - 1 (steps <= S) from buffer cur into the
 // other one, S the iterations per launch that pd_tile_steps chose, and with a
@@ -501,9 +514,14 @@ int64_t pd_tiles(const PdArgs &a, int S);
 hipError_t launch_pd_tile(const LaunchCtx &lc, const PdArgs &a, int t, int cur, int S, int steps);
 // Resident form (every iteration in one cooperative launch, state in buffer 1
 // afterwards): the rows of its tiles, 0 where the image does not fit; its
-// exchange words; the launch (an error leaves the start state as it was).
+// exchange words; the launch.  Its tiles first wait for each other's arrival;
+// where that takes too long they all leave, nothing is written, and the other
+// form has to run (a.host_out tells).  A tile that waits in vain later on sets
+// ctl[kPdCtlGaveUp].
+constexpr int kPdCtlDecided = 0, kPdCtlGaveUp = 1, kPdCtlWords = 2;
 int pd_resident_rows(const LaunchCtx &lc, const PdArgs &a);
 size_t pd_resident_words(const PdArgs &a, int th);
+unsigned int *pd_resident_ctl(const PdArgs &a, int th);  // its control and arrival words, the last of these
 hipError_t launch_pd_resident(const LaunchCtx &lc, const PdArgs &a, int th);
 hipError_t launch_pd_msum(const LaunchCtx &lc, const PdArgs &a, int S);
 

@@ -358,11 +358,57 @@ __global__ __launch_bounds__(64) void k_pd_msum(PdArgs a, int ntiles) {
 // workgroup, which adds them and sends the totals to every tile (the low 16
 // bits of the FP64 sums carry the iteration number).
 //
-// The tiles wait for each other, so the launch is a cooperative one (all of
-// them resident; tiles that start early wait for compute units that other work
-// still holds).  A wait of more than ten seconds gives up: the tile's state
-// becomes NaN, no wait follows, and the launch ends.
+// The tiles wait for each other, so they have to be on the chip together: the
+// launch is a cooperative one, and before its first iteration every workgroup
+// waits until all have arrived (all_arrived).  Where that takes longer than
+// a.arrive_ticks, as where another kernel keeps compute units for long, one of
+// them decides that all leave without having written anything, the host sees it
+// and runs k_pd_tile instead.  Once all have arrived, every later wait ends by
+// itself; it still has an end of its own, kWaitPolls reads of its words (a look
+// at the clock in the loop took 0.1 us of an iteration, 0.5 with a label cost): the tile's state becomes NaN, no wait follows, ctl[kPdCtlGaveUp] is set,
+// and the launch ends.
+//
+// Every workgroup has an arrival word, and the first one reads them all (one
+// counter for all, whose additions follow one another, took 15 us of a solve).
 constexpr int kWaitPolls = 1 << 24;
+
+__device__ __forceinline__ bool all_arrived(const PdArgs &a, int nthr) {
+    __shared__ bool s_go;
+    unsigned int *decided = a.ctl + kPdCtlDecided, *arrived = a.ctl + kPdCtlWords;
+    const int tid = threadIdx.x, grid = gridDim.x;
+    auto decision = [&]() { return __hip_atomic_load(decided, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    auto decide = [&](unsigned int v) {  // the first decision stands, and is told to the host
+        unsigned int cur = 0;
+        if (!__hip_atomic_compare_exchange_strong(decided, &cur, v, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT))
+            return cur;
+        a.host_out[0] = (int32_t)v;
+        __threadfence_system();
+        a.host_out[kHostTag] = a.tag;
+        return v;
+    };
+    const int64_t t0 = (int64_t)wall_clock64();
+    auto late = [&]() { return (int64_t)wall_clock64() - t0 > a.arrive_ticks; };
+    if (blockIdx.x == 0) {
+        bool in = a.arrive_ticks >= 0;
+        for (int i = tid ? tid : nthr; in && i < grid; i += nthr)
+            while (in && !__hip_atomic_load(arrived + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                in = !decision() && !late();
+        const bool all = __syncthreads_and(in);
+        if (tid == 0) s_go = decide(all ? 1u : 2u) == 1u;
+    } else if (tid == 0) {
+        unsigned int d = a.arrive_ticks < 0 ? decide(2u) : 0u;
+        __hip_atomic_store(arrived + blockIdx.x, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        while (!d) {
+            d = decision();
+            if (!d && late()) d = decide(2u);
+            if (!d) __builtin_amdgcn_s_sleep(1);
+        }
+        s_go = d == 1u;
+    }
+    __syncthreads();
+    return s_go;
+}
 
 __device__ __forceinline__ void put_word(uint64_t *p, uint64_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -423,7 +469,8 @@ __global__ __launch_bounds__(NT) void k_pd_resident(PdArgs a, int th, int tiles_
     }
     // [2][L][tile] sums of mu, [2][16] their totals
     uint64_t *psum = a.exch + 2 * ebuf, *ptot = psum + 2 * (int64_t)ntiles * L;
-    bool alive = true;
+    if (!all_arrived(a, nthr)) return;
+    bool alive = a.wait_words;
     if constexpr (MDL) {
         if (tile == ntiles) {
             // the workgroup past the tiles adds the tiles' sums, one wave per label
@@ -457,6 +504,7 @@ __global__ __launch_bounds__(NT) void k_pd_resident(PdArgs a, int th, int tiles_
                     }
                 }
             }
+            if (!alive) a.ctl[kPdCtlGaveUp] = 1u;
             return;
         }
         for (int i = tid; i < kWaves * 16; i += nthr) (&s_red[0][0])[i] = 0.0f;
@@ -592,6 +640,7 @@ __global__ __launch_bounds__(NT) void k_pd_resident(PdArgs a, int th, int tiles_
         }
         __syncthreads();
     }
+    if (!alive) a.ctl[kPdCtlGaveUp] = 1u;
     if (own) {
         float *U = (float *)a.u[1], *PX = (float *)a.px[1], *PY = (float *)a.py[1];
         float *MU = MDL ? (float *)a.mu[1] : nullptr;
@@ -677,9 +726,17 @@ static int64_t resident_tiles(const PdArgs &a, int th) {
     return (int64_t)((a.W + kTd - 3) / (kTd - 2)) * ((a.H + th - 3) / (th - 2));
 }
 
+// Control words, then an arrival word per workgroup (an even number).
+static size_t ctl_words(const PdArgs &a, int th) { return kPdCtlWords + (resident_tiles(a, th) + 2) / 2 * 2; }
+
 size_t pd_resident_words(const PdArgs &a, int th) {
     const int per_tile = 2 * (kTd - 2) + 2 * (th - 4);
-    return (size_t)resident_tiles(a, th) * 2 * a.L * (per_tile + (a.mdl ? 1 : 0)) + (a.mdl ? 2 * 16 : 0);
+    return (size_t)resident_tiles(a, th) * 2 * a.L * (per_tile + (a.mdl ? 1 : 0)) + (a.mdl ? 2 * 16 : 0) +
+           ctl_words(a, th) / 2;
+}
+
+unsigned int *pd_resident_ctl(const PdArgs &a, int th) {
+    return (unsigned int *)(a.exch + pd_resident_words(a, th)) - ctl_words(a, th);
 }
 
 template <bool MDL>
@@ -699,6 +756,7 @@ hipError_t launch_pd_resident(const LaunchCtx &lc, const PdArgs &a, int th) {
     hipError_t e = launch_fill_u32(lc, (unsigned int *)a.exch, 2 * pd_resident_words(a, th), 0u);
     if (e != hipSuccess) return e;
     PdArgs arg = a;
+    arg.ctl = pd_resident_ctl(a, th);
     int tiles_x = (a.W + kTd - 3) / (kTd - 2), nt = (int)resident_tiles(a, th);
     void *args[] = {&arg, &th, &tiles_x, &nt};
     e = hipLaunchCooperativeKernel(a.mdl ? resident_kernel<true>(a.L) : resident_kernel<false>(a.L),

@@ -516,27 +516,28 @@ __global__ __launch_bounds__(256) void k_pd_primal(PdArgs a, int t) {
 // stores one row of L per lane were most of 35 us at 481 x 321).
 template <typename T>
 __global__ __launch_bounds__(256) void k_pd_labels(PdArgs a, int buf, int32_t *labels, float *u_out,
-                                                   unsigned long long *used) {
+                                                   unsigned long long *used, const unsigned int *gave_up) {
     extern __shared__ float s_u[];  // [L][257]
     __shared__ unsigned long long s_bits[4];
     const int64_t x0 = (int64_t)blockIdx.x * 256, x = x0 + threadIdx.x;
     const int L = a.L, n = (int)(a.N - x0 < 256 ? a.N - x0 : 256);
     const T *U = (const T *)a.u[buf];
     unsigned long long bit = 0;
+    const bool none = gave_up && *gave_up;  // the solve ended without a result
     if (x < a.N) {
         int best = 0;
         T bv = U[x];
 #pragma unroll 4
         for (int l = 0; l < L; ++l) {
-            const T v = U[(int64_t)l * a.N + x];
+            const T v = none ? (T)__builtin_nanf("") : U[(int64_t)l * a.N + x];
             if (u_out) s_u[l * 257 + threadIdx.x] = (float)v;
             if (v > bv) {
                 bv = v;
                 best = l;
             }
         }
-        labels[x] = best;
-        bit = 1ull << best;
+        labels[x] = none ? -1 : best;
+        bit = none ? 0ull : 1ull << best;
     }
     for (int off = 32; off >= 1; off >>= 1) bit |= __shfl_xor(bit, off);
     if ((threadIdx.x & 63) == 0) s_bits[threadIdx.x >> 6] = bit;
@@ -614,7 +615,7 @@ __global__ __launch_bounds__(256) void k_pd_energy(PdArgs a, int buf, const int3
         }
     }
     if (in) {
-        bin = bin + (double)F[(int64_t)lx * N + x];
+        bin = bin + (double)F[(int64_t)max(lx, 0) * N + x];
         dual = dmin;
     } else {
         prim = bin = 0.0;
@@ -637,9 +638,10 @@ __global__ __launch_bounds__(256) void k_pd_energy(PdArgs a, int buf, const int3
 // The partial energies added in a fixed order (one workgroup, a wave per row:
 // lanes strided, then a butterfly); for a label cost also the label-cost terms
 // and sum_i min(0, nu + sum_x mu_i).  out: {primal, binary (without the label
-// cost), dual}, then the labels present as a bit mask.
+// cost), dual}, then the labels present as a bit mask and whether the solve ended
+// without a result.
 __global__ __launch_bounds__(1024) void k_pd_energy_final(PdArgs a, const double *part, const unsigned long long *used,
-                                                         int nparts, double *out) {
+                                                         int nparts, const unsigned int *gave_up, double *out) {
 #pragma clang fp contract(off)
     __shared__ double s_row[3 + kMaxLabels];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -676,6 +678,7 @@ __global__ __launch_bounds__(1024) void k_pd_energy_final(PdArgs a, const double
         out[0] = s_row[0] + mdl_p;
         out[1] = s_row[1];
         out[2] = s_row[2] + mdl_d;
+        out[4] = gave_up && *gave_up ? 1.0 : 0.0;
     }
 }
 
@@ -751,21 +754,24 @@ hipError_t launch_pd_iter(const LaunchCtx &lc, const PdArgs &a, int precision, i
 
 template <typename T>
 static hipError_t pd_finish(const LaunchCtx &lc, const PdArgs &a, int buf, int32_t *labels, float *u_out,
-                            unsigned long long *used, double *part, double *energies) {
+                            unsigned long long *used, double *part, double *energies,
+                            const unsigned int *gave_up) {
     const unsigned nb = (unsigned)((a.N + 255) / 256);
     hipLaunchKernelGGL(k_pd_labels<T>, dim3(nb), dim3(256), u_out ? sizeof(float) * 257 * (size_t)a.L : 0, lc.stream,
-                       a, buf, labels, u_out, used);
+                       a, buf, labels, u_out, used, gave_up);
     if (energies) {
         hipLaunchKernelGGL(k_pd_energy<T>, dim3(nb), dim3(256), 0, lc.stream, a, buf, labels, part);
-        hipLaunchKernelGGL(k_pd_energy_final, dim3(1), dim3(1024), 0, lc.stream, a, part, used, (int)nb, energies);
+        hipLaunchKernelGGL(k_pd_energy_final, dim3(1), dim3(1024), 0, lc.stream, a, part, used, (int)nb, gave_up,
+                           energies);
     }
     return hipGetLastError();
 }
 
 hipError_t launch_pd_finish(const LaunchCtx &lc, const PdArgs &a, int precision, int buf, int32_t *labels,
-                            float *u_out, unsigned long long *used, double *part, double *energies) {
-    if (precision == CS_FP64) return pd_finish<double>(lc, a, buf, labels, u_out, used, part, energies);
-    return pd_finish<float>(lc, a, buf, labels, u_out, used, part, energies);
+                            float *u_out, unsigned long long *used, double *part, double *energies,
+                            const unsigned int *gave_up) {
+    if (precision == CS_FP64) return pd_finish<double>(lc, a, buf, labels, u_out, used, part, energies, gave_up);
+    return pd_finish<float>(lc, a, buf, labels, u_out, used, part, energies, gave_up);
 }
 
 }  // namespace cs
