@@ -49,9 +49,11 @@ struct cs_ctx {
     int32_t tag = 0;
     // how long the tiles of the resident segmentation wait for each other: for
     // their arrival (seconds), beyond which the other form runs, and whether for
-    // the words of tiles that have arrived; the device's wall clock
+    // the words of tiles that have arrived; the device's wall clock; an error
+    // that stands for the launch (tests)
     double arrive_s = 0.02;
     bool wait_words = true;
+    int launch_error = 0;
     int wall_khz = 0;
     // device counters that are zero between calls (kCtr*)
     unsigned int *dctr = nullptr;
@@ -1789,11 +1791,14 @@ int cs_segment(cs_ctx *ctx, const float *rgb, int H, int W, const float *loglik,
         a.host_out = ctx->hcounts_dev;
         a.tag = ctx->tag = ctx->tag >= 0x3FFFFFFF ? 1 : ctx->tag + 1;
         ctx->hcounts[kHostTag] = 0;
-        bool launched;
-        {
+        hipError_t e = (hipError_t)ctx->launch_error;
+        if (e == hipSuccess) {
             Timed t(ctx, "pd_iter");
-            launched = launch_pd_resident(lc, a, rows) == hipSuccess;
+            e = launch_pd_resident(lc, a, rows);
         }
+        // only a device that cannot hold the launch takes the other form
+        const bool launched = e != hipErrorCooperativeLaunchTooLarge && e != hipErrorNotSupported;
+        if (launched) HIP_TRY(e);
         // (its tiles arrive within microseconds, or leave: the solve is not waited for)
         if (launched && (rc = wait_host_tag(ctx, a.tag))) return rc;
         if (launched && ((volatile int32_t *)ctx->hcounts)[0] == 1) {
@@ -1836,9 +1841,11 @@ int cs_segment(cs_ctx *ctx, const float *rgb, int H, int W, const float *loglik,
 }
 
 // Not part of the interface: the waits of the resident segmentation, for tests
-// (arrive_s below 0: none for the tiles' arrival; wait_words 0: none for words).
-int cs_segment_waits(cs_ctx *ctx, double arrive_s, int wait_words) {
+// (arrive_s below 0: none for the tiles' arrival; wait_words 0: none for words),
+// and an error that stands for its launch (0: none).
+int cs_segment_waits(cs_ctx *ctx, double arrive_s, int wait_words, int launch_error) {
     if (!ctx) return CS_ERR_ARG;
+    ctx->launch_error = launch_error;
     ctx->arrive_s = arrive_s;
     ctx->wait_words = wait_words != 0;
     return CS_OK;

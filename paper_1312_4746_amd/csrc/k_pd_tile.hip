@@ -761,7 +761,8 @@ hipError_t launch_pd_resident(const LaunchCtx &lc, const PdArgs &a, int th) {
     void *args[] = {&arg, &th, &tiles_x, &nt};
     e = hipLaunchCooperativeKernel(a.mdl ? resident_kernel<true>(a.L) : resident_kernel<false>(a.L),
                                    dim3((unsigned)(nt + (a.mdl ? 1 : 0))), dim3((unsigned)(kTd * th)), args, 0, lc.stream);
-    if (e != hipSuccess) (void)hipGetLastError();  // the caller takes the other form
+    // (for these the caller takes the other form)
+    if (e == hipErrorCooperativeLaunchTooLarge || e == hipErrorNotSupported) (void)hipGetLastError();
     return e;
 }
 

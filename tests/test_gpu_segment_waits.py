@@ -14,12 +14,12 @@ from workloads import make_workload
 pytestmark = pytest.mark.gpu
 
 
-def _ctx(arrive=0.02, words=1):
+def _ctx(arrive=0.02, words=1, error=0):
     from paper_1312_4746_amd import Context, lib
     c = Context(0)
     f = lib().cs_segment_waits
-    f.argtypes = [ctypes.c_void_p, ctypes.c_double, ctypes.c_int]
-    assert f(c._h, arrive, words) == 0
+    f.argtypes = [ctypes.c_void_p, ctypes.c_double, ctypes.c_int, ctypes.c_int]
+    assert f(c._h, arrive, words, error) == 0
     return c
 
 
@@ -71,8 +71,24 @@ def test_lost_words_are_reported(H, W, L, nu):
     lab, u, _ = _solve(c, w, ll, _params(nu, 9), stats=False)
     assert bool((lab == -1).all()) and bool(u.isnan().all())
     from paper_1312_4746_amd import lib
-    assert lib().cs_segment_waits(c._h, 0.02, 1) == 0
+    assert lib().cs_segment_waits(c._h, 0.02, 1, 0) == 0
     _check(c, w.rgb, ll, 1.5, nu, 9, "fp32")
+    c.close()
+
+
+@pytest.mark.parametrize("error,falls_back", [(720, True), (801, True), (1, False), (2, False), (719, False)])
+def test_errors_of_the_launch(error, falls_back):
+    """A launch too large for the device (720) or not supported (801) takes the
+    tile form; any other error is the call's."""
+    from paper_1312_4746_amd import CosparseError
+    w, ll = _case(40, 61, 3, 29)
+    c = _ctx(error=error)
+    if falls_back:
+        _check(c, w.rgb, ll, 1.5, 0.0, 9, "fp32")
+    else:
+        with pytest.raises(CosparseError) as e:
+            _solve(c, w, ll, _params(0.0, 9))
+        assert e.value.code == 3
     c.close()
 
 
