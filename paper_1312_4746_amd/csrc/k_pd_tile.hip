@@ -151,6 +151,18 @@ __device__ __forceinline__ void wave_sums16(float (&x)[16]) {
     ROW_ADD(0x118)
 #undef ROW_ADD
 }
+// The FP64 value whose halves rows of 16 lanes hold, high, low, high, low: to
+// both rows of a pair.
+__device__ __forceinline__ double join_rows(uint32_t half) {
+    const auto p = __builtin_amdgcn_permlane16_swap(half, half, false, false);
+    return __builtin_bit_cast(double, (uint64_t)p[0] << 32 | p[1]);
+}
+// This lane's half of v (high in even rows of 16 lanes).
+__device__ __forceinline__ uint32_t row_half(double v, int lane) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    return (uint32_t)(lane & 16 ? b : b >> 32);
+}
+
 // The label of x[i] in this lane's row, after wave_sums16.
 __device__ __forceinline__ int sums16_label(int i, int lane) { return i + 4 * ((lane >> 4) & 1) + 8 * (lane >> 5); }
 
@@ -354,9 +366,9 @@ __global__ __launch_bounds__(64) void k_pd_msum(PdArgs a, int ntiles) {
 // holds its value and no further ordering is needed; two buffers alternate,
 // and a tile can only be one iteration ahead of its neighbours (its next
 // iteration needs theirs), so no word is overwritten before it was read.
-// With a label cost the tiles' sums of mu travel the same way to one more
-// workgroup, which adds them and sends the totals to every tile (the low 16
-// bits of the FP64 sums carry the iteration number).
+// With a label cost the tiles' sums of mu travel the same way, each half of an
+// FP64 value in a word of its own and a tile's words in a row, to one more
+// workgroup, which adds them and sends the totals to every tile.
 //
 // The tiles wait for each other, so they have to be on the chip together: the
 // launch is a cooperative one, and before its first iteration every workgroup
@@ -431,6 +443,9 @@ __global__ __launch_bounds__(NT) void k_pd_resident(PdArgs a, int th, int tiles_
     constexpr bool kHoldF = !MDL || L <= 8;  // f in registers, else (the thread's own words) in LDS
     __shared__ float s_f[kHoldF ? 1 : L][NT];
     __shared__ float s_red[MDL ? kWaves : 1][16];
+    __shared__ float s_mb[MDL ? 16 : 1];
+    __shared__ double s_sum[MDL ? 2 : 1][kWaves][16];
+    constexpr int kAhead = 5;  // pairs of tiles a wave reads together (two rounds for 240 tiles and 12 waves)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nthr = kTd * th, nwave = nthr / 64;
     const int W = a.W, H = a.H, ih = th - 2;
     const int64_t N = a.N;
@@ -467,42 +482,45 @@ __global__ __launch_bounds__(NT) void k_pd_resident(PdArgs a, int th, int tiles_
             dst[k] = ok ? l * NT + sy * kTd + sx : 0;
         }
     }
-    // [2][L][tile] sums of mu, [2][16] their totals
-    uint64_t *psum = a.exch + 2 * ebuf, *ptot = psum + 2 * (int64_t)ntiles * L;
+    // [2][tile][high, low][16] sums of mu, [2][high, low][16] their totals
+    uint64_t *psum = a.exch + 2 * ebuf, *ptot = psum + 2 * 32 * (int64_t)ntiles;
+    const int ml = lane & 15;  // the label of this lane's sums
     if (!all_arrived(a, nthr)) return;
     bool alive = a.wait_words;
     if constexpr (MDL) {
         if (tile == ntiles) {
-            // the workgroup past the tiles adds the tiles' sums, one wave per label
+            // the workgroup past the tiles adds the tiles' sums: a wave's load
+            // has the words of two of them, a wave takes every nwave-th pair,
+            // and the first wave adds the waves' sums
             for (int t = 0; t < a.iters; ++t) {
-                const uint64_t stag = (uint64_t)(t % 65535 + 1);
-                for (int l = wave; l < L; l += nwave) {
-                    const uint64_t *ps = psum + ((int64_t)(t & 1) * L + l) * ntiles;
-                    double s = 0.0;
-                    for (int i0 = lane; i0 < ntiles; i0 += 256) {
-                        for (int n = 0;; ++n) {
-                            uint64_t w[4];
+                const uint32_t tag = (uint32_t)t + 1u;
+                const uint64_t *ps = psum + (int64_t)(t & 1) * 32 * ntiles;
+                double s = 0.0;
+                for (int i0 = 2 * wave; i0 < ntiles; i0 += 2 * kAhead * nwave) {  // (wave-uniform)
+                    uint64_t w[kAhead];
+                    bool got = false;
+                    for (int n = 0; alive && !got; ++n) {
+                        got = true;
 #pragma unroll
-                            for (int q = 0; q < 4; ++q) w[q] = i0 + 64 * q < ntiles ? get_word(ps + i0 + 64 * q) : stag;
-                            bool got = true;
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) got &= (w[q] & 0xffff) == stag;
-                            if (!got && alive && n < kWaitPolls) continue;
-                            alive &= got;
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) s = s + __builtin_bit_cast(double, w[q] & ~(uint64_t)0xffff);
-                            break;
+                        for (int q = 0; q < kAhead; ++q) {
+                            const int i = i0 + 2 * nwave * q + (lane >> 5);
+                            w[q] = i < ntiles && ml < L ? get_word(ps + i * 32 + (lane & 31)) : (uint64_t)tag << 32;
                         }
-                    }
-                    s = alive ? s : __builtin_nan("");
 #pragma unroll
-                    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-                    if (lane == 0) {
-                        put_word(ptot + (t & 1) * 16 + l,
-                                 (__builtin_bit_cast(uint64_t, s) & ~(uint64_t)0xffff) | stag);
-                        if (t + 1 == a.iters) a.msum[(int64_t)a.iters * L + l] = s;
+                        for (int q = 0; q < kAhead; ++q) got &= (uint32_t)(w[q] >> 32) == tag;
+                        alive = n < kWaitPolls;
                     }
+#pragma unroll
+                    for (int q = 0; q < kAhead; ++q) s = s + join_rows(got ? (uint32_t)w[q] : 0x7ff80000u);
                 }
+                s = s + __shfl_xor(s, 32);
+                if (lane < 16) s_sum[t & 1][wave][lane] = s;
+                __syncthreads();
+                if (wave != 0) continue;
+                s = 0.0;
+                for (int v = 0; v < nwave; ++v) s = s + s_sum[t & 1][v][ml];
+                if (ml < L && lane < 32) put_word(ptot + (t & 1) * 32 + lane, (uint64_t)tag << 32 | row_half(s, lane));
+                if (lane < L && t + 1 == a.iters) a.msum[(int64_t)a.iters * L + lane] = s;
             }
             if (!alive) a.ctl[kPdCtlGaveUp] = 1u;
             return;
@@ -529,8 +547,7 @@ __global__ __launch_bounds__(NT) void k_pd_resident(PdArgs a, int th, int tiles_
     const bool plain = __all(!in || (rad > 1e-9f && rad < 1e9f));  // the wave's
     const float rad2 = rad * rad * (1.0f - 0x1p-20f);
     const int dn = tid + kTd < nthr ? tid + kTd : tid, up = tid >= kTd ? tid - kTd : tid;
-    // label lane & 15: m^t (every wave keeps the same)
-    const int ml = lane & 15;
+    // of label ml: m^t (the first wave's) and m_bar^t
     double m = 1.0;
     float mb = 1.0f;
     __syncthreads();
@@ -538,6 +555,8 @@ __global__ __launch_bounds__(NT) void k_pd_resident(PdArgs a, int th, int tiles_
         if (ring && t > 0)
 #pragma unroll
             for (int l = 0; l < L; ++l) ub[l] = s_ub[l][tid];
+        if constexpr (MDL)
+            if (t > 0) mb = s_mb[ml];
         float gy[L];
 #pragma unroll
         for (int l = 0; l < L; ++l) gy[l] = s_ub[l][dn];
@@ -566,13 +585,11 @@ __global__ __launch_bounds__(NT) void k_pd_resident(PdArgs a, int th, int tiles_
         }
         __syncthreads();
         if constexpr (MDL) {
-            if (tid < L) {
+            if (tid < 32 && ml < L) {
                 double tot = 0.0;
 #pragma unroll
-                for (int w = 0; w < kWaves; ++w) tot = tot + (double)s_red[w][tid];
-                const uint64_t bits = __builtin_bit_cast(uint64_t, tot);
-                put_word(psum + ((int64_t)(t & 1) * L + tid) * ntiles + tile,
-                         (bits & ~(uint64_t)0xffff) | (uint64_t)(t % 65535 + 1));
+                for (int w = 0; w < kWaves; ++w) tot = tot + (double)s_red[w][ml];
+                put_word(psum + ((int64_t)(t & 1) * ntiles + tile) * 32 + tid, (uint64_t)(t + 1) << 32 | row_half(tot, lane));
             }
         }
 #pragma unroll
@@ -609,19 +626,19 @@ __global__ __launch_bounds__(NT) void k_pd_resident(PdArgs a, int th, int tiles_
                     put_word(e + (int64_t)tile * per_tile * L + tid + k * nthr,
                              (uint64_t)tag << 32 | __builtin_bit_cast(uint32_t, ub0[src[k]]));
         }
-        // the neighbours' words and, with a label cost, the total of label
-        // lane & 15 (every wave keeps m of its own)
+        // the neighbours' words and, with a label cost, in the first wave half a
+        // total of label lane & 15 (every wave reading them and keeping an m of its
+        // own, 13.6 us an iteration)
         if (more) {
             const uint64_t *e = a.exch + (int64_t)(t & 1) * ebuf;
-            const uint64_t *pt = ptot + (t & 1) * 16 + (ml < L ? ml : 0);
-            const uint64_t stag = (uint64_t)(t % 65535 + 1);
+            const uint64_t *pt = ptot + (t & 1) * 32 + (ml < L ? lane & 31 : 0);
             uint64_t w[3], sw = 0;
             bool got = false;
             for (int n = 0; alive && !got; ++n) {
 #pragma unroll
                 for (int k = 0; k < 3; ++k) w[k] = rd[k] >= 0 ? get_word(e + rd[k]) : (uint64_t)tag << 32;
-                if constexpr (MDL) sw = get_word(pt);
-                got = !MDL || (sw & 0xffff) == stag;
+                if (MDL && wave == 0) sw = get_word(pt);
+                got = !MDL || wave != 0 || (uint32_t)(sw >> 32) == tag;
 #pragma unroll
                 for (int k = 0; k < 3; ++k) got &= (uint32_t)(w[k] >> 32) == tag;
                 alive = n < kWaitPolls;
@@ -630,11 +647,10 @@ __global__ __launch_bounds__(NT) void k_pd_resident(PdArgs a, int th, int tiles_
             for (int k = 0; k < 3; ++k)
                 if (rd[k] >= 0)
                     (&s_ub[0][0])[dst[k]] = got ? __builtin_bit_cast(float, (uint32_t)w[k]) : __builtin_nanf("");
-            if constexpr (MDL) {
-                const double s = got ? __builtin_bit_cast(double, sw & ~(uint64_t)0xffff) : __builtin_nan("");
-                double mn = m - a.tau_m * (a.nu + s);
+            if (MDL && wave == 0) {
+                double mn = m - a.tau_m * (a.nu + join_rows(got ? (uint32_t)sw : 0x7ff80000u));
                 mn = mn < 0.0 ? 0.0 : (mn > 1.0 ? 1.0 : mn);
-                mb = (float)(2.0 * mn - m);
+                if (tid < 16) s_mb[tid] = (float)(2.0 * mn - m);
                 m = mn;
             }
         }
@@ -731,7 +747,7 @@ static size_t ctl_words(const PdArgs &a, int th) { return kPdCtlWords + (residen
 
 size_t pd_resident_words(const PdArgs &a, int th) {
     const int per_tile = 2 * (kTd - 2) + 2 * (th - 4);
-    return (size_t)resident_tiles(a, th) * 2 * a.L * (per_tile + (a.mdl ? 1 : 0)) + (a.mdl ? 2 * 16 : 0) +
+    return (size_t)resident_tiles(a, th) * 2 * (a.L * per_tile + (a.mdl ? 32 : 0)) + (a.mdl ? 2 * 32 : 0) +
            ctl_words(a, th) / 2;
 }
 

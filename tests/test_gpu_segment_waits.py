@@ -5,6 +5,7 @@ other work.  Every launch ends by itself.  Bars as in test_gpu_segment."""
 import ctypes
 import threading
 
+import numpy as np
 import pytest
 import torch
 from test_gpu_segment import _check, _synthetic_term, dev
@@ -143,3 +144,28 @@ def test_beside_other_work():
     torch.cuda.synchronize()
     assert torch.equal(r[0], alone[0]) and torch.equal(r[1], alone[1])
     c.close()
+
+
+@pytest.mark.parametrize("nu,top", [(1e5, 3), (3e5, 3), (3e5, 6)])
+def test_label_cost_sums_keep_every_bit(nu, top):
+    """450 x 480 with 3 labels has the same tiles in both forms, whose FP64 sums of
+    the multipliers differ by the order of additions alone: 2^-53 for each of the
+    240 tiles and 400 iterations of a sum that the dual energy contains.  The data
+    term's strength varies by rows, so that a tile's sum spans more binades than
+    37 bits hold."""
+    w, ll = _case(450, 480, 3, 30)
+    rows = np.exp(np.random.default_rng(1).uniform(-9, top, w.H)).astype(np.float32)
+    ll = ll * np.repeat(rows, w.W)[:, None]
+    prm = _params(nu, 400)
+    c, c2 = _ctx(), _ctx(arrive=-1.0)
+    c.profile_only("pd_iter")
+    c.profile_enable(True)
+    got = _solve(c, w, ll, prm)
+    assert c.profile_read("pd_iter")[1] == 1
+    c.profile_enable(False)
+    ref = _solve(c2, w, ll, prm)
+    print(got[2], ref[2])
+    assert abs(got[2]["dual"] - ref[2]["dual"]) <= 240 * 400 * 2.0 ** -53 * abs(ref[2]["dual"])
+    assert float((got[1] - ref[1]).abs().max()) <= 2.0 ** -24
+    c.close()
+    c2.close()
