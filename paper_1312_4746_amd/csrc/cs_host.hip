@@ -1322,6 +1322,7 @@ struct cs_mlp {
     int64_t t = 0;  // Adam steps taken
     char *mem = nullptr;
     float *params = nullptr, *m = nullptr, *v = nullptr;
+    double *bsum = nullptr;  // partial sums of cs_mlp_fit_output_bias
     short *W1f = nullptr, *W2f = nullptr, *W3f = nullptr, *W2Tf = nullptr, *W3Tf = nullptr;
 };
 
@@ -1460,6 +1461,7 @@ int cs_mlp_init(cs_ctx *ctx, cs_mlp **net, int in_dim, int hidden, int out_dim, 
     const size_t o_w2t = cv.take(sizeof(short) * kMlpHid * kMlpHid);
     const size_t o_w3 = cv.take(sizeof(short) * kMlpOutPad * kMlpHid);
     const size_t o_w3t = cv.take(sizeof(short) * kMlpHid * kMlpOutPad);
+    const size_t o_bs = cv.take(mlp_bias_mean_bytes(n->out));
     if (hipMalloc((void **)&n->mem, cv.off) != hipSuccess) {
         delete n;
         return fail(ctx, CS_ERR_NOMEM, "network memory of %zu bytes could not be allocated", cv.off);
@@ -1467,6 +1469,7 @@ int cs_mlp_init(cs_ctx *ctx, cs_mlp **net, int in_dim, int hidden, int out_dim, 
     n->params = (float *)(n->mem + o_p);
     n->m = (float *)(n->mem + o_m);
     n->v = (float *)(n->mem + o_v);
+    n->bsum = (double *)(n->mem + o_bs);
     n->W1f = (short *)(n->mem + o_w1);
     n->W2f = (short *)(n->mem + o_w2);
     n->W2Tf = (short *)(n->mem + o_w2t);
@@ -1561,9 +1564,7 @@ int cs_mlp_fit_output_bias(cs_ctx *ctx, cs_mlp *net, const float *ell, int64_t n
     if (!ctx) return CS_ERR_ARG;
     if (!net || !ell || n < 1) return fail(ctx, CS_ERR_ARG, "null pointer or n < 1");
     HIP_TRY(hipSetDevice(ctx->device));
-    int rc = ensure_ws(ctx, mlp_bias_mean_bytes(n, net->out));
-    if (rc) return rc;
-    HIP_TRY(launch_mlp_bias_mean(lc_of(ctx), ell, n, net->out, (double *)ctx->ws, net->params + net->off_b3));
+    HIP_TRY(launch_mlp_bias_mean(lc_of(ctx), ell, n, net->out, net->bsum, net->params + net->off_b3));
     return CS_OK;
 }
 

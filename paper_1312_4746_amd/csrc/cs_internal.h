@@ -593,8 +593,9 @@ hipError_t launch_mlp_fwdbwd(const LaunchCtx &lc, const MlpTrainArgs &a);
 hipError_t launch_mlp_grad_adam(const LaunchCtx &lc, const MlpAdamArgs &a);
 hipError_t launch_mlp_convert(const LaunchCtx &lc, const MlpAdamArgs &a);
 hipError_t launch_mlp_infer(const LaunchCtx &lc, const MlpInferArgs &a);
-// part: mlp_bias_mean_bytes of scratch
-size_t mlp_bias_mean_bytes(int64_t n, int out);
+// part: mlp_bias_mean_bytes of scratch, whatever the rows (the network's own: the
+// call needs no workspace)
+size_t mlp_bias_mean_bytes(int out);
 hipError_t launch_mlp_bias_mean(const LaunchCtx &lc, const float *ell, int64_t n, int out, double *part, float *b3);
 // Exact fallback of the surrogate: pixels whose top-two outputs differ by less
 // than margin are listed (count zero before), and exact rows are put back.

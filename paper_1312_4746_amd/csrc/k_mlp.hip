@@ -884,8 +884,9 @@ __global__ __launch_bounds__(64) void k_mlp_bias_mean(const double *part, int np
     if (threadIdx.x == 0) b3[blockIdx.x] = (float)(s / (double)n);
 }
 
-static unsigned target_parts(int64_t n) { return (unsigned)(n < 256 * 256 ? (n + 255) / 256 : 256); }
-size_t mlp_bias_mean_bytes(int64_t n, int out) { return sizeof(double) * (size_t)out * target_parts(n); }
+constexpr int kTargetParts = 256;
+static unsigned target_parts(int64_t n) { return (unsigned)(n < 256 * kTargetParts ? (n + 255) / 256 : kTargetParts); }
+size_t mlp_bias_mean_bytes(int out) { return sizeof(double) * (size_t)out * kTargetParts; }
 hipError_t launch_mlp_bias_mean(const LaunchCtx &lc, const float *ell, int64_t n, int out, double *part, float *b3) {
     const unsigned parts = target_parts(n);
     hipLaunchKernelGGL(k_mlp_target_sums, dim3(parts), dim3(256), 0, lc.stream, ell, n, out, part);
