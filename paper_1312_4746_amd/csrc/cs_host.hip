@@ -554,7 +554,7 @@ int tau_stage(cs_ctx *ctx, const float *rgb, int H, int W, int p, const float *o
     {
         Timed t(ctx, "tau_exact");
         HIP_TRY(tau_finish(lc, rgb, H, W, p, n, ctx->wmask, omega, k, cand, cap, vals, frac, st, parts, tau_out,
-                           pstats, nullptr, nullptr, nullptr, mmax));
+                           pstats, nullptr, nullptr, nullptr, mmax, !first));
     }
     return CS_OK;
 }
@@ -836,7 +836,7 @@ int cs_cosupport_median(cs_ctx *ctx, const float *rgb, int H, int W, int p, doub
         {
             Timed t(ctx, "tau_exact");
             HIP_TRY(tau_finish(lc, rgb, H, W, p, n, ctx->wmask, omega, k, cand, count, vals, frac, st, parts,
-                               tau_dev, pst, ccnt, &fl, hist3 + 2 * kHistBins, mmax));
+                               tau_dev, pst, ccnt, &fl, hist3 + 2 * kHistBins, mmax, false));
         }
         {
             Timed t(ctx, "cosupport_fix");

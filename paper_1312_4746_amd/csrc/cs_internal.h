@@ -230,12 +230,13 @@ hipError_t list_compact(const LaunchCtx &lc, int64_t nw, const int64_t *cand, co
 // ccnt non-null the candidates come from the fused co-support pass (fl: its
 // compact list, or its per-wave regions of cand when it did not fit).  bins:
 // kHistBins cleared words in which the values are counted for the selection, or
-// null; max_margin: the largest row margin.
+// null; max_margin: the largest row margin; retry: a second pass with room for
+// more candidates.
 hipError_t tau_finish(const LaunchCtx &lc, const float *rgb, int H, int W, int p, int n,
                       const double *wmask, const float *omega, int k, const int64_t *cand,
                       int64_t cap, double *vals, double frac, TauState *st, unsigned long long *parts,
                       double *tau_out, const double *pstats, const unsigned int *ccnt, const FusedLists *fl,
-                      unsigned int *bins, const double *max_margin);
+                      unsigned int *bins, const double *max_margin, bool retry);
 // Device counters of a context that are zero between calls (each use resets
 // its own): [kCtrSampleCount] the groups of sample-count workgroups done, those
 // done of group g at kCtrGroup0 + g kCtrStride from there (a cache line each),

@@ -776,7 +776,7 @@ hipError_t tau_finish(const LaunchCtx &lc, const float *rgb, int H, int W, int p
                       const double *wmask, const float *omega, int k, const int64_t *cand,
                       int64_t cap, double *vals, double frac, TauState *st, unsigned long long *parts,
                       double *tau_out, const double *pstats, const unsigned int *ccnt, const FusedLists *fl,
-                      unsigned int *bins, const double *max_margin) {
+                      unsigned int *bins, const double *max_margin, bool retry) {
     // eight entries per wave and round
     int64_t blocks = (int64_t)lc.num_cu * kExactWaves;
     if (blocks > (cap + 7) / 8) blocks = (cap + 7) / 8;
@@ -785,8 +785,9 @@ hipError_t tau_finish(const LaunchCtx &lc, const float *rgb, int H, int W, int p
                        k, cand, st, cap, vals, pstats, ccnt, fl ? fl->coff : nullptr, fl ? fl->ccomp : nullptr, bins,
                        max_margin);
     unsigned long long *rk = parts + kTauParts;  // kRankMax (less, equal) pairs
-    // (binned values, and short calls, which have few candidates, go without)
-    const bool ranked = !bins && cap > ((int64_t)1 << 20);
+    // (binned values, short calls, which have few candidates, and a retry, which
+    // has more of them than are ranked, go without)
+    const bool ranked = !bins && (int64_t)H * W * k > ((int64_t)1 << 20) && !retry;
     if (ranked)
         hipLaunchKernelGGL(k_tau_rank, dim3((unsigned)lc.num_cu * 4), dim3(64), 0, lc.stream, vals, cap, st, rk);
     hipLaunchKernelGGL(k_tau_select, dim3(1), dim3(1024), 0, lc.stream, vals, cap, frac, st, parts, rk, ranked,
