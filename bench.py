@@ -622,13 +622,18 @@ def main():
     ctx.profile_enable(True)
     for _ in range(stage_steps):
         step()
+    # (the coefficients' launch is the stream's)
     stage_names = ["analyze", "tau_select", "cosupport", "tau_exact", "cosupport_fix", "thresholds", "samples",
-                   "edt", "stream", "texture_rep", "coef", "parzen", "parzen_fixup", "texture", "normalise"]
+                   "edt", "stream", "texture_rep", "parzen", "parzen_fixup", "texture", "normalise"]
     stages = {}
     for nm in stage_names:
         ms_, n_ = ctx.profile_read(nm)
         if n_:
             stages[nm] = ms_ / stage_steps
+    # the analysis alone (up to 9 x 9 the step's launch also decides the masks)
+    ctx.profile_enable(True)
+    for _ in range(stage_steps):
+        ctx.analyze_patches(rgb, w.p, w.mask_sigma, om, precision=w.precision, out=alpha)
     analyze_ms, analyze_n = ctx.profile_read("analyze")
     ctx.profile_enable(False)
 

@@ -303,7 +303,9 @@ int cs_last_loglik_stats(cs_ctx *ctx, cs_loglik_stats *stats);
 /* Kernel timing on the context stream (HIP events around each launch of the
  * named kernel).  cs_profile_enable(ctx, 1) starts recording and clears totals;
  * cs_profile_read synchronises and returns the summed milliseconds and launch
- * count of kernel `name` ("parzen", "analyze", "edt", ...). */
+ * count of kernel `name` ("parzen", "analyze", "edt", ...).  A launch that does
+ * the work of two names ("kmeans" and "kmedians", "mlp_wgrad" and "mlp_adam",
+ * "stream" and "coef", "analyze" and "analyze_bf16") counts in full under both. */
 int cs_profile_enable(cs_ctx *ctx, int on);
 /* Record only the kernel `name` (NULL: every kernel); each recorded launch
  * adds two events to the stream. */

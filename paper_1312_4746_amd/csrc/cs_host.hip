@@ -67,7 +67,7 @@ struct cs_ctx {
     int prof_period = 1;                       // record one launch in prof_period per name
     std::map<std::string, int64_t> prof_seen;  // launches of each name seen while recording
     struct Span {
-        std::string name;
+        const char *name, *also;  // also: the other name of a launch that does the work of two, or null
         hipEvent_t a, b;
     };
     std::vector<Span> spans;
@@ -212,10 +212,10 @@ int ensure_cand(cs_ctx *ctx, size_t bytes) {
 // HIP events around one launch when timing is on.
 struct Timed {
     cs_ctx *c;
-    const char *name;
+    const char *name, *also;
     hipEvent_t a = nullptr, b = nullptr;
-    Timed(cs_ctx *ctx, const char *nm) : c(ctx), name(nm) {
-        if (!c->prof || (!c->only.empty() && c->only != nm)) return;
+    Timed(cs_ctx *ctx, const char *nm, const char *nm2 = nullptr) : c(ctx), name(nm), also(nm2) {
+        if (!c->prof || (!c->only.empty() && c->only != nm && (!nm2 || c->only != nm2))) return;
         if (c->prof_period > 1 && c->prof_seen[nm]++ % c->prof_period != 0) return;
         a = take();
         b = take();
@@ -234,7 +234,7 @@ struct Timed {
     ~Timed() {
         if (!c->prof || !a || !b) return;
         hipEventRecord(b, c->stream);
-        c->spans.push_back({name, a, b});
+        c->spans.push_back({name, also, a, b});
     }
 };
 
@@ -785,37 +785,36 @@ int cs_cosupport_median(cs_ctx *ctx, const float *rgb, int H, int W, int p, doub
         a.k = k;
         a.wmask = ctx->wmask;
         a.omega = omega;
+        AnalyzeArgs f = a;
+        f.alpha = fused16 ? alpha : a32;
+        f.pstats = pst;
+        f.tau_st = st;
+        f.tau_hist3 = hist3;
+        f.tau_hist_words = hist_words;
+        f.tau_margins = marg;
+        f.tau_max_margin = mmax;
+        f.tau_coef = median_coef(p);
+        f.tau_rank0 = (unsigned long long)((count - 1) / 2);
+        if (fused) {
+            Timed t(ctx, "tau_select");
+            HIP_TRY(median_patch_sample(lc, f, frac, hist3 + 3 * kHistBins));
+            f.masks = masks;
+            f.sel_st = st;
+            f.tau_st = nullptr;  // set up already
+            f.sel_frac = frac;
+            f.sel_blist = (uint64_t *)vals;
+            f.sel_dlist = (uint64_t *)didx;
+            f.sel_bcnt = ccnt;
+            f.sel_dcnt = dcnt;
+            f.sel_parts = parts;
+        }
         {
-            AnalyzeArgs f = a;
-            f.alpha = fused16 ? alpha : a32;
-            f.pstats = pst;
-            f.tau_st = st;
-            f.tau_hist3 = hist3;
-            f.tau_hist_words = hist_words;
-            f.tau_margins = marg;
-            f.tau_max_margin = mmax;
-            f.tau_coef = median_coef(p);
-            f.tau_rank0 = (unsigned long long)((count - 1) / 2);
-            Timed t(ctx, "analyze");
-            if (fused) {
-                f.masks = masks;
-                f.sel_frac = frac;
-                f.sel_blist = (uint64_t *)vals;
-                f.sel_dlist = (uint64_t *)didx;
-                f.sel_bcnt = ccnt;
-                f.sel_dcnt = dcnt;
-                f.sel_parts = parts;
-                HIP_TRY(median_bracket_analyze(lc, f, fused16 ? CS_BF16 : CS_FP32, hist3 + 3 * kHistBins, cand));
-                if (fused16) {
-                    // the FP32 vectors, for the digits where the bracket missed
-                    AnalyzeArgs b = a;
-                    b.alpha = a32;
-                    b.skip = st;
-                    HIP_TRY(launch_analyze(lc, b, CS_FP32));
-                }
-            } else {
-                HIP_TRY(launch_analyze(lc, f, CS_FP32));
-            }
+            Timed t(ctx, "analyze", fused16 ? "analyze_bf16" : nullptr);
+            HIP_TRY(launch_analyze(lc, f, fused16 ? CS_BF16 : CS_FP32));
+        }
+        if (fused) {
+            Timed t(ctx, "cosupport");
+            HIP_TRY(median_bracket_list(lc, mmax, st, (uint64_t *)vals, cand, ccnt, parts, hist3 + 3 * kHistBins));
         }
         if (bracket && !fused) {
             Timed t(ctx, "cosupport");
@@ -824,6 +823,13 @@ int cs_cosupport_median(cs_ctx *ctx, const float *rgb, int H, int W, int p, doub
         }
         {
             Timed t(ctx, "tau_select");
+            if (fused16) {
+                // the FP32 vectors, for the digits where the bracket missed
+                AnalyzeArgs b = a;
+                b.alpha = a32;
+                b.skip = st;
+                HIP_TRY(launch_analyze(lc, b, CS_FP32));
+            }
             HIP_TRY(tau_digits_folded(lc, a32, count, hist3, st));
         }
         {
@@ -1103,7 +1109,7 @@ static int label_loglik(cs_ctx *ctx, const float *rgb, int H, int W, const uint6
     pa.ntiles_real = (int)ntiles;
     pa.ntiles_pad = (int)ntiles_pad;
     if (fast) {
-        Timed t(ctx, "stream");
+        Timed t(ctx, "stream", "coef");
         const float cscale = (float)std::sqrt(1.4426950408889634 / (2.0 * prm->sigma_c * prm->sigma_c));
         PrepArgs pr{};
         pr.recs = recs;
@@ -1299,9 +1305,12 @@ int cs_profile_read(cs_ctx *ctx, const char *name, double *total_ms, int64_t *la
     for (auto &s : ctx->spans) {
         float ms = 0.f;
         HIP_TRY(hipEventElapsedTime(&ms, s.a, s.b));
-        auto &t = ctx->totals[s.name];
-        t.first += ms;
-        t.second += 1;
+        for (const char *nm : {s.name, s.also})
+            if (nm) {
+                auto &t = ctx->totals[nm];
+                t.first += ms;
+                t.second += 1;
+            }
         ctx->pool.push_back(s.a);
         ctx->pool.push_back(s.b);
     }
@@ -1532,7 +1541,7 @@ int cs_mlp_grad(cs_ctx *ctx, cs_mlp *net, const float *x, const float *ell, int6
     if (rc) return rc;
     a.grad_out = grad;
     a.loss_out = loss;
-    Timed tm(ctx, "mlp_adam");
+    Timed tm(ctx, "mlp_adam", "mlp_wgrad");
     HIP_TRY(launch_mlp_grad_adam(lc_of(ctx), a));
     return CS_OK;
 }
@@ -1554,7 +1563,7 @@ int cs_mlp_train(cs_ctx *ctx, cs_mlp *net, const float *x, const float *ell, int
         a.bc1 = (float)(1.0 - std::pow(0.9, (double)net->t));
         a.bc2 = (float)(1.0 - std::pow(0.999, (double)net->t));
         a.loss_out = loss_trace ? loss_trace + s : nullptr;
-        Timed tm(ctx, "mlp_adam");
+        Timed tm(ctx, "mlp_adam", "mlp_wgrad");
         HIP_TRY(launch_mlp_grad_adam(lc_of(ctx), a));
     }
     return CS_OK;
@@ -1909,7 +1918,7 @@ int cs_unsupervised_loglik(cs_ctx *ctx, const float *rgb, int H, int W, const ui
     const LaunchCtx lc = lc_of(ctx);
     HIP_TRY(launch_unsup_init(lc, a, init));
     {
-        Timed t(ctx, "cluster");
+        Timed t(ctx, "kmeans", "kmedians");
         for (int it = 0; it < prm->iterations; ++it) HIP_TRY(launch_unsup_step(lc, a, true));
         HIP_TRY(launch_unsup_step(lc, a, false));
     }

@@ -276,11 +276,9 @@ hipError_t median_bracket(const LaunchCtx &lc, const float *alpha, int64_t N, in
 // Its steps after the pass over the entries.
 hipError_t median_bracket_list(const LaunchCtx &lc, const double *max_margin, TauState *st, const uint64_t *blist,
                                int64_t *cand, unsigned int *ccnt, unsigned long long *parts, unsigned int *br_hist);
-// The analysis (p <= kPatchSelMax) with that pass in it: the
-// set-up a.tau_*, a bracket from sampled pixels, the vectors, masks and lists
-// (a.sel_*), and the steps after the pass.
-hipError_t median_bracket_analyze(const LaunchCtx &lc, const AnalyzeArgs &a, int precision, unsigned int *br_hist,
-                                  int64_t *cand);
+// For an analysis that makes that pass itself (p <= kPatchSelMax, a.sel_*; then
+// median_bracket_list): the set-up a.tau_* and a bracket from sampled pixels.
+hipError_t median_patch_sample(const LaunchCtx &lc, const AnalyzeArgs &a, double frac, unsigned int *br_hist);
 // After the exact tau: the listed entries, decided in one launch (the rounded
 // value where it is clear of tau by the row margin, else in FP64).
 hipError_t median_mask_finish(const LaunchCtx &lc, const float *alpha, const float *rgb, int H, int W, int p,

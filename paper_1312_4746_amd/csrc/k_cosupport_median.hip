@@ -607,19 +607,11 @@ hipError_t median_bracket_list(const LaunchCtx &lc, const double *max_margin, Ta
     return hipGetLastError();
 }
 
-hipError_t median_bracket_analyze(const LaunchCtx &lc, const AnalyzeArgs &a, int precision, unsigned int *br_hist,
-                                  int64_t *cand) {
+hipError_t median_patch_sample(const LaunchCtx &lc, const AnalyzeArgs &a, double frac, unsigned int *br_hist) {
     hipLaunchKernelGGL(k_select_setup, dim3(1), dim3(1024), 0, lc.stream, a);
     hipLaunchKernelGGL(k_patch_sample, dim3(kPatchSampleBlocks + 1), dim3(1024), 0, lc.stream, a, br_hist);
-    hipLaunchKernelGGL(k_bracket_pick, dim3(1), dim3(1024), 0, lc.stream, br_hist, a.tau_max_margin,
-                       a.sel_frac, a.tau_st);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    AnalyzeArgs b = a;
-    b.sel_st = a.tau_st;
-    b.tau_st = nullptr;
-    if ((e = launch_analyze(lc, b, precision)) != hipSuccess) return e;
-    return median_bracket_list(lc, a.tau_max_margin, a.tau_st, a.sel_blist, cand, a.sel_bcnt, a.sel_parts, br_hist);
+    hipLaunchKernelGGL(k_bracket_pick, dim3(1), dim3(1024), 0, lc.stream, br_hist, a.tau_max_margin, frac, a.tau_st);
+    return hipGetLastError();
 }
 
 int64_t median_gather_waves(int64_t N) {
