@@ -344,13 +344,19 @@ def mean_dice(labels, truth, L: int) -> float:
     return float(np.mean(d))
 
 
+# Operations of an iteration per pixel and label: dual step 4, disc 8 (squared
+# norm, root, quotient, two scalings, test), divergence 3, primal step 3, one
+# round of the simplex 3, over-relaxation 2.
+SEG_OPS = 23
+
+
 def segment_line(args, config: int = 1) -> dict:
     """Segmentation by convex relaxation (Sec. 4) on the exact data term of
     workload `config`: the primal-dual iteration's time per iteration against
-    the HBM roofline of a state that makes a trip per iteration (per pixel and
-    label: read u_bar, xi_x, xi_y, u, f; write xi_x, xi_y, u, u_bar: 36 B in
-    FP32; the on-chip forms make fewer trips, so the rate can pass the peak),
-    the energies and the relaxation gap, Dice against the synthetic regions, and the FP64 oracle's
+    the nearer of two peaks, FP32 vector operations (SEG_OPS per pixel and
+    label) and HBM (one trip of the state per launch, which runs several
+    iterations or all; per pixel and label: read u_bar, xi_x, xi_y, u, f; write
+    xi_x, xi_y, u, u_bar: 36 B in FP32), the energies and the relaxation gap, Dice against the synthetic regions, and the FP64 oracle's
     iteration on the host."""
     import numpy as np
     import torch
@@ -375,11 +381,20 @@ def segment_line(args, config: int = 1) -> dict:
     lab, _, st = ctx.segment(rgb, ll, sp)
     torch.cuda.synchronize()
     t_solve = time.perf_counter() - t0
-    it_ms, _ = ctx.profile_read("pd_iter")  # every launch of the iterations (one launch runs several)
+    it_ms, it_n = ctx.profile_read("pd_iter")  # every launch of the iterations
     ctx.profile_enable(False)
     ctx.profile_only(None)
     avg_it = it_ms / 1e3 / max(args.seg_iters, 1)
-    bytes_it = w.N * w.L * 36 + w.N * 4
+    # one trip of the state per launch; the launches also tell the form that ran
+    # (the tile form runs at most 8 iterations a launch)
+    bytes_it = (w.N * w.L * 36 + w.N * 4) * it_n / max(args.seg_iters, 1)
+    kernel = None if args.seg_iters <= 8 else "k_pd_resident" if it_n == 1 else "k_pd_tile"
+    alu_frac = w.N * w.L * SEG_OPS / avg_it / PEAK_FP32_VECTOR
+    hbm_frac = bytes_it / avg_it / PEAK_HBM
+    bound = ({"bound": "alu", "achieved": alu_frac * PEAK_FP32_VECTOR / 1e12, "peak": PEAK_FP32_VECTOR / 1e12,
+              "unit": "TFLOP/s", "frac": alu_frac} if alu_frac >= hbm_frac else
+             {"bound": "hbm", "achieved": hbm_frac * PEAK_HBM / 1e9, "peak": PEAK_HBM / 1e9, "unit": "GB/s",
+              "frac": hbm_frac})
     lab_np = lab.cpu().numpy().reshape(w.H, w.W)
     ll_np = ll.cpu().numpy()
     dice0 = mean_dice(np.argmax(ll_np, 1).reshape(w.H, w.W), w.region, w.L)
@@ -404,9 +419,9 @@ def segment_line(args, config: int = 1) -> dict:
         "workload": w.name, "H": w.H, "W": w.W, "labels": w.L,
         "iterations": args.seg_iters, "lambda": args.seg_lambda, "dtype": "f32",
         "ms_per_iteration": avg_it * 1e3, "solve_ms": t_solve * 1e3,
-        "roofline": {"bound": "hbm", "achieved": bytes_it / avg_it / 1e9, "peak": PEAK_HBM / 1e9, "unit": "GB/s",
-                     "frac": bytes_it / avg_it / PEAK_HBM, "traffic": None, "kernel": "k_pd_resident" if w.N <= 480 * 480 else "k_pd_tile",
-                     "bytes_per_iteration": bytes_it},
+        "roofline": {**bound, "traffic": None, "kernel": kernel, "launches": it_n, "ops_per_pixel_label": SEG_OPS,
+                     "bytes_per_iteration": bytes_it, "alu_frac": alu_frac, "hbm_frac": hbm_frac,
+                     "note": "the one-launch form waits for its neighbours' borders once an iteration"},
         "energies": st,
         "relaxation_gap": (st["binary"] - st["dual"]) / abs(st["dual"]),
         "dice_vs_regions": {"pointwise_argmax": dice0, "segmentation": dice1},
