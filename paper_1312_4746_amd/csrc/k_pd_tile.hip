@@ -46,9 +46,12 @@ __device__ __forceinline__ float lane_left(float v) {  // lane i gets lane i - 1
 // Square root and quotient correctly rounded, for operands whose intermediate
 // steps neither overflow nor fall below the normal range (the guard below):
 // the root by two Newton steps on the reciprocal root with fused remainders,
-// the quotient by the same on the reciprocal.  Equal to sqrtf and to the
-// division bit for bit in that range, at 9 and 8 instructions instead of
-// about 40 for the two with scaling and special cases.
+// the quotient by the same on the reciprocal (P. Markstein, IBM J. Res. Dev. 34,
+// 1990).  The root is, from any estimate within a unit; the quotient by his
+// theorem, the reciprocal after its step being correctly rounded for every
+// significand (run on gfx950 over 2^-60 to 2^62).  So equal to sqrtf and to the
+// division bit for bit in that range, at 9 and 8 instructions instead of about
+// 40 for the two with scaling and special cases.
 __device__ __forceinline__ float sqrt_rn(float x) {
     const float r0 = __builtin_amdgcn_rsqf(x);
     float s = x * r0, h = 0.5f * r0;
