@@ -311,6 +311,9 @@ hipError_t tau_gather(const LaunchCtx &lc, const float *alpha, int64_t count,
     return hipGetLastError();
 }
 
+constexpr int kSelfRank = 256;  // candidates ranked by the selection itself
+constexpr int kPairRank = 128;  // members of a bin ranked by pairs
+
 // Bins of the exact values of the candidates, which lie within the largest
 // margin of the candidate window: monotone in the value (one bin where the
 // window is not finite).  With them the one-workgroup selection reads the values
@@ -334,28 +337,30 @@ struct ExactBins {
 // bit pattern of the oracle's evaluation).  Persistent waves read the
 // candidate count from the device state (no host round trip); counts beyond
 // the capacity are left to the host's retry.
-__global__ __launch_bounds__(64) void k_tau_recompute(const float *rgb, int H, int W, int p,
-                                                       const double *wmask, const float *omega,
-                                                       int k, const int64_t *cand, const TauState *st,
-                                                       int64_t cap, double *vals, const double *pstats,
-                                                       const unsigned int *ccnt, const unsigned long long *coff,
-                                                       const int64_t *ccomp, unsigned int *bins,
-                                                       const double *max_margin) {
+// The values are counted in the workgroup's bins first: candidates of one value
+// (a flat image, a repeated pattern) would meet in one global counter, 12 ns each.
+constexpr int kRecomputeWaves = 4;  // per workgroup
+__global__ __launch_bounds__(64 * kRecomputeWaves) void k_tau_recompute(
+    const float *rgb, int H, int W, int p, const double *wmask, const float *omega, int k, const int64_t *cand,
+    const TauState *st, int64_t cap, double *vals, const double *pstats, const unsigned int *ccnt,
+    const unsigned long long *coff, const int64_t *ccomp, unsigned int *bins, const double *max_margin) {
     constexpr int G = 64 / kExactLanes;
-    extern __shared__ double s_exact[];  // exact_lds(n)
-    const int n = p * p, grp = threadIdx.x / kExactLanes;
-    double *const buf = s_exact + grp * (n + 1);
-    const bool lead = (threadIdx.x & (kExactLanes - 1)) == 0;
+    extern __shared__ double s_exact[];  // exact_lds(n) per wave, then the bins
+    const int n = p * p, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, grp = lane / kExactLanes;
+    double *const buf = s_exact + (wave * G + grp) * (n + 1);
+    unsigned int *const h = reinterpret_cast<unsigned int *>(s_exact + kRecomputeWaves * G * (n + 1));
+    const bool lead = (lane & (kExactLanes - 1)) == 0;
     auto entry = [&](int64_t e, bool live) {
         const int64_t pix = e / k;
         const int j = (int)(e - pix * k);
         return fabs(exact_entry(rgb, H, W, p, wmask, omega + (int64_t)j * n, pix, pstats, buf, live));
     };
+    const int64_t gw = (int64_t)blockIdx.x * kRecomputeWaves + wave, nwaves = (int64_t)gridDim.x * kRecomputeWaves;
     if (ccnt && (int64_t)st->ncand > kListCap) {
         // per-wave regions of the fused gather (a list too long to compact):
         // the wave walks a region, its values written at the region's offset
         const int64_t nw = (int64_t)st->rg_waves, region = (int64_t)st->rg_size;
-        for (int64_t r = blockIdx.x; r < nw; r += gridDim.x) {
+        for (int64_t r = gw; r < nw; r += nwaves) {
             const unsigned int cnt = ccnt[r];
             const int64_t *src = cand + r * region;
             double *dst = vals + coff[r];
@@ -369,17 +374,26 @@ __global__ __launch_bounds__(64) void k_tau_recompute(const float *rgb, int H, i
     }
     // compact list: the fused gather's in ccomp (see k_list_compact), else cand
     const int64_t *lst = ccnt ? ccomp : cand;
-    const ExactBins eb(st, max_margin);
     const unsigned long long nc = st->ncand;
     const int64_t ncand = (int64_t)nc < cap ? (int64_t)nc : cap;
-    for (int64_t c0 = (int64_t)blockIdx.x * G; c0 < ncand; c0 += (int64_t)gridDim.x * G) {
+    const ExactBins eb(st, max_margin);
+    const bool binned = bins && ncand > kSelfRank;  // (fewer are ranked without)
+    if (binned) {
+        for (int i = threadIdx.x; i < kHistBins; i += 64 * kRecomputeWaves) h[i] = 0u;
+        __syncthreads();
+    }
+    for (int64_t c0 = gw * G; c0 < ncand; c0 += nwaves * G) {
         const bool live = c0 + grp < ncand;
         const double v = entry(lst[live ? c0 + grp : 0], live);
         if (live && lead) {
             vals[c0 + grp] = v;
-            if (bins) atomicAdd(&bins[eb.of(v)], 1u);
+            if (binned) atomicAdd(&h[eb.of(v)], 1u);
         }
     }
+    if (!binned) return;
+    __syncthreads();
+    for (int i = threadIdx.x; i < kHistBins; i += 64 * kRecomputeWaves)
+        if (h[i]) atomicAdd(&bins[i], h[i]);
 }
 
 // Offsets of the fused gather's per-wave regions in the compact lists
@@ -493,7 +507,6 @@ __global__ __launch_bounds__(64) void k_tau_rank(const double *vals, int64_t cap
 // differ are common to all candidates and skipped; the remaining digits are
 // selected 8 bits at a time with an LDS histogram and a one-wave scan.
 constexpr int kSelLds = 4096;  // candidates kept in LDS for the last digits
-constexpr int kSelfRank = 256;  // candidates ranked by the selection itself
 __global__ __launch_bounds__(1024) void k_tau_select(const double *vals, int64_t cap, double frac,
                                                       TauState *st, const unsigned long long *parts,
                                                       const unsigned long long *rk, bool ranked, double *tau_out,
@@ -581,7 +594,7 @@ __global__ __launch_bounds__(1024) void k_tau_select(const double *vals, int64_t
             s_left = second ? b1 : b0;
         }
         __syncthreads();
-        if (s_left <= 1024u) {
+        if (s_left <= (unsigned int)kSelLds) {
             const ExactBins eb(st, max_margin);
             const unsigned int bin = (unsigned int)s_prefix;
             for (int64_t c0 = 0; c0 < ncand; c0 += 8 * 1024) {
@@ -598,21 +611,79 @@ __global__ __launch_bounds__(1024) void k_tau_select(const double *vals, int64_t
             }
             __syncthreads();
             const int nk = (int)s_nkeys;
-            if (tid < nk) {
-                const unsigned long long key = s_keys[tid], rr = s_rank;
-                unsigned int less = 0, equal = 0;
-                for (int q = 0; q < nk; ++q) {
-                    less += s_keys[q] < key ? 1u : 0u;
-                    equal += s_keys[q] == key ? 1u : 0u;
+            auto result = [&](unsigned long long key) {
+                const double med = __longlong_as_double((long long)key);
+                st->median = med;
+                st->tau = frac * med;
+                if (tau_out) *tau_out = frac * med;
+            };
+            if (nk <= kPairRank) {
+                if (tid < nk) {
+                    const unsigned long long key = s_keys[tid], rr = s_rank;
+                    unsigned int less = 0, equal = 0;
+                    for (int q = 0; q < nk; ++q) {
+                        less += s_keys[q] < key ? 1u : 0u;
+                        equal += s_keys[q] == key ? 1u : 0u;
+                    }
+                    if (rr >= less && rr < (unsigned long long)less + equal) result(key);
                 }
-                if (rr >= less && rr < (unsigned long long)less + equal) {
-                    const double med = __longlong_as_double((long long)key);
-                    st->median = med;
-                    st->tau = frac * med;
-                    if (tau_out) *tau_out = frac * med;
+                return;
+            }
+            // more, as where values are tied (1024 of one value: 40 us by pairs, 5 us
+            // by pivots): by pivots, the first value in play of a lane and wave that
+            // change from pass to pass
+            static_assert(kSelLds == 4 * 1024, "four members per thread");
+            __shared__ unsigned long long s_piv[16], s_cnt[16];
+            __shared__ bool s_has[16];
+            unsigned long long key[4], lo = 0, hi = ~0ull, rr = s_rank;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) key[u] = s_keys[min(tid + 1024 * u, nk - 1)];
+            for (int pass = 0; pass < 64; ++pass) {
+                unsigned long long mine = 0;
+                bool has = false;
+#pragma unroll
+                for (int u = 3; u >= 0; --u)
+                    if (tid + 1024 * u < nk && key[u] >= lo && key[u] <= hi) {
+                        mine = key[u];
+                        has = true;
+                    }
+                const unsigned long long m = __ballot(has);
+                const int turn = (pass * 37) & 63;
+                const unsigned long long after = m >> turn;
+                const int from = after ? turn + __builtin_ctzll(after) : m ? __builtin_ctzll(m) : 0;
+                const unsigned long long piv = __shfl(mine, from);
+                if (lane == 0) {
+                    s_piv[wave] = piv;
+                    s_has[wave] = m != 0;
+                }
+                __syncthreads();
+                int w = (pass * 7) & 15;
+                for (int i = 0; i < 16 && !s_has[w]; ++i) w = (w + 1) & 15;
+                const unsigned long long pivot = s_piv[w];
+                unsigned int less = 0, equal = 0;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const bool in = tid + 1024 * u < nk && key[u] >= lo && key[u] <= hi;
+                    less += (unsigned int)__popcll(__ballot(in && key[u] < pivot));
+                    equal += (unsigned int)__popcll(__ballot(in && key[u] == pivot));
+                }
+                if (lane == 0) s_cnt[wave] = (unsigned long long)equal << 32 | less;
+                __syncthreads();
+                unsigned long long sum = 0;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) sum += s_cnt[i];
+                const unsigned long long nl = sum & 0xFFFFFFFFull, ne = sum >> 32;
+                if (rr < nl) {
+                    hi = pivot - 1;
+                } else if (rr < nl + ne) {
+                    if (tid == 0) result(pivot);
+                    return;
+                } else {
+                    rr -= nl + ne;
+                    lo = pivot + 1;
                 }
             }
-            return;
+            __syncthreads();  // (not found: by digits below, which write what is read here)
         }
     }
     if (ranked && ncand <= kRankMax) {
@@ -778,11 +849,13 @@ hipError_t tau_finish(const LaunchCtx &lc, const float *rgb, int H, int W, int p
                       double *tau_out, const double *pstats, const unsigned int *ccnt, const FusedLists *fl,
                       unsigned int *bins, const double *max_margin, bool retry) {
     // eight entries per wave and round
-    int64_t blocks = (int64_t)lc.num_cu * kExactWaves;
-    if (blocks > (cap + 7) / 8) blocks = (cap + 7) / 8;
+    constexpr int per = kRecomputeWaves * 64 / kExactLanes;
+    int64_t blocks = (int64_t)lc.num_cu * kExactWaves / kRecomputeWaves;
+    if (blocks > (cap + per - 1) / per) blocks = (cap + per - 1) / per;
     if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(k_tau_recompute, dim3((unsigned)blocks), dim3(64), exact_lds(n), lc.stream, rgb, H, W, p, wmask, omega,
-                       k, cand, st, cap, vals, pstats, ccnt, fl ? fl->coff : nullptr, fl ? fl->ccomp : nullptr, bins,
+    const size_t lds = kRecomputeWaves * exact_lds(n) + (bins ? sizeof(unsigned int) * kHistBins : 0);
+    hipLaunchKernelGGL(k_tau_recompute, dim3((unsigned)blocks), dim3(64 * kRecomputeWaves), lds, lc.stream, rgb, H, W, p,
+                       wmask, omega, k, cand, st, cap, vals, pstats, ccnt, fl ? fl->coff : nullptr, fl ? fl->ccomp : nullptr, bins,
                        max_margin);
     unsigned long long *rk = parts + kTauParts;  // kRankMax (less, equal) pairs
     // (binned values, short calls, which have few candidates, and a retry, which
