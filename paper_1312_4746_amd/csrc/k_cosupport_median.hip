@@ -500,6 +500,8 @@ __global__ __launch_bounds__(64) void k_median_mask_finish(const float *alpha, c
     const double tau = st->tau;
     const bool packed = st->br_ok != 0;  // the list carries the keys
     const uint32_t dbase = st->br_dbase;
+    ExactRun run;
+    int64_t zero_pix = -1;  // the wave's
     auto set = [&](int64_t pix, int j) {
         atomicOr(reinterpret_cast<unsigned long long *>(masks + pix * W64 + (j >> 6)), 1ull << (j & 63));
     };
@@ -525,6 +527,10 @@ __global__ __launch_bounds__(64) void k_median_mask_finish(const float *alpha, c
                 set(pix, j);
             else
                 near = !(a > tau + m);  // within the margin, or NaN
+            if (near && pix == zero_pix) {
+                if (0.0 <= tau) set(pix, j);
+                near = false;
+            }
         }
         const unsigned long long nm = __ballot(near);
         if (!nm) return;
@@ -535,10 +541,11 @@ __global__ __launch_bounds__(64) void k_median_mask_finish(const float *alpha, c
             const bool on = i0 + grp < nn;
             const int64_t f = s_near[on ? i0 + grp : 0], pix = f / k;
             const int j = (int)(f - pix * k);
-            const double v = exact_entry(rgb, H, W, p, wmask, omega + (int64_t)j * p * p, pix, pstats,
-                                         s_exact + grp * (p * p + 1), on);
+            const double v = run.entry(rgb, H, W, p, wmask, omega + (int64_t)j * p * p, pix, pstats,
+                                       s_exact + grp * (p * p + 1), on);
             if (on && (lane & (kExactLanes - 1)) == 0 && fabs(v) <= tau) set(pix, j);
         }
+        zero_pix = run.wave_zero();
         __builtin_amdgcn_wave_barrier();
     };
     const int64_t nd = (int64_t)st->n_d;

@@ -350,10 +350,11 @@ __global__ __launch_bounds__(64 * kRecomputeWaves) void k_tau_recompute(
     double *const buf = s_exact + (wave * G + grp) * (n + 1);
     unsigned int *const h = reinterpret_cast<unsigned int *>(s_exact + kRecomputeWaves * G * (n + 1));
     const bool lead = (lane & (kExactLanes - 1)) == 0;
+    ExactRun run;
     auto entry = [&](int64_t e, bool live) {
         const int64_t pix = e / k;
         const int j = (int)(e - pix * k);
-        return fabs(exact_entry(rgb, H, W, p, wmask, omega + (int64_t)j * n, pix, pstats, buf, live));
+        return fabs(run.entry(rgb, H, W, p, wmask, omega + (int64_t)j * n, pix, pstats, buf, live));
     };
     const int64_t gw = (int64_t)blockIdx.x * kRecomputeWaves + wave, nwaves = (int64_t)gridDim.x * kRecomputeWaves;
     if (ccnt && (int64_t)st->ncand > kListCap) {
@@ -364,10 +365,19 @@ __global__ __launch_bounds__(64 * kRecomputeWaves) void k_tau_recompute(
             const unsigned int cnt = ccnt[r];
             const int64_t *src = cand + r * region;
             double *dst = vals + coff[r];
-            for (unsigned int q0 = 0; q0 < cnt; q0 += G) {
+            for (unsigned int q0 = 0; q0 < cnt;) {
+                // (zero patches are passed over 64 entries at a time)
+                const int64_t zero_pix = run.wave_zero();
+                const bool z = q0 + lane < cnt && zero_pix >= 0 && src[q0 + lane] / k == zero_pix;
+                const unsigned long long rest = ~__ballot(z);
+                const unsigned int nz = rest ? __builtin_ctzll(rest) : 64u;
+                if (lane < (int)nz) dst[q0 + lane] = 0.0;
+                q0 += nz;
+                if (nz == 64u || q0 >= cnt) continue;
                 const bool live = q0 + grp < cnt;
                 const double v = entry(src[live ? q0 + grp : 0], live);
                 if (live && lead) dst[q0 + grp] = v;
+                q0 += G;
             }
         }
         return;
