@@ -218,7 +218,10 @@ void k_patch(AnalyzeArgs a, int tiles_x, int ntiles) {
     constexpr bool kB16 = PREC == CS_BF16, kF32 = !kB16 || kSel;  // the selection runs on the FP32 vectors
     if (a.skip && a.skip->br_ok) return;
     __shared__ double gh2[2][T::halo];  // this tile's gray halo and the next one's
-    __shared__ double s_c1[hw], s_c2[hw];
+    // sequential statistics a row of the patch at a time, the mask in LDS (the
+    // other outputs have no registers for it)
+    constexpr bool kSeqRow = OUT == kPatchAlpha;
+    __shared__ double s_c1[hw], s_c2[hw], s_w[kSeqRow ? n : 1];
     __shared__ double s_mu[TP], s_ri[TP];  // mu and 1 / nu (0 for a zero patch)
     __shared__ __align__(16) float s[TP * ss];
     __shared__ char near_lds[OUT == kPatchMasks ? sizeof(PatchNear) : 1] __attribute__((aligned(16)));
@@ -351,6 +354,7 @@ void k_patch(AnalyzeArgs a, int tiles_x, int ntiles) {
         }
     };
     const uint32_t lane_off = (uint32_t)(4 * g * a.k + jl);
+    if (kSeqRow && tid < n) s_w[tid] = a.wmask[tid];
     int tile = blockIdx.x, par = 0;
     if (tile < ntiles) {
         request(tile);
@@ -397,13 +401,41 @@ void k_patch(AnalyzeArgs a, int tiles_x, int ntiles) {
             double mu = m / (double)n, nu2 = q - m * mu;
             // (a term below the normal range is off by 2^-1074, nothing to a q above 2^-900)
             if (tid < valid_px && !(nu2 > 1e-6 * q && q > 0x1p-900)) {
-                double sum = 0.0;
-                for (int t = 0; t < n; ++t) sum = sum + a.wmask[t] * gh[(t / P) * hw + tid + t % P];
-                mu = sum / (double)n;
-                nu2 = 0.0;
-                for (int t = 0; t < n; ++t) {
-                    const double z = a.wmask[t] * gh[(t / P) * hw + tid + t % P] - mu;
-                    nu2 = nu2 + z * z;
+                uint32_t any = 1;  // 0: a zero patch, told without its sums (black areas)
+                if (q == 0.0) {
+                    any = 0;
+#pragma unroll 4
+                    for (int t = 0; t < n; ++t) {
+                        const uint64_t b = __builtin_bit_cast(uint64_t, gh[(t / P) * hw + tid + t % P]);
+                        any |= (uint32_t)b | (uint32_t)(b >> 32);
+                    }
+                }
+                if (any == 0) {
+                    mu = nu2 = 0.0;
+                } else if constexpr (kSeqRow) {
+                    double sum = 0.0;
+#pragma unroll 1
+                    for (int u = 0; u < P; ++u)
+#pragma unroll
+                        for (int v = 0; v < P; ++v) sum = sum + s_w[u * P + v] * gh[u * hw + tid + v];
+                    mu = sum / (double)n;
+                    nu2 = 0.0;
+#pragma unroll 1
+                    for (int u = 0; u < P; ++u)
+#pragma unroll
+                        for (int v = 0; v < P; ++v) {
+                            const double z = s_w[u * P + v] * gh[u * hw + tid + v] - mu;
+                            nu2 = nu2 + z * z;
+                        }
+                } else {
+                    double sum = 0.0;
+                    for (int t = 0; t < n; ++t) sum = sum + a.wmask[t] * gh[(t / P) * hw + tid + t % P];
+                    mu = sum / (double)n;
+                    nu2 = 0.0;
+                    for (int t = 0; t < n; ++t) {
+                        const double z = a.wmask[t] * gh[(t / P) * hw + tid + t % P] - mu;
+                        nu2 = nu2 + z * z;
+                    }
                 }
             }
             const double ri = nu2 == 0.0 || tid >= valid_px ? 0.0 : 1.0 / sqrt(nu2);
