@@ -18,7 +18,9 @@
 //
 // The row pass is bound by its vector instructions.  1024 x 1024, 16 labels: 495 ->
 // 298 us with the runs (most of a walk passes far blocks of other labels' samples)
-// and a multiply-add per column scanned; 481 x 321: 33 -> 28 us.  The listed form
+// and a multiply-add per column scanned; 481 x 321: 33 -> 28 us.  Whole runs cost
+// short walks: with 50000 random samples the transform at 1024 x 1024 takes 172 us
+// block by block, 231 by runs; decided lane by lane, 191.  The listed form
 // waits for its loads: 2048 x 2048, 1171 -> 594 us with kWalkAhead minima and whole
 // blocks requested together (runs, or an upper bound from the minima before the
 // first scan, measured 624 and 657 us).  The column pass likewise: 220 -> 80 us
@@ -30,6 +32,7 @@ namespace cs {
 constexpr int kSegRows = 16;
 constexpr int kSegAhead = 8;  // segments of a column read together in the search for the nearest seed row
 constexpr int kWalk = 8;       // blocks of a row, on each side, that the row pass passes over together
+constexpr int kShort = 8 * 16;  // columns to each side up to which the row pass looks at every block
 constexpr int kWalkAhead = 4;  // ... and whose minima the listed pass reads together
 constexpr int kNoSeed = -1;
 constexpr int kRowBlk = 16;  // columns per block of the row pass
@@ -240,8 +243,20 @@ __global__ __launch_bounds__(1024) void k_edt_rows(const int32_t *colrow, int H,
         scan(cb);  // own block, every column
         // blocks outward on both sides; a block is scanned only if its
         // nearest column and smallest f could beat the best so far, and the
-        // walk stops once the nearest column of the next blocks is too far
-        for (int d0 = 1;; d0 += kWalk) {
+        // walk stops once the nearest column of the next blocks is too far.
+        // Where the best so far leaves every lane of the wave a run at most, as
+        // among many samples, it goes block by block, else run by run.
+        const bool more = !__all(best < kShort * kShort);
+        for (int d = 1; !more; ++d) {
+            const int bl = cb - d, br = cb + d;
+            const int gl = c - (bl * kRowBlk + kRowBlk - 1);  // distance to the left block's last column
+            const int gr = br * kRowBlk - c;                     // distance to the right block's first column
+            const bool lok = bl >= 0 && gl * gl < best, rok = br < nb && gr * gr < best;
+            if (!lok && !rok) break;
+            if (lok && gl * gl + fmin[bl] < best) scan(bl);
+            if (rok && gr * gr + fmin[br] < best) scan(br);
+        }
+        for (int d0 = 1; more; d0 += kWalk) {
             const int g0l = c - (cb - d0) * kRowBlk - (kRowBlk - 1), g0r = (cb + d0) * kRowBlk - c;
             const bool lok0 = cb - d0 >= 0 && g0l * g0l < best, rok0 = cb + d0 < nb && g0r * g0r < best;
             if (!lok0 && !rok0) break;
@@ -251,8 +266,7 @@ __global__ __launch_bounds__(1024) void k_edt_rows(const int32_t *colrow, int H,
             if (!lt && !rt) continue;
             for (int u = 0; u < kWalk; ++u) {
                 const int bl = cb - d0 - u, br = cb + d0 + u;
-                const int gl = c - (bl * kRowBlk + kRowBlk - 1);  // distance to the left block's last column
-                const int gr = br * kRowBlk - c;                     // distance to the right block's first column
+                const int gl = c - (bl * kRowBlk + kRowBlk - 1), gr = br * kRowBlk - c;
                 if (lt && bl >= 0 && gl * gl + fmin[bl] < best) scan(bl);
                 if (rt && br < nb && gr * gr + fmin[br] < best) scan(br);
             }
