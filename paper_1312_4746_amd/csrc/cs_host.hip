@@ -131,19 +131,23 @@ hipError_t scratch_address(int device, char **out) {
     return hipSuccess;
 }
 
-// Waits until a kernel of this call has written `tag` into host memory (what it
-// wrote there before, as the label counts, is then visible): spins, yields
+// Waits until a kernel of this call has written `tag`, or -tag, into host memory
+// (what it wrote there before, as the label counts, is then visible): spins, yields
 // after 2 ms, and after 5 s waits for the stream and looks once more (a failed
 // stream reports its error there).
 int wait_host_tag(cs_ctx *ctx, int32_t tag) {
     volatile int32_t *t = ctx->hcounts + kHostTag;
     const auto t0 = std::chrono::steady_clock::now();
-    for (int64_t it = 0; *t != tag; ++it) {
+    auto there = [&]() {
+        const int32_t v = *t;
+        return v == tag || v == -tag;
+    };
+    for (int64_t it = 0; !there(); ++it) {
         if ((it & 1023) == 1023) {
             const double sec = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
             if (sec > 5.0) {
                 HIP_TRY(hipStreamSynchronize(ctx->stream));
-                if (*t != tag) return fail(ctx, CS_ERR_HIP, "a result did not arrive from the device");
+                if (!there()) return fail(ctx, CS_ERR_HIP, "a result did not arrive from the device");
                 break;
             }
             if (sec > 2e-3) std::this_thread::yield();
@@ -1798,7 +1802,7 @@ int cs_segment(cs_ctx *ctx, const float *rgb, int H, int W, const float *loglik,
     if (rows) {
         a.arrive_ticks = (int64_t)(ctx->arrive_s * 1e3 * ctx->wall_khz);
         a.wait_words = ctx->wait_words;
-        a.host_out = ctx->hcounts_dev;
+        a.host_tag = ctx->hcounts_dev + kHostTag;
         a.tag = ctx->tag = ctx->tag >= 0x3FFFFFFF ? 1 : ctx->tag + 1;
         ctx->hcounts[kHostTag] = 0;
         hipError_t e = (hipError_t)ctx->launch_error;
@@ -1811,7 +1815,7 @@ int cs_segment(cs_ctx *ctx, const float *rgb, int H, int W, const float *loglik,
         if (launched) HIP_TRY(e);
         // (its tiles arrive within microseconds, or leave: the solve is not waited for)
         if (launched && (rc = wait_host_tag(ctx, a.tag))) return rc;
-        if (launched && ((volatile int32_t *)ctx->hcounts)[0] == 1) {
+        if (launched && ((volatile int32_t *)ctx->hcounts)[kHostTag] == a.tag) {
             buf = 1;
             it = prm->iterations;
             gave_up = pd_resident_ctl(a, rows) + kPdCtlGaveUp;

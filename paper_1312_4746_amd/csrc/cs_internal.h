@@ -475,12 +475,11 @@ struct PdArgs {
     // ... its control words (kPdCtl*, cleared by the launch), how long its tiles
     // wait for each other's arrival (ticks of the device's wall clock, below 0:
     // not at all), whether they wait for each other's words (tests do without),
-    // and where the host reads whether they have all arrived ({1 yes, 2 no},
-    // then tag at kHostTag)
+    // and where the host reads whether they have all arrived (tag: yes, -tag: no)
     unsigned int *ctl;
     int64_t arrive_ticks;
     bool wait_words;
-    volatile int32_t *host_out;
+    volatile int32_t *host_tag;
     int32_t tag;
     double *mpart;           // tile launches with a label cost: 2 x L x tiles sums of mu
 };
@@ -515,7 +514,7 @@ hipError_t launch_pd_tile(const LaunchCtx &lc, const PdArgs &a, int t, int cur, 
 // afterwards): the rows of its tiles, 0 where the image does not fit; its
 // exchange words; the launch.  Its tiles first wait for each other's arrival;
 // where that takes too long they all leave, nothing is written, and the other
-// form has to run (a.host_out tells).  A tile that waits in vain later on sets
+// form has to run (a.host_tag tells).  A tile that waits in vain later on sets
 // ctl[kPdCtlGaveUp].
 constexpr int kPdCtlDecided = 0, kPdCtlGaveUp = 1, kPdCtlWords = 2;
 int pd_resident_rows(const LaunchCtx &lc, const PdArgs &a);
