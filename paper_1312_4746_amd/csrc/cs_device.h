@@ -35,12 +35,12 @@ __device__ __forceinline__ double gray64(const float *rgb, int64_t N, int64_t id
 // The lanes load and divide in parallel (buf: the group's n + 1 doubles of
 // LDS), lane 0's sums are the serial part; with one lane per entry the chain of
 // loads took 20 us however few the entries (1024 x 1024, 11 x 11, k = 242: the
-// median's recompute 102 -> 44 us, the masks' last entries 77 -> 31 us).  mu = sum_t q_t / n and nu2 = sum_t
-// (q_t - mu)^2 come from stats[2 pix], stats[2 pix + 1] (the analysis kernel's
-// exact values, the same operations) when stats is non-null, else they are
-// computed here.  Every lane of the wave takes part (live: the group has an
-// entry); the group's lanes return the same value.  zero: the patch has nu2 = 0,
-// so every entry of the pixel is 0.
+// median's recompute 102 -> 35 us, the masks' last entries 77 -> 53 us).  mu =
+// sum_t q_t / n and nu2 = sum_t (q_t - mu)^2 come from stats[2 pix], stats[2 pix
+// + 1] (the analysis kernel's exact values, the same operations) when stats is
+// non-null, else they are computed here.  Every lane of the wave takes part
+// (live: the group has an entry); the group's lanes return the same value.  zero:
+// the patch has nu2 = 0, so every entry of the pixel is 0.
 constexpr int kExactLanes = 8;
 // LDS of a wave's groups, n + 1 doubles each (an odd stride of banks), and waves
 // per compute unit: sixteen fit up to 11 x 11 patches (with eight, 31000 entries of

@@ -384,11 +384,10 @@ __device__ __forceinline__ float wave_sum_f32(float v) {
 }
 
 // The first workgroups take one 16 x 16 tile of a weight gradient each (tiles of
-// one row block of the deltas on one XCD: workgroup w runs on XCD w mod 8):
-// wave c
-// the rows of chunk c (kc chunks, a chain of 16-row products in row order),
-// whose partial sums meet in LDS and are added in chunk order by the thread
-// that then updates the parameter.  The others add the per-tile bias
+// one row block of the deltas on one XCD: workgroup w runs on XCD w mod 8).  Wave
+// c takes the rows of chunk c (kc chunks, a chain of 16-row products in row
+// order); the waves' partial sums meet in LDS and are added in chunk order by the
+// thread that then updates the parameter.  The others add the per-tile bias
 // gradients, 16 units each, and the last one the loss.
 __global__ __launch_bounds__(1024) void k_mlp_grad_adam(MlpAdamArgs a, int wblocks) {
     __shared__ float s_part[16][256];

@@ -358,7 +358,8 @@ __device__ __forceinline__ void pixel_operands(const float *rgb, const uint64_t 
 // [0, b_coef) compute the coefficients (parzen_coef.h; the longest, so they
 // start first), the next b_stream build the sample stream, the next b_tiles
 // the pixel records, the rest the pixel operands (no dependence between the
-// four; 481 x 321: 37 us in two launches, 30 us in this one).
+// four; 481 x 321: 37 us in two launches, 36 us in this one with a label per
+// thread, 30 us with four, see launch_prep).
 template <int NW>
 __global__ __launch_bounds__(256) void k_prep(PrepArgs a, ParzenArgs pa, float4 *__restrict__ coef) {
     int b = blockIdx.x;
@@ -390,8 +391,9 @@ hipError_t launch_prep(const LaunchCtx &lc, PrepArgs a, const ParzenArgs &pa, fl
     a.b_stream = (int)((a.Mpad + 255) / 256);
     a.b_tiles = (int)((a.nslots + 255) / 256);
     // a thread takes four labels of its pixel, read once, where that still fills
-    // the chip (four workgroups per compute unit: 481 x 321, 10 labels 36 -> 30 us,
-    // 1024 x 1024, 16 labels 370 -> 337 us), else one (64 x 64: 6.4 us against 11.3)
+    // the chip (four workgroups per compute unit; in one launch, with one label and with
+    // four: 481 x 321, 10 labels 36 and 30 us, 1024 x 1024, 16 labels 370 and 337
+    // us), else one (64 x 64: 6.4 us, with four 11.3)
     a.coef_labels = (int64_t)a.b_tiles * ((a.L + 3) / 4) >= 4 * lc.num_cu ? 4 : 1;
     a.b_coef = a.b_tiles * ((a.L + a.coef_labels - 1) / a.coef_labels);
     const int64_t blocks = (int64_t)a.b_coef + a.b_stream + a.b_tiles + (a.nthreads + 255) / 256;

@@ -13,14 +13,15 @@
 //
 // Two forms.  k_pd_resident runs every iteration in one cooperative launch,
 // the tiles exchanging their borders, where the image fits one tile per
-// compute unit: 481 x 321 with 10 labels 25.4 -> 4.9 us per iteration, with 16
-// labels and a label cost 82 -> 9.9 us.  k_pd_tile serves larger images: it
+// compute unit: 481 x 321 with 10 labels 25.4 -> 4.1 to 4.9 us per iteration (by
+// the data: how often a wave's discs and simplex need their long way), with 16
+// labels and a label cost 82 -> 7.4 us.  k_pd_tile serves larger images: it
 // loads a 32 x 32 tile, runs S iterations (up to 8) and writes the pixels that
 // are still right; an iteration at x reads u_bar at x + 1, x + W and the new xi
 // at x - 1, x - W, so the valid square loses one pixel on each side per
 // iteration and a tile yields (32 - 2 S)^2 pixels.  1024 x 1024: 16 labels 175
-// -> 118 us, 3 labels 51 -> 22 us per iteration; with a label cost (16 labels)
-// 598 -> 341 us.  There the state's trip through HBM and the 1 tile per
+// -> 86 to 118 us by the data, 3 labels 51 -> 22 us per iteration; with a label cost
+// (16 labels) 598 -> 341 us.  There the state's trip through HBM and the 1 tile per
 // compute unit that 128 registers leave bound it.
 //
 // With a label cost the multipliers need sum_x mu of the whole image between
