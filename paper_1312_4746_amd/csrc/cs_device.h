@@ -117,7 +117,11 @@ struct ExactRun {
         return form ? v : 0.0;
     }
     // the zero patch that the wave's last group met, -1: none
-    __device__ __forceinline__ int64_t wave_zero() const { return __shfl(zero_pix, 63); }
+    __device__ __forceinline__ int64_t wave_zero() const {
+        const uint64_t z = (uint64_t)zero_pix;
+        return (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(z >> 32), 63) << 32 |
+                         (uint32_t)__builtin_amdgcn_readlane((uint32_t)z, 63));
+    }
 };
 
 // Per-row decision margin: the given absolute margin when >= 0, else the
